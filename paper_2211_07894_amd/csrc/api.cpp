@@ -49,6 +49,21 @@ lrdm_status begin(lrdm_ctx* ctx, size_t bytes) {
   return lrdm::ws_reserve(ctx, bytes + (1u << 20));
 }
 
+// begin() for a call whose projections prefer more partial sums than they need:
+// bytes(0) where the context can hold it, else (a workspace limit, a capture, no
+// memory) bytes(kLeanSplits).
+template <typename F>
+lrdm_status begin_sized(lrdm_ctx* ctx, F&& bytes) {
+  if (ctx) ctx->split_limit = 0;
+  const size_t want = bytes(0), least = bytes(lrdm::kLeanSplits);
+  lrdm_status st = begin(ctx, want);
+  if (st == LRDM_ENOMEM && least < want) {
+    ctx->split_limit = lrdm::kLeanSplits;
+    st = begin(ctx, least);
+  }
+  return st;
+}
+
 // Epilogue: in checking mode wait for the stream and turn device status words
 // into status codes.
 lrdm_status finish(lrdm_ctx* ctx, lrdm_status st) {
@@ -397,7 +412,7 @@ extern "C" lrdm_status lrdm_projected_perturbation(lrdm_ctx* ctx, const lrdm_gri
   LRDM_NONNULL(ctx, dV, "dV");
   LRDM_NONNULL(ctx, Hp, "Hp");
   const Grid3 g = make_grid3(grid);
-  lrdm_status st = begin(ctx, tn_bytes(N, g.M, r * nspin, prec));
+  lrdm_status st = begin_sized(ctx, [&](int sl) { return tn_bytes(N, g.M, r * nspin, prec, sl); });
   if (st != LRDM_OK) return st;
   return guarded(ctx, [&]() -> lrdm_status {
     hipError_t e;
@@ -638,9 +653,9 @@ hipError_t run_backward(lrdm_ctx* ctx, const Grid3& g, const T* Psi, const doubl
   return hipSuccess;
 }
 
-size_t backward_bytes(int N, int64_t M, int r, int ns, lrdm_prec prec) {
+size_t backward_bytes(int N, int64_t M, int r, int ns, lrdm_prec prec, int split_limit = 0) {
   const int batch = r * ns;
-  const size_t scratch = std::max({tn_bytes(N, M, batch, prec),
+  const size_t scratch = std::max({tn_bytes(N, M, batch, prec, split_limit),
                                    backproj_workspace_bytes(N, M, ns, batch, prec),
                                    adj_psi_workspace_bytes(N, M, ns, r, prec != LRDM_FP64),
                                    prec == LRDM_BF16X3 ? adj_psi_bf16x3_bytes(N, M, ns, r)
@@ -787,7 +802,7 @@ extern "C" lrdm_status subspace_rayleigh_ritz(lrdm_ctx* ctx, const lrdm_grid* gr
   LRDM_NONNULL(ctx, Psi, "Psi");
   LRDM_NONNULL(ctx, eps, "eps");
   const Grid3 g = make_grid3(grid);
-  lrdm_status st = begin(ctx, rr_workspace_bytes(N, g.M, prec));
+  lrdm_status st = begin_sized(ctx, [&](int sl) { return rr_workspace_bytes(N, g.M, prec, sl); });
   if (st != LRDM_OK) return st;
   return guarded(ctx, [&]() -> lrdm_status {
     if (prec == LRDM_FP64)
@@ -809,7 +824,8 @@ extern "C" lrdm_status subspace_rayleigh_ritz_bloch(lrdm_ctx* ctx, const lrdm_gr
   LRDM_NONNULL(ctx, Psi, "Psi");
   LRDM_NONNULL(ctx, eps, "eps");
   const Grid3 g = make_grid3(grid);
-  lrdm_status st = begin(ctx, rr_bloch_workspace_bytes(N, g.M, prec));
+  lrdm_status st =
+      begin_sized(ctx, [&](int sl) { return rr_bloch_workspace_bytes(N, g.M, prec, sl); });
   if (st != LRDM_OK) return st;
   const double kvec[3] = {kx, ky, kz};
   return guarded(ctx, [&]() -> lrdm_status {
@@ -833,7 +849,8 @@ extern "C" lrdm_status density_response(lrdm_ctx* ctx, const lrdm_grid* grid, co
   LRDM_NONNULL(ctx, dV, "dV");
   LRDM_NONNULL(ctx, drho, "drho");
   const Grid3 g = make_grid3(grid);
-  lrdm_status st = begin(ctx, response_bytes(N, g.M, r, occ->nspin, prec));
+  lrdm_status st =
+      begin_sized(ctx, [&](int sl) { return response_bytes(N, g.M, r, occ->nspin, prec, sl); });
   if (st != LRDM_OK) return st;
   return guarded(ctx, [&]() -> lrdm_status {
     hipError_t e = (prec == LRDM_FP64)
@@ -893,6 +910,10 @@ extern "C" lrdm_status density_response_noalloc(lrdm_ctx* ctx, const lrdm_grid* 
   int limit = 0;
   size_t need = response_bytes(N, g.M, r, ns, prec) + (1u << 20);
   if (need > cap) {
+    limit = kLeanSplits;
+    need = response_bytes(N, g.M, r, ns, prec, limit) + (1u << 20);
+  }
+  if (need > cap) {
     const int ntb = (N + 127) / 128;
     for (limit = tn_split_cap(ntb * (ntb + 1) / 2 * r * ns, g.M); limit > 1 && need > cap;
          limit /= 2)
@@ -925,11 +946,12 @@ extern "C" lrdm_status density_response_noalloc(lrdm_ctx* ctx, const lrdm_grid* 
 
 namespace {
 
-size_t response_bz_bytes(int N, int64_t M, int r, int ns, int nk, lrdm_prec prec) {
+size_t response_bz_bytes(int N, int64_t M, int r, int ns, int nk, lrdm_prec prec,
+                         int split_limit) {
   const int nsk = ns * nk, batch = r * nsk, N2 = 2 * N;
   return ws_align(8) + ws_align((size_t)r * 8) + 3 * ws_align((size_t)nsk * N * 8) +
          ws_align((size_t)nsk * N * N * 8) + 2 * ws_align((size_t)batch * M * 8) +
-         ws_align((size_t)batch * N2 * N2 * 8) + ws_align(tn_bytes(N2, M, batch, prec)) +
+         ws_align((size_t)batch * N2 * N2 * 8) + ws_align(tn_bytes(N2, M, batch, prec, split_limit)) +
          backproj_workspace_bytes(N2, M, nsk, batch, prec);
 }
 
@@ -981,7 +1003,8 @@ extern "C" lrdm_status density_response_bz(lrdm_ctx* ctx, const lrdm_grid* grid,
   LRDM_NONNULL(ctx, dV, "dV");
   LRDM_NONNULL(ctx, drho, "drho");
   const Grid3 g = make_grid3(grid);
-  lrdm_status st = begin(ctx, response_bz_bytes(N, g.M, r, occ->nspin, nk, prec));
+  lrdm_status st = begin_sized(
+      ctx, [&](int sl) { return response_bz_bytes(N, g.M, r, occ->nspin, nk, prec, sl); });
   if (st != LRDM_OK) return st;
   return guarded(ctx, [&]() -> lrdm_status {
     hipError_t e = (prec == LRDM_FP64)
@@ -1013,8 +1036,10 @@ lrdm_status residual_derivative_impl(lrdm_ctx* ctx, const lrdm_grid* grid, const
   const size_t ubytes = (size_t)r * ns * g.M * sizeof(double);
   if (overlaps(u, ubytes, t, ubytes)) return fail(ctx, LRDM_EINVAL, "u and t must not overlap");
   const size_t scratch = 2 * (size_t)r * g.M * sizeof(double);
-  lrdm_status st = begin(ctx, ws_align(ubytes) + ws_align(scratch) + hartree_workspace_bytes(g) +
-                                  response_bytes(N, g.M, r, ns, prec));
+  lrdm_status st = begin_sized(ctx, [&](int sl) {
+    return ws_align(ubytes) + ws_align(scratch) + hartree_workspace_bytes(g) +
+           response_bytes(N, g.M, r, ns, prec, sl);
+  });
   if (st != LRDM_OK) return st;
   return guarded(ctx, [&]() -> lrdm_status {
     double* dV = static_cast<double*>(ws_take(ctx, ubytes));
@@ -1075,7 +1100,8 @@ extern "C" lrdm_status density_response_backward(lrdm_ctx* ctx, const lrdm_grid*
     return fail(ctx, LRDM_EUNSUPPORTED,
                 "density_response_backward differentiates the exact Fermi-Dirac form only "
                 "(the context is set to the recursive expansion)");
-  lrdm_status st = begin(ctx, backward_bytes(N, g.M, r, ns, prec));
+  lrdm_status st =
+      begin_sized(ctx, [&](int sl) { return backward_bytes(N, g.M, r, ns, prec, sl); });
   if (st != LRDM_OK) return st;
   return guarded(ctx, [&]() -> lrdm_status {
     hipError_t e = (prec == LRDM_FP64)
@@ -1092,7 +1118,6 @@ extern "C" lrdm_status density_response_batched(lrdm_ctx* ctx, const lrdm_system
   if (nsys < 1 || nsys > 4096) return fail(ctx, LRDM_EINVAL, "nsys must be in [1, 4096]");
   LRDM_NONNULL(ctx, sys, "sys");
   LRDM_CHECK(ctx, check_prec(prec));
-  size_t total = 0;
   for (int s = 0; s < nsys; ++s) {
     const lrdm_system& y = sys[s];
     LRDM_CHECK(ctx, check_grid(&y.grid));
@@ -1103,9 +1128,14 @@ extern "C" lrdm_status density_response_batched(lrdm_ctx* ctx, const lrdm_system
     LRDM_NONNULL(ctx, y.eps, "sys[].eps");
     LRDM_NONNULL(ctx, y.dV, "sys[].dV");
     LRDM_NONNULL(ctx, y.drho, "sys[].drho");
-    total += ws_align(response_bytes(y.N, grid_points(&y.grid), y.r, y.occ.nspin, prec));
   }
-  lrdm_status st = begin(ctx, total);
+  lrdm_status st = begin_sized(ctx, [&](int sl) {
+    size_t total = 0;
+    for (int s = 0; s < nsys; ++s)
+      total += ws_align(response_bytes(sys[s].N, grid_points(&sys[s].grid), sys[s].r,
+                                       sys[s].occ.nspin, prec, sl));
+    return total;
+  });
   if (st != LRDM_OK) return st;
   if (prec == LRDM_FP32 && ctx->fermi_depth == 0) {
     // the systems' projections in one launch, then their back-projections in one
@@ -1471,9 +1501,10 @@ extern "C" lrdm_status lrdm_lowrank_step(lrdm_ctx* ctx, const lrdm_grid* grid, c
                        ws_align(sizeof(int)) + dots_workspace_bytes(K);
   const size_t pieces = prec == LRDM_BF16X3
       ? psi_pieces_p3_bytes(N, g.M, ns) + psi_pieces_pt3_bytes(N, g.M, ns) : 0;
-  const size_t bytes = small + 2 * ws_align(vb) + ws_align(2 * (size_t)g.M * 8) + pieces +
-                       hartree_workspace_bytes(g) + response_bytes(N, g.M, 1, ns, prec);
-  lrdm_status st = begin(ctx, bytes);
+  lrdm_status st = begin_sized(ctx, [&](int sl) {
+    return small + 2 * ws_align(vb) + ws_align(2 * (size_t)g.M * 8) + pieces +
+           hartree_workspace_bytes(g) + response_bytes(N, g.M, 1, ns, prec, sl);
+  });
   if (st != LRDM_OK) return st;
   return guarded(ctx, [&]() -> lrdm_status {
     return (prec == LRDM_FP64)
@@ -1522,11 +1553,12 @@ extern "C" lrdm_status lrdm_autotune(lrdm_ctx* ctx, const lrdm_grid* grid, int32
   const Grid3 g = make_grid3(grid);
   const int batch = r * nspin;
   const size_t el = prec_bytes(prec);
-  const size_t ws = std::max({tn_workspace_bytes(N, g.M, batch, prec),
-                              tn_workspace_bytes(N, g.M, nspin, prec),
-                              tn_workspace_bytes(N, g.M, 1, LRDM_FP64),
-                              backproj_workspace_bytes(N, g.M, nspin, batch, prec)});
-  lrdm_status st = begin(ctx, ws);
+  lrdm_status st = begin_sized(ctx, [&](int sl) {
+    return std::max({tn_workspace_bytes(N, g.M, batch, prec, sl),
+                     tn_workspace_bytes(N, g.M, nspin, prec, sl),
+                     tn_workspace_bytes(N, g.M, 1, LRDM_FP64, sl),
+                     backproj_workspace_bytes(N, g.M, nspin, batch, prec)});
+  });
   if (st != LRDM_OK) return st;
   void* A = nullptr;
   double* w = nullptr;

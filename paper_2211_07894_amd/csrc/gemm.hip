@@ -497,7 +497,8 @@ size_t tn_part_bytes(int N, int64_t M, int batch, int split_limit) {
   const int ntiles = ntb * (ntb + 1) / 2;
   int ns = tn_split_cap(ntiles * batch, M);
   if (split_limit > 0) ns = std::min(ns, split_limit);
-  return (size_t)batch * ns * ntiles * BT * BT * sizeof(double);
+  const size_t tiles = (size_t)batch * ns * ntiles * BT * BT * sizeof(double);
+  return split_limit > 0 ? tiles : std::max(tiles, tn_direct_bytes(N, M, batch));
 }
 
 int tn_split_count(const lrdm_ctx* ctx, int N, int64_t M, int batch, int arith, bool weighted) {
@@ -530,6 +531,16 @@ hipError_t launch_tn_sym_f64(lrdm_ctx* ctx, const SA* A, const SB* B, const doub
   int64_t kchunk = (M + ns - 1) / ns;
   kchunk = (kchunk + KT - 1) / KT * KT;
   double* part = static_cast<double*>(ws_take(ctx, tn_part_bytes(N, M, batch, ctx->split_limit)));
+  if (tn_direct_ok(N, M, batch)) {
+    // the autotuned count, relative to the default one, scales the number of ranges
+    const TnDirectPlan p = tn_direct_plan(N, M, batch, tn_part_bytes(N, M, batch, ctx->split_limit),
+                                          (double)ns / tn_splits(ntiles * batch, M));
+    if (B)
+      return launch_tn_direct<SA, SB>(ctx, p, A, B, w, w_stride, N, M, nspin, batch, part, H, active,
+                                      static_cast<const void*>(A) == static_cast<const void*>(B));
+    return launch_tn_direct<SA, SA>(ctx, p, A, A, w, w_stride, N, M, nspin, batch, part, H, active,
+                                    true);
+  }
   const unsigned grd = (unsigned)(ntiles * ns * batch);
   {
     ProfScope prof(ctx, w ? "proj" : "gram");

@@ -1988,7 +1988,7 @@ hipError_t launch_tn_sym_fused(lrdm_ctx* ctx, const FusedProjItem* items, int n)
                                     it.batch, LRDM_FP32, it.H, it.active));
       continue;
     }
-    parts[k] = static_cast<double*>(ws_take(ctx, tn_part_bytes(it.N, it.M, it.batch)));
+    parts[k] = static_cast<double*>(ws_take(ctx, tn_part_bytes(it.N, it.M, it.batch, ctx->split_limit)));
     splits[k] = ns;
     const int s = t.nsys++;
     const int used = ntiles * ns * it.batch;

@@ -43,7 +43,8 @@ struct lrdm_ctx {
   int eigh_max_sweeps = 40;  // block Jacobi sweeps before the eigensolver gives up
   double block_tau = 1e-14;  // response blocks with max |F| below tau max |F| are skipped
   int bp_variant = 1;        // BF16X3 back-projection layout (BP_VAR_*)
-  int split_limit = 0;       // > 0: cap on the projection's K-split count (allocation-free calls)
+  int split_limit = 0;       // > 0: cap on the projection's K-split count (allocation-free calls,
+                             // kLeanSplits under a workspace limit)
   lrdm_psi_pieces pieces;
   // K-split counts of the projection contraction chosen by lrdm_autotune, keyed by
   // (N, M, batch, arithmetic, weighted)
@@ -215,7 +216,9 @@ hipError_t launch_recursive_multiplier(lrdm_ctx* ctx, const double* eps, const d
 // only the upper triangle is formed and mirrored (the callers' products are
 // symmetric).  B == nullptr means B = A; w == nullptr means w = 1.
 // A, B: nspin blocks of [N][M].
-// split_limit > 0 caps the K-split count (and with it the partial sums' size).
+// split_limit > 0 caps the K-split count (and with it the partial sums' size);
+// kLeanSplits keeps it and drops only the extra partial sums of tn_direct.hip.
+constexpr int kLeanSplits = 1 << 30;
 size_t tn_workspace_bytes(int N, int64_t M, int batch, lrdm_prec prec, int split_limit = 0);
 size_t tn_split_bytes(int N, int64_t M, lrdm_prec prec);
 size_t tn_part_bytes(int N, int64_t M, int batch, int split_limit = 0);
@@ -272,6 +275,25 @@ template <typename SA, typename SB>
 hipError_t launch_tn_sym_f64(lrdm_ctx* ctx, const SA* A, const SB* B, const double* w,
                              int64_t w_stride, int N, int64_t M, int nspin, int batch, double* H,
                              const unsigned char* active = nullptr);
+
+// The FP64 projection on small tiles, split along the points (tn_direct.hip): where
+// it is used, its preferred bytes of partial sums (0 where it is not used), and the
+// tile edge, number of point ranges and their length within a budget of such bytes.
+struct TnDirectPlan {
+  int tile;
+  int nsplit;
+  int64_t kchunk;
+};
+bool tn_direct_ok(int N, int64_t M, int batch);
+size_t tn_direct_bytes(int N, int64_t M, int batch);
+// scale: factor on the number of ranges (the autotuner's choice over its default).
+TnDirectPlan tn_direct_plan(int N, int64_t M, int batch, size_t budget, double scale);
+// part: the budget's partial sums; same: A and B are one block.
+template <typename SA, typename SB>
+hipError_t launch_tn_direct(lrdm_ctx* ctx, const TnDirectPlan& p, const SA* A, const SB* B,
+                            const double* w, int64_t w_stride, int N, int64_t M, int nspin,
+                            int batch, double* part, double* H, const unsigned char* active,
+                            bool same);
 
 // The response's block mask (blocks.h): active [nspin][ntb][ntb] from the
 // multiplier F [nspin][N][N]; tmax: nspin * ntb * ntb doubles of scratch.
@@ -375,13 +397,13 @@ lrdm_status sym_eigh(lrdm_ctx* ctx, const double* S, int lda, int N, const doubl
 template <typename T>
 lrdm_status rayleigh_ritz(lrdm_ctx* ctx, const Grid3& g, const double* V, T* Psi, int N,
                           lrdm_prec prec, double* eps);
-size_t rr_workspace_bytes(int N, int64_t M, lrdm_prec prec);
+size_t rr_workspace_bytes(int N, int64_t M, lrdm_prec prec, int split_limit = 0);
 // Rayleigh-Ritz of the Bloch Hamiltonian H_k on N complex states [2][N][M]
 // (real parts, then imaginary parts) stored as T; FP64 arithmetic.
 template <typename T>
 lrdm_status rayleigh_ritz_bloch(lrdm_ctx* ctx, const Grid3& g, const double* V,
                                 const double kvec[3], T* Psi, int N, double* eps);
-size_t rr_bloch_workspace_bytes(int N, int64_t M, lrdm_prec prec);
+size_t rr_bloch_workspace_bytes(int N, int64_t M, lrdm_prec prec, int split_limit = 0);
 
 // Hartree kernel (poisson.hip): dV[k] = 4 pi (-Lap_h)^{-1} (sum_c u[k][c]) for k < r,
 // written to every channel slot of dV when nspin_out > 1.

@@ -538,7 +538,7 @@ lrdm_status sym_eigh(lrdm_ctx* ctx, const double* S, int lda, int N, const doubl
   return LRDM_OK;
 }
 
-size_t rr_workspace_bytes(int N, int64_t M, lrdm_prec prec) {
+size_t rr_workspace_bytes(int N, int64_t M, lrdm_prec prec, int split_limit) {
   const int Np = ((N + JS - 1) / JS) * JS;
   const int nb = Np / JB;
   const size_t s = prec == LRDM_FP64 ? sizeof(double) : sizeof(float);
@@ -552,7 +552,7 @@ size_t rr_workspace_bytes(int N, int64_t M, lrdm_prec prec) {
   inner = std::max(inner, 2 * ws_align((size_t)Np * Np * sizeof(double)) +
                               ws_align((size_t)(nb / 2) * JS * JS * 8) + ws_align(256) +
                               ws_align((size_t)Np * 4) + ws_align(kFrobBlocks * sizeof(double)));
-  inner = std::max(inner, ws_align(tn_workspace_bytes(N, M, 1, prec)));
+  inner = std::max(inner, ws_align(tn_workspace_bytes(N, M, 1, prec, split_limit)));
   if (prec == LRDM_BF16X3) inner = std::max(inner, rotate_bf16x3_bytes(N, M));
   return b + inner;
 }
@@ -1018,7 +1018,7 @@ __global__ void cluster_combine_kernel(const T* __restrict__ R, const cplx* __re
 
 }  // namespace
 
-size_t rr_bloch_workspace_bytes(int N, int64_t M, lrdm_prec prec) {
+size_t rr_bloch_workspace_bytes(int N, int64_t M, lrdm_prec prec, int split_limit) {
   const int n2 = 2 * N;
   const int Np = ((n2 + JS - 1) / JS) * JS;
   const int nb = Np / JB;
@@ -1035,7 +1035,7 @@ size_t rr_bloch_workspace_bytes(int N, int64_t M, lrdm_prec prec) {
   inner = std::max(inner, 2 * ws_align((size_t)Np * Np * sizeof(double)) +
                               ws_align((size_t)(nb / 2) * JS * JS * 8) + ws_align(256) +
                               ws_align((size_t)Np * 4) + ws_align(kFrobBlocks * sizeof(double)));
-  inner = std::max(inner, ws_align(tn_workspace_bytes(n2, 2 * M, 1, prec)));
+  inner = std::max(inner, ws_align(tn_workspace_bytes(n2, 2 * M, 1, prec, split_limit)));
   return b + inner;
 }
 
