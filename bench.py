@@ -183,7 +183,7 @@ def main():
             log(f"form {form} unavailable: {ex}")
             continue
         ctx.profile(True)
-        for k in ["cheb_step", "cheb_pair", "cheb_triple", "hpsi", "proj", "gram", "backproj", "nn", "eigh", "chol", "jac_sweep", "jac_solve", "jac_update", "hartree"]:
+        for k in ["cheb_step", "cheb_sweep", "cheb_lds", "hpsi", "proj", "gram", "backproj", "nn", "eigh", "chol", "jac_sweep", "jac_solve", "jac_update", "hartree"]:
             ctx.profile_read(k)
         torch.cuda.synchronize()
         t_start = time.perf_counter()
@@ -193,7 +193,7 @@ def main():
         elapsed = time.perf_counter() - t_start
         ctx.profile(False)
         kern = {k: ctx.profile_read(k) for k in
-                ["cheb_step", "cheb_pair", "cheb_triple", "hpsi", "proj", "gram", "backproj", "nn", "eigh", "chol", "jac_sweep", "jac_solve", "jac_update", "hartree"]}
+                ["cheb_step", "cheb_sweep", "cheb_lds", "hpsi", "proj", "gram", "backproj", "nn", "eigh", "chol", "jac_sweep", "jac_solve", "jac_update", "hartree"]}
         ms_step = 1e3 * elapsed / args.steps
         # response only (r directions on this form's Ritz pairs): r / T_resp
         torch.cuda.synchronize()
@@ -333,13 +333,11 @@ def main():
         # algorithmic work per launch, the method's own: the projection H' = Psi^T
         # diag(dV) Psi and the back-projection sum_ij Psi_i Gamma_ij Psi_j are
         # symmetric in (i, j), M N^2 flops per direction each (the dense
-        # equivalent, 2 M N^2, is reported beside it); a filter step moves 3 M N s
-        # bytes, two or three steps in one sweep 4 M N s bytes
+        # equivalent, 2 M N^2, is reported beside it); a single filter step
+        # moves 3 M N s bytes
         "backproj": ("mfma", r * 1.0 * M * N * N),
         "proj": ("mfma", r * 1.0 * M * N * N),
         "cheb_step": ("hbm", 3.0 * M * N * s_bytes + 8.0 * M),
-        "cheb_pair": ("hbm", 4.0 * M * N * s_bytes + 8.0 * M),
-        "cheb_triple": ("hbm", 4.0 * M * N * s_bytes + 8.0 * M),
     }
     dense_equiv = {"backproj": r * (2.0 * M * N * N + 2.0 * M * N), "proj": r * 2.0 * M * N * N}
     dom = max(per_launch, key=lambda k: hr["kernels"][k][0])

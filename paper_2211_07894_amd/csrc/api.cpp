@@ -449,13 +449,24 @@ namespace {
 
 template <typename T>
 hipError_t run_filter(lrdm_ctx* ctx, const Grid3& g, const double* V, const T* X, T* Y, int N,
-                      int degree, double a, double b, double a0) {
-  T* W = static_cast<T*>(ws_take(ctx, (size_t)g.M * N * sizeof(T)));
+                      int degree, double a, double b, double a0, int64_t room) {
   const double e = (b - a) / 2.0, c0 = (b + a) / 2.0;
   const double sigma1 = e / (a0 - c0);
-  // the vectorised step reads V in the storage type
+  // Y_{k+1} = alpha[k] (H - c0) Y_k + beta[k] Y_{k-1}
+  std::vector<double> alpha(degree), beta(degree);
+  alpha[0] = sigma1 / e;
+  beta[0] = 0.0;
+  double sigma = sigma1;
+  for (int k = 1; k < degree; ++k) {
+    const double s1 = 1.0 / (2.0 / sigma1 - sigma);
+    alpha[k] = 2.0 * s1 / e;
+    beta[k] = -sigma * s1;
+    sigma = s1;
+  }
+  // the vectorised forms read V in the storage type
   auto aligned = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-  const bool vec = cheb_vec_ok<T>(g) && aligned(X) && aligned(Y) && aligned(W);
+  const bool vec = cheb_vec_ok<T>(g) && aligned(X) && aligned(Y) &&
+                   (sizeof(T) == sizeof(float) || aligned(V));
   const T* Vt = nullptr;
   if (vec) {
     if constexpr (sizeof(T) == sizeof(double)) {
@@ -466,47 +477,33 @@ hipError_t run_filter(lrdm_ctx* ctx, const Grid3& g, const double* V, const T* X
       Vt = Vf;
     }
   }
-  auto step = [&](const T* yin, const T* yold, T* yout, double alpha, double beta) {
-    return vec ? launch_cheb_step_vec<T>(ctx, g, Vt, yin, yold, yout, N, alpha, c0, beta)
-               : launch_cheb_step<T>(ctx, g, V, yin, yold, yout, N, alpha, c0, beta);
+  const ChebPlan plan = vec ? cheb_plan<T>(g, N, degree, room) : ChebPlan{};
+  if (plan.kind == ChebPlan::kLds) return launch_cheb_lds<T>(ctx, g, Vt, X, Y, N, c0, alpha, beta);
+  T* W = static_cast<T*>(ws_take(ctx, (size_t)plan.states(N) * g.M * sizeof(T)));
+  if (plan.kind == ChebPlan::kSweeps)
+    return launch_cheb_sweeps<T>(ctx, plan, g, Vt, X, Y, W, N, c0, alpha, beta);
+  auto step = [&](int k, const T* yin, const T* yold, T* yout) {
+    return vec ? launch_cheb_step_vec<T>(ctx, g, Vt, yin, yold, yout, N, alpha[k], c0, beta[k])
+               : launch_cheb_step<T>(ctx, g, V, yin, yold, yout, N, alpha[k], c0, beta[k]);
   };
-  // Y_k lands in bufA for odd k and bufB for even k; choose so that Y_c is in Y.
+  // Y_k lands in bufA for odd k and bufB for even k, so that Y_c is in Y; Y_k
+  // overwrites Y_{k-2} (k > 2)
   T* bufA = (degree % 2 == 1) ? Y : W;
   T* bufB = (degree % 2 == 1) ? W : Y;
-  LRDM_HIP(step(X, nullptr, bufA, sigma1 / e, 0.0));
-  // steps k .. k+2 (or k, k+1) in one sweep where the vectorised form can own
-  // whole z columns
-  const bool pair = vec && cheb_pair_ok<T>(g, N);
-  const bool triple = vec && cheb_triple_ok<T>(g, N);
-  double sigma = sigma1;
-  for (int k = 2; k <= degree;) {
-    T* ykm1 = (k % 2 == 0) ? bufA : bufB;         // Y_{k-1}
-    const T* ykm2 = (k == 2) ? X : ((k % 2 == 0) ? bufB : bufA);  // Y_{k-2}
-    T* out = (k % 2 == 1) ? bufA : bufB;          // overwrites Y_{k-2} (k > 2)
-    const double s1 = 1.0 / (2.0 / sigma1 - sigma);
-    if (triple && k + 2 <= degree) {
-      const double s2 = 1.0 / (2.0 / sigma1 - s1);
-      const double s3 = 1.0 / (2.0 / sigma1 - s2);
-      const double a[3] = {2.0 * s1 / e, 2.0 * s2 / e, 2.0 * s3 / e};
-      const double b[3] = {-sigma * s1, -s1 * s2, -s2 * s3};
-      // Y_{k+1} overwrites Y_{k-1}, Y_{k+2} overwrites Y_{k-2}; Y_k stays on chip
-      LRDM_HIP(launch_cheb_triple_vec<T>(ctx, g, Vt, ykm2, ykm1, ykm1, out, N, c0, a, b));
-      sigma = s3;
-      k += 3;
-    } else if (pair && k + 1 <= degree) {
-      const double s2 = 1.0 / (2.0 / sigma1 - s1);
-      // Y_{k+1} overwrites Y_{k-1}
-      LRDM_HIP(launch_cheb_pair_vec<T>(ctx, g, Vt, ykm2, ykm1, out, ykm1, N, c0,
-                                       2.0 * s1 / e, -sigma * s1, 2.0 * s2 / e, -s1 * s2));
-      sigma = s2;
-      k += 2;
-    } else {
-      LRDM_HIP(step(ykm1, ykm2, out, 2.0 * s1 / e, -sigma * s1));
-      sigma = s1;
-      k += 1;
-    }
+  LRDM_HIP(step(0, X, nullptr, bufA));
+  for (int k = 2; k <= degree; ++k) {
+    const T* ykm1 = (k % 2 == 0) ? bufA : bufB;
+    const T* ykm2 = (k == 2) ? X : ((k % 2 == 0) ? bufB : bufA);
+    LRDM_HIP(step(k - 1, ykm1, ykm2, (k % 2 == 1) ? bufA : bufB));
   }
   return hipSuccess;
+}
+
+// States of workspace a filter wants (room 0), or has room for under a limit.
+int64_t filter_states(const Grid3& g, int N, lrdm_prec prec, int degree, int64_t room) {
+  const ChebPlan p = prec == LRDM_FP64 ? cheb_plan<double>(g, N, degree, room)
+                                       : cheb_plan<float>(g, N, degree, room);
+  return std::max<int64_t>(N, p.states(N));
 }
 
 // The Fermi-level quantities a response needs: mu, f, 1 - f, the multiplier's
@@ -690,14 +687,20 @@ extern "C" lrdm_status chfsi_filter(lrdm_ctx* ctx, const lrdm_grid* grid, const 
   const Grid3 g = make_grid3(grid);
   const size_t blk = (size_t)g.M * N * prec_bytes(prec);
   if (overlaps(X, blk, Y, blk)) return fail(ctx, LRDM_EINVAL, "X and Y must not overlap");
-  lrdm_status st = begin(ctx, ws_align(blk) + ws_align((size_t)g.M * sizeof(float)));
+  const size_t state = (size_t)g.M * prec_bytes(prec);
+  int64_t room = 0;                    // states of workspace: the plan's, or N under a limit
+  lrdm_status st = begin_sized(ctx, [&](int sl) {
+    return ws_align((sl ? N : filter_states(g, N, prec, degree, 0)) * state) +
+           ws_align((size_t)g.M * sizeof(float));
+  });
+  if (st == LRDM_OK && ctx->split_limit) room = N;
   if (st != LRDM_OK) return st;
   return guarded(ctx, [&]() -> lrdm_status {
     hipError_t e = (prec == LRDM_FP64)
         ? run_filter<double>(ctx, g, V, static_cast<const double*>(X), static_cast<double*>(Y), N,
-                             degree, a, b, a0)
+                             degree, a, b, a0, room)
         : run_filter<float>(ctx, g, V, static_cast<const float*>(X), static_cast<float*>(Y), N,
-                            degree, a, b, a0);
+                            degree, a, b, a0, room);
     return e == hipSuccess ? LRDM_OK : fail_hip(ctx, "chfsi_filter", e);
   });
 }

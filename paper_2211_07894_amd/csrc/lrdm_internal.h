@@ -118,28 +118,28 @@ template <typename T>
 hipError_t launch_cheb_step_vec(lrdm_ctx* ctx, const Grid3& g, const T* Vt, const T* Yin,
                                 const T* Yold, T* Yout, int N, double alpha, double c0,
                                 double beta);
-// Two consecutive steps in one sweep (vectorised form):
-//   Yc = a1 (H - c0) Yb + b1 Ya,   Yd = a2 (H - c0) Yc + b2 Yb,
-// each element as launch_cheb_step_vec forms it.  Usable when cheb_pair_ok(g, N):
-// the vectorised form applies with at most 1024 groups per plane, nz >= 4, and a
-// block can own a whole z column.
-// Yc may equal Ya and Yd may equal Yb.
+// The form a filter of `degree` steps takes (stencil.hip).  room: states the
+// workspace can hold (0: as many as the plan wants; ChebPlan::states says).
+struct ChebPlan {
+  enum { kSteps = 0, kLds = 1, kSweeps = 2 };
+  int kind = kSteps;
+  int stages = 0;     // kSweeps: steps per sweep, states per batch, planes per run
+  int batch = 0;
+  int zrun = 0;
+  int64_t states(int N) const { return kind == kSteps ? N : (kind == kSweeps ? 3 * (int64_t)batch : 0); }
+};
 template <typename T>
-bool cheb_pair_ok(const Grid3& g, int N);
+ChebPlan cheb_plan(const Grid3& g, int N, int degree, int64_t room);
+// Y = the recurrence Y_{k+1} = a[k] (H - c0) Y_k + b[k] Y_{k-1} (b[0] = 0) from
+// Y_0 = X over all of a and b, with V in the storage type (Vt) and 16-byte aligned
+// blocks: whole states in LDS, or sweeps with W of plan.states(N) states.
 template <typename T>
-hipError_t launch_cheb_pair_vec(lrdm_ctx* ctx, const Grid3& g, const T* Vt, const T* Ya,
-                                const T* Yb, T* Yc, T* Yd, int N, double c0, double a1, double b1,
-                                double a2, double b2);
-// Three consecutive steps in one sweep: Y_{k+s} = a[s-1] (H - c0) Y_{k+s-1} +
-// b[s-1] Y_{k+s-2} for s = 1, 2, 3 with Ya = Y_{k-1}, Yb = Y_k; writes Y_{k+2} to
-// Yp and Y_{k+3} to Yq only.  Usable when cheb_triple_ok(g, N): cheb_pair_ok and
-// nz >= 8.  Yp and Yq may be the buffers of Ya and Yb, either way round.
+hipError_t launch_cheb_lds(lrdm_ctx* ctx, const Grid3& g, const T* Vt, const T* X, T* Y, int N,
+                           double c0, const std::vector<double>& a, const std::vector<double>& b);
 template <typename T>
-bool cheb_triple_ok(const Grid3& g, int N);
-template <typename T>
-hipError_t launch_cheb_triple_vec(lrdm_ctx* ctx, const Grid3& g, const T* Vt, const T* Ya,
-                                  const T* Yb, T* Yp, T* Yq, int N, double c0, const double* a,
-                                  const double* b);
+hipError_t launch_cheb_sweeps(lrdm_ctx* ctx, const ChebPlan& plan, const Grid3& g, const T* Vt,
+                              const T* X, T* Y, T* W, int N, double c0,
+                              const std::vector<double>& a, const std::vector<double>& b);
 // b[i] = (float)a[i], i < n.
 hipError_t launch_to_float(lrdm_ctx* ctx, const double* a, int64_t n, float* b);
 

@@ -20,11 +20,13 @@
 // fewer registers than the scalar form.  Yout may be the same buffer as Yold
 // (each element is read, then written, by the same thread).
 //
-// Where a block owns a whole z column (N of 1024 and more, or short columns)
-// three (or two) consecutive steps run in one sweep: each intermediate block is
-// formed plane by plane and used by the next step while its planes are still in
-// registers and LDS, and only the last two blocks (the next sweep's inputs) are
-// written, so three steps move 4 M N s bytes instead of 9.
+// A filter seldom takes single steps: a state that fits in LDS takes the whole filter
+// in one workgroup (cheb_lds_kernel), and else up to five consecutive steps run in
+// one sweep (cheb_sweep_kernel): each intermediate block is formed plane by plane and
+// used by the next step while its planes are in registers and LDS, and only the last
+// two blocks are written, so S steps move 4 M N s bytes instead of 3 S M N s.
+#include <algorithm>
+
 #include "lrdm_internal.h"
 
 namespace lrdm {
@@ -293,299 +295,234 @@ hipError_t launch_vec(lrdm_ctx* ctx, const char* scope, const Grid3& g, const T*
   return hipGetLastError();
 }
 
-// One group of W points of a recurrence step: alpha (H - c0) y + beta o at the
-// group gi of the plane pl (LDS, for the x and y neighbours), with c the group's
-// own values and pz, nzv its values on the planes below and above.
-template <typename T, int W>
-__device__ inline vec_t<T, W> step_group(const vec_t<T, W>* pl, int gi, int G, int nx, int ny,
-                                         int nxg, vec_t<T, W> c, vec_t<T, W> pz, vec_t<T, W> nzv,
-                                         vec_t<T, W> vv, vec_t<T, W> o, T wx, T wy, T wz,
-                                         T dshift, T alpha, T beta) {
-  const T* pls = reinterpret_cast<const T*>(pl);
-  const int y = gi / nxg, x0 = (gi - y * nxg) * W;
-  const int q = W * gi;
-  const vec_t<T, W> ym = pl[y == 0 ? gi + G - nxg : gi - nxg];
-  const vec_t<T, W> yp = pl[y == ny - 1 ? gi - G + nxg : gi + nxg];
-  const T left = pls[x0 == 0 ? q + nx - 1 : q - 1];
-  const T right = pls[x0 + W == nx ? q + W - nx : q + W];
-  vec_t<T, W> out;
-#pragma unroll
-  for (int e = 0; e < W; ++e) {
-    const T xl = e == 0 ? left : c[e == 0 ? 0 : e - 1];
-    const T xr = e == W - 1 ? right : c[e == W - 1 ? 0 : e + 1];
-    const T hy = wx * (xl + xr) + wy * (ym[e] + yp[e]) + wz * (pz[e] + nzv[e]) +
-                 (vv[e] + dshift) * c[e];
-    out[e] = alpha * hy + beta * o[e];
-  }
-  return out;
-}
-
-// Two recurrence steps in one sweep, for a block that owns the whole z column of
-// one vector (periodic in z, nz >= 4):
-//   C = a1 (H - c0) B + b1 A,   D = a2 (H - c0) C + b2 B
-// (A, B, C, D = Y_{k-1}, Y_k, Y_{k+1}, Y_{k+2}).  Each element is computed as
-// the single step computes it; C never makes the round trip through HBM before
-// D uses it, so the pair moves 4 M N s bytes instead of 6.  C may be the buffer
-// of A and D that of B: every element of A and B that a thread reads is read by
-// that thread before it writes the same element of C or D, and A on the planes
-// nz-1 and 0 (C written there first) and B on 0 .. 2 are never read again.
-// At plane z the sweep forms C(z+1) (from B(z), B(z+1), B(z+2)) and D(z) (from
-// C(z-1), C(z), C(z+1)); C(nz-1) and C(0), which close the period, are formed
-// before the sweep and kept in registers.  LDS holds the planes B(z+1) and C(z),
-// double-buffered: [2 buffers][B, C][G groups].
-template <typename T, int Q>
-__global__ __launch_bounds__(1024) void cheb_pair_kernel(const T* Ya, const T* Yb, T* Yc, T* Yd,
-                                                        const T* __restrict__ Vt, int nx, int ny,
-                                                        int nz, T wx, T wy, T wz, T dshift, T a1,
-                                                        T b1, T a2, T b2) {
-  constexpr int W = 16 / sizeof(T);
-  using V = vec_t<T, W>;
-  extern __shared__ unsigned char smem_raw[];
-  V* lds = reinterpret_cast<V*>(smem_raw);
-  const int P = nx * ny, G = P / W, nxg = nx / W;
-  const int64_t base = (int64_t)blockIdx.x * G * nz;
-  const V* A = reinterpret_cast<const V*>(Ya) + base;
-  const V* B = reinterpret_cast<const V*>(Yb) + base;
-  V* C = reinterpret_cast<V*>(Yc) + base;
-  V* D = reinterpret_cast<V*>(Yd) + base;
-  const V* vg = reinterpret_cast<const V*>(Vt);
-  const V zero = V(T(0));
-  const int zl = nz - 1;
-  V b0[Q], b1v[Q], b2v[Q], av[Q], vc[Q], vd[Q], cm[Q], cc[Q], cl[Q], cf[Q];
-  // C(nz-1) and C(0): B planes nz-2, nz-1, 0, 1 and A, V on nz-1 and 0
-  {
-    V bm2[Q], bm1[Q];
-#pragma unroll
-    for (int j = 0; j < Q; ++j) {
-      const int gi = threadIdx.x + j * blockDim.x;
-      bm2[j] = bm1[j] = b0[j] = b1v[j] = zero;
-      if (gi < G) {
-        bm2[j] = B[(int64_t)(zl - 1) * G + gi];
-        bm1[j] = B[(int64_t)zl * G + gi];
-        b0[j] = B[gi];
-        b1v[j] = B[(int64_t)G + gi];
-        lds[gi] = bm1[j];              // buffer 0, B slot: plane nz-1
-        lds[2 * G + gi] = b0[j];       // buffer 1, B slot: plane 0
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int j = 0; j < Q; ++j) {
-      const int gi = threadIdx.x + j * blockDim.x;
-      cl[j] = cf[j] = zero;
-      if (gi < G) {
-        const V al = A[(int64_t)zl * G + gi], a0 = A[gi];
-        const V vl = vg[(int64_t)zl * G + gi], v0 = vg[gi];
-        cl[j] = step_group<T, W>(lds, gi, G, nx, ny, nxg, bm1[j], bm2[j], b0[j], vl, al, wx, wy,
-                                 wz, dshift, a1, b1);
-        cf[j] = step_group<T, W>(lds + 2 * G, gi, G, nx, ny, nxg, b0[j], bm1[j], b1v[j], v0, a0,
-                                 wx, wy, wz, dshift, a1, b1);
-        C[(int64_t)zl * G + gi] = cl[j];
-        C[gi] = cf[j];
-      }
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int j = 0; j < Q; ++j) {
-    const int gi = threadIdx.x + j * blockDim.x;
-    b2v[j] = av[j] = vc[j] = vd[j] = zero;
-    if (gi < G) {
-      b2v[j] = B[(int64_t)2 * G + gi];
-      av[j] = A[(int64_t)G + gi];
-      vd[j] = vg[gi];
-      vc[j] = vg[(int64_t)G + gi];
-    }
-    cm[j] = cl[j];
-    cc[j] = cf[j];
-  }
-  for (int z = 0; z < nz; ++z) {
-    V* lb = lds + (z & 1) * 2 * G;
-    V* lc = lb + G;
-#pragma unroll
-    for (int j = 0; j < Q; ++j) {
-      const int gi = threadIdx.x + j * blockDim.x;
-      if (gi < G) {
-        lb[gi] = b1v[j];
-        lc[gi] = cc[j];
-      }
-    }
-    __syncthreads();
-    // operands of the next plane, issued before this plane's arithmetic: B(z+3)
-    // and A(z+2) while C(z+2) is still to be formed, V(z+2) while z+2 < nz
-    const bool nextc = z + 2 <= nz - 2;
-    V nb[Q], na[Q], nv[Q];
-#pragma unroll
-    for (int j = 0; j < Q; ++j) {
-      const int gi = threadIdx.x + j * blockDim.x;
-      nb[j] = na[j] = nv[j] = zero;
-      if (gi < G) {
-        if (nextc) {
-          nb[j] = B[(int64_t)(z + 3) * G + gi];
-          na[j] = A[(int64_t)(z + 2) * G + gi];
-        }
-        if (z + 2 < nz) nv[j] = vg[(int64_t)(z + 2) * G + gi];
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < Q; ++j) {
-      const int gi = threadIdx.x + j * blockDim.x;
-      if (gi >= G) continue;
-      V cn;
-      if (z + 1 <= nz - 2) {
-        cn = step_group<T, W>(lb, gi, G, nx, ny, nxg, b1v[j], b0[j], b2v[j], vc[j], av[j], wx, wy,
-                              wz, dshift, a1, b1);
-        C[(int64_t)(z + 1) * G + gi] = cn;
-      } else {
-        cn = (z + 1 == zl) ? cl[j] : cf[j];
-      }
-      D[(int64_t)z * G + gi] = step_group<T, W>(lc, gi, G, nx, ny, nxg, cc[j], cm[j], cn, vd[j],
-                                                b0[j], wx, wy, wz, dshift, a2, b2);
-      cm[j] = cc[j];
-      cc[j] = cn;
-    }
-#pragma unroll
-    for (int j = 0; j < Q; ++j) {
-      b0[j] = b1v[j];
-      b1v[j] = b2v[j];
-      b2v[j] = nb[j];
-      av[j] = na[j];
-      vd[j] = vc[j];
-      vc[j] = nv[j];
-    }
-  }
-}
-
 template <typename T, int S>
 struct ChebCoef {
   T a[S], b[S];
 };
 
-// S recurrence steps in one sweep, for a block that owns the whole z column of
-// one vector (periodic in z, nz >= 2 S + 2).  Stage 0 is Y_k (Yb), stage -1 is
-// Y_{k-1} (Ya); stage s = 1 .. S is Y_{k+s} = a_s (H - c0) Y_{k+s-1} + b_s Y_{k+s-2},
-// each element formed as the single step forms it.  Only the last two stages are
-// written (stage S-1 to Yp, stage S to Yq; they are the next group's inputs), so
-// S steps move 4 M N s bytes.  Yp and Yq may be the buffers of Ya and Yb (either
-// way round): a thread reads each element of Ya and Yb before it writes the same
-// element of Yp or Yq, and the planes written first are never read again.
-// At step h of the sweep stage s is formed on plane h + S - s from stage s-1 on
-// planes h + S - s - 1 .. h + S - s + 1 (registers for z, an LDS plane for x and
-// y) and stage s-2 on its own plane.  The planes that close the period (stage s on
-// nz - (S - s) .. nz - 1 and 0 .. S - s - 1) are formed before the sweep and kept
-// in registers.  LDS: [2 buffers][S planes][G groups].
-template <typename T, int S>
-__global__ __launch_bounds__(1024) void cheb_multi_kernel(const T* Ya, const T* Yb, T* Yp, T* Yq,
-                                                         const T* __restrict__ Vt, int nx, int ny,
-                                                         int nz, T wx, T wy, T wz, T dshift,
-                                                         ChebCoef<T, S> cf) {
+// The whole filter of one state in one workgroup, for states that fit in LDS: Y_k
+// of every point in LDS for the x and y neighbours, Y_k and Y_{k-1} of the
+// thread's own points in registers, so that a state is read once and written once.
+// Thread t owns group t % G of the plane on the ZP planes from (t / G) ZP (ZP divides nz; the z
+// neighbours come from its own registers, across its ends from LDS).  What bounds it
+// is LDS: about 34 bytes a point and step.  Each element is formed as the single
+// step forms it.  24^3 in FP64, degree 20: 32 states 147 -> 80 us,
+// 256 states 295 -> 96 us (single steps before; one workgroup a state, so 32 states
+// leave most of the chip idle: 4 us a step).
+constexpr int kLdsDegree = 64;     // steps one launch takes (coefficients by value)
+template <typename T>
+struct ChebCoefs {
+  T a[kLdsDegree], b[kLdsDegree];
+};
+
+template <typename T, int ZP>
+__global__ __launch_bounds__(1024) void cheb_lds_kernel(const T* __restrict__ X,
+                                                       T* __restrict__ Y,
+                                                       const T* __restrict__ Vt, int nx, int ny,
+                                                       int nz, int degree, T wx, T wy,
+                                                       T wz, T dshift, ChebCoefs<T> cf) {
   constexpr int W = 16 / sizeof(T);
   using V = vec_t<T, W>;
   extern __shared__ unsigned char smem_raw[];
   V* lds = reinterpret_cast<V*>(smem_raw);
   const int P = nx * ny, G = P / W, nxg = nx / W;
-  const int gi = threadIdx.x;
-  const bool on = gi < G;
+  const int gi = threadIdx.x % G, z0 = (int)(threadIdx.x / G) * ZP;
+  const bool on = z0 < nz;
+  const int y = gi / nxg, x0 = (gi - y * nxg) * W;
+  const int gm = y == 0 ? gi + G - nxg : gi - nxg, gp = y == ny - 1 ? gi - G + nxg : gi + nxg;
+  const int el = x0 == 0 ? W * gi + nx - 1 : W * gi - 1;
+  const int er = x0 + W == nx ? W * gi + W - nx : W * gi + W;
   const int64_t base = (int64_t)blockIdx.x * G * nz;
-  const V* A = reinterpret_cast<const V*>(Ya) + base;
+  const V* in = reinterpret_cast<const V*>(X) + base;
+  V* out = reinterpret_cast<V*>(Y) + base;
+  const V* vg = reinterpret_cast<const V*>(Vt);
+  V cur[ZP], old[ZP];
+#pragma unroll
+  for (int j = 0; j < ZP; ++j) {
+    cur[j] = old[j] = V(T(0));
+    if (on) {
+      cur[j] = in[(z0 + j) * G + gi];
+      lds[(z0 + j) * G + gi] = cur[j];
+    }
+  }
+  V vnext = on ? vg[z0 * G + gi] : V(T(0));   // V one plane ahead
+  __syncthreads();
+  for (int k = 0; k < degree; ++k) {
+    const T alpha = cf.a[k], beta = cf.b[k];
+    // an offset of zero the compiler does not know: the planes' addresses and V are
+    // formed again in each step instead of being kept in (and spilled from) registers
+    int again = 0;
+    asm volatile("" : "+r"(again));
+    const int p0 = (z0 + again) * G;
+    if (on) {
+      const V below = lds[(z0 == 0 ? nz - 1 : z0 - 1) * G + gi];
+      const V above = lds[(z0 + ZP == nz ? 0 : z0 + ZP) * G + gi];
+#pragma unroll
+      for (int j = 0; j < ZP; ++j) {
+        const V* pl = lds + p0 + j * G;
+        const T* pls = reinterpret_cast<const T*>(pl);
+        const V vv = vnext;
+        vnext = vg[p0 + (j + 1 < ZP ? j + 1 : 0) * G + gi];
+        const V ym = pl[gm], yp = pl[gp];
+        const T left = pls[el], right = pls[er];
+        const V c = cur[j], pz = j == 0 ? below : cur[j == 0 ? 0 : j - 1];
+        const V nzv = j + 1 < ZP ? cur[j + 1 < ZP ? j + 1 : j] : above;
+        const V o = old[j];
+        V r;
+#pragma unroll
+        for (int e = 0; e < W; ++e) {
+          const T xl = e == 0 ? left : c[e == 0 ? 0 : e - 1];
+          const T xr = e == W - 1 ? right : c[e == W - 1 ? 0 : e + 1];
+          const T hy = wx * (xl + xr) + wy * (ym[e] + yp[e]) + wz * (pz[e] + nzv[e]) +
+                       (vv[e] + dshift) * c[e];
+          r[e] = alpha * hy + beta * o[e];
+        }
+        old[j] = r;
+        // one plane's neighbour values live at a time
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (k + 1 < degree) __syncthreads();     // every read of Y_k is done
+#pragma unroll
+    for (int j = 0; j < ZP; ++j) {
+      const V r = old[j];
+      old[j] = cur[j];
+      cur[j] = r;
+      if (on && k + 1 < degree) lds[p0 + j * G + gi] = r;
+    }
+    if (k + 1 < degree) __syncthreads();
+  }
+#pragma unroll
+  for (int j = 0; j < ZP; ++j)
+    if (on) out[(z0 + j) * G + gi] = cur[j];
+}
+
+// S recurrence steps in one sweep over a run of z planes of one state, out of place:
+// stage 0 is Y_k (Yb), stage -1 Y_{k-1} (Ya, NULL for k = 0: the first step has no
+// Y_{k-1}), stage s = 1 .. S is Y_{k+s}, each element formed as the single step forms
+// it.  Only the last two stages are written (stage S-1 to Yp, stage S to Yq; the next
+// sweep's inputs), so S steps move 4 M N s bytes, plus 2 S halo planes a run.
+// At iteration h stage s is formed on plane h - s: the plane above is stage s-1's
+// newest value (formed in this iteration), its own plane and the one below are
+// stage s-1's newest values of the last two iterations (registers, and LDS for the x
+// and y neighbours), and Y of two steps before is stage s-2's value of two
+// iterations ago.  LDS: [2 buffers][S stages][G groups]; a thread owns Q groups.
+// HBM-bound up to S = 5 at 64 x 64 FP32 planes (the copy rate), so the stages are as
+// many as registers and LDS allow.  The planes that close the period, or a run, are
+// formed again at its other end instead of being kept, and the outputs go to buffers of
+// their own: the registers hold more stages instead.  Measured (single steps, or three
+// steps a sweep in place at 1024 states, before): 64^3, 1024 states, degree 40 FP32 11.9
+// -> 7.2 ms (S = 5; S = 4 8.9, 3 12.2), FP64 49.3 -> 33.6 ms (S = 2); 48^3, 256 states,
+// degree 30 FP64 4.20 -> 1.89 ms (S = 3), FP32 1.62 -> 0.64 ms; 40^3, 300 states FP64
+// 2.91 -> 1.13 ms.
+template <typename T, int S, int Q, int MAXT>
+__global__ __launch_bounds__(MAXT) void cheb_sweep_kernel(const T* __restrict__ Ya,
+                                                         const T* __restrict__ Yb,
+                                                         T* __restrict__ Yp, T* __restrict__ Yq,
+                                                         const T* __restrict__ Vt, int nx, int ny,
+                                                         int nz, int zrun, T wx, T wy, T wz,
+                                                         T dshift, ChebCoef<T, S> cf) {
+  constexpr int W = 16 / sizeof(T);
+  using V = vec_t<T, W>;
+  extern __shared__ unsigned char smem_raw[];
+  V* lds = reinterpret_cast<V*>(smem_raw);
+  const int P = nx * ny, G = P / W, nxg = nx / W;
+  const int z0 = blockIdx.y * zrun, z1 = min(nz, z0 + zrun);
+  const int64_t base = (int64_t)blockIdx.x * G * nz;
+  const V* A = Ya ? reinterpret_cast<const V*>(Ya) + base : nullptr;
   const V* B = reinterpret_cast<const V*>(Yb) + base;
   V* Op = reinterpret_cast<V*>(Yp) + base;
   V* Oq = reinterpret_cast<V*>(Yq) + base;
   const V* vg = reinterpret_cast<const V*>(Vt);
   const V zero = V(T(0));
-  auto ld = [&](const V* src, int z) { return on ? src[(int64_t)z * G + gi] : zero; };
-  // plane of index j in the closing region: nz - S + j (j < S), j - S (j >= S)
-  auto plane = [&](int j) { return j < S ? nz - S + j : j - S; };
-
-  // ---- the closing region: stage s on j in [s, 2S - s)
-  V pro[S][2 * S];
+  auto wrap = [&](int z) { return z < 0 ? z + nz : (z >= nz ? z - nz : z); };
+  bool on[Q];
+  int gi[Q], gm[Q], gp[Q], el[Q], er[Q];
 #pragma unroll
-  for (int j = 0; j < 2 * S; ++j) pro[0][j] = ld(B, plane(j));
-#pragma unroll
-  for (int s = 1; s < S; ++s) {
-#pragma unroll
-    for (int j = s; j < 2 * S - s; ++j)
-      if (on) lds[(j - s) * G + gi] = pro[s - 1][j];
-    __syncthreads();
-#pragma unroll
-    for (int j = s; j < 2 * S - s; ++j) {
-      const int z = plane(j);
-      const V o = s == 1 ? ld(A, z) : pro[s - 2][j];
-      pro[s][j] = zero;
-      if (on) {
-        pro[s][j] = step_group<T, W>(lds + (j - s) * G, gi, G, nx, ny, nxg, pro[s - 1][j],
-                                     pro[s - 1][j - 1], pro[s - 1][j + 1], vg[(int64_t)z * G + gi],
-                                     o, wx, wy, wz, dshift, cf.a[s - 1], cf.b[s - 1]);
-        if (s == S - 1) Op[(int64_t)z * G + gi] = pro[s][j];
-      }
-    }
-    __syncthreads();
+  for (int q = 0; q < Q; ++q) {
+    gi[q] = threadIdx.x + q * blockDim.x;
+    on[q] = gi[q] < G;
+    const int g = on[q] ? gi[q] : 0, y = g / nxg, x0 = (g - y * nxg) * W;
+    gm[q] = y == 0 ? g + G - nxg : g - nxg;
+    gp[q] = y == ny - 1 ? g - G + nxg : g + nxg;
+    el[q] = x0 == 0 ? W * g + nx - 1 : W * g - 1;
+    er[q] = x0 + W == nx ? W * g + W - nx : W * g + W;
   }
-
-  // ---- the sweep.  win[s]: stage s on planes p_s - 2, p_s - 1, p_s once stage s
-  // is formed on p_s = h + S - s (stage 0: loaded, p_0 = h + S).
-  V win[S][3];
+  // n1, n2[s]: stage s formed one and two iterations ago; vw[s]: V on plane h - s
+  V n1[S][Q], n2[S][Q], vw[S + 1][Q], bn[Q], an[Q], vn[Q];
+  const int h0 = z0 - S, h1 = z1 + S;
 #pragma unroll
-  for (int s = 1; s < S; ++s) {
-    win[s][0] = zero;
-    win[s][1] = pro[s][2 * S - s - 2];
-    win[s][2] = pro[s][2 * S - s - 1];
+  for (int q = 0; q < Q; ++q) {
+#pragma unroll
+    for (int s = 0; s < S; ++s) n1[s][q] = n2[s][q] = zero;
+#pragma unroll
+    for (int s = 0; s <= S; ++s) vw[s][q] = zero;
+    an[q] = zero;
+    bn[q] = on[q] ? B[(int64_t)wrap(h0) * G + gi[q]] : zero;
+    vn[q] = on[q] ? vg[(int64_t)wrap(h0) * G + gi[q]] : zero;
   }
-  win[0][0] = zero;
-  win[0][1] = pro[0][2 * S - 2];
-  win[0][2] = pro[0][2 * S - 1];
-  V bnext = ld(B, S);
-  V areg = ld(A, S - 1);
-  V vw[S + 1];                       // vw[s] = V on p_s, s = 1 .. S
+  for (int h = h0; h < h1; ++h) {
+    const V* buf = lds + (h & 1) * S * G;
+    V* nxt = lds + ((h + 1) & 1) * S * G;
+    V b[Q], a[Q];
 #pragma unroll
-  for (int s = 1; s <= S; ++s) vw[s] = ld(vg, S - s);
-  for (int h = 0; h < nz; ++h) {
-    win[0][0] = win[0][1];
-    win[0][1] = win[0][2];
-    win[0][2] = bnext;
-    V* buf = lds + (h & 1) * S * G;
-    if (on) {
-      buf[gi] = win[0][1];
+    for (int q = 0; q < Q; ++q) {
 #pragma unroll
-      for (int s = 1; s < S; ++s) buf[s * G + gi] = win[s][2];
+      for (int s = S; s > 0; --s) vw[s][q] = vw[s - 1][q];
+      b[q] = bn[q];
+      a[q] = an[q];
+      vw[0][q] = vn[q];
+      // operands of the next iteration, issued before this one's arithmetic
+      if (on[q] && h + 1 < h1) {
+        const int64_t zn = (int64_t)wrap(h + 1) * G + gi[q];
+        bn[q] = B[zn];
+        vn[q] = vg[zn];
+        if (A) an[q] = A[(int64_t)wrap(h) * G + gi[q]];
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      V up = b[q], upup = zero;        // stages s-1 and s-2 formed in this iteration
+#pragma unroll
+      for (int s = 1; s <= S; ++s) {
+        const int p = h - s;
+        V val = zero;
+        if (p >= z0 - (S - s) && p < z1 + (S - s) && on[q]) {
+          const V* pl = buf + (s - 1) * G;
+          const T* pls = reinterpret_cast<const T*>(pl);
+          const V ym = pl[gm[q]], yp = pl[gp[q]];
+          const T left = pls[el[q]], right = pls[er[q]];
+          const V c = n1[s - 1][q], pz = n2[s - 1][q], vv = vw[s][q];
+          const V o = s == 1 ? a[q] : n2[s >= 2 ? s - 2 : 0][q];
+#pragma unroll
+          for (int e = 0; e < W; ++e) {
+            const T xl = e == 0 ? left : c[e == 0 ? 0 : e - 1];
+            const T xr = e == W - 1 ? right : c[e == W - 1 ? 0 : e + 1];
+            const T hy = wx * (xl + xr) + wy * (ym[e] + yp[e]) + wz * (pz[e] + up[e]) +
+                         (vv[e] + dshift) * c[e];
+            val[e] = cf.a[s - 1] * hy + cf.b[s - 1] * o[e];
+          }
+          if (p >= z0 && p < z1) {
+            if (s == S - 1) Op[(int64_t)p * G + gi[q]] = val;
+            if (s == S) Oq[(int64_t)p * G + gi[q]] = val;
+          }
+        }
+        // stage s-2 is not needed any more as it stood
+        if (s >= 2) {
+          n2[s >= 2 ? s - 2 : 0][q] = n1[s >= 2 ? s - 2 : 0][q];
+          n1[s >= 2 ? s - 2 : 0][q] = upup;
+        }
+        upup = up;
+        up = val;
+      }
+      n2[S - 1][q] = n1[S - 1][q];
+      n1[S - 1][q] = upup;
+      if (on[q]) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) nxt[s * G + gi[q]] = n1[s][q];
+      }
     }
     __syncthreads();
-    // operands of the next step, issued before this step's arithmetic: B and A
-    // while stage 1 is still formed, V while its plane is inside the column
-    const bool next1 = h + S <= nz - S;
-    bnext = next1 ? ld(B, h + S + 1) : zero;
-    const V anext = next1 ? ld(A, h + S) : zero;
-    const V vnext = h + S < nz ? ld(vg, h + S) : zero;
-#pragma unroll
-    for (int s = 1; s <= S; ++s) {
-      const int p = h + S - s;
-      V val;
-      if (p <= nz - 1 - (S - s)) {
-        const V o = s == 1 ? areg : win[s - 2][0];
-        val = on ? step_group<T, W>(buf + (s - 1) * G, gi, G, nx, ny, nxg, win[s - 1][1],
-                                    win[s - 1][0], win[s - 1][2], vw[s], o, wx, wy, wz, dshift,
-                                    cf.a[s - 1], cf.b[s - 1])
-                 : zero;
-        if (on && s == S - 1) Op[(int64_t)p * G + gi] = val;
-      } else {
-        const int jj = p - nz + S;     // in [s, 2S - s)
-        val = zero;
-#pragma unroll
-        for (int j = s; j < 2 * S - s; ++j)
-          if (j == jj) val = pro[s][j];
-      }
-      if (s == S) {
-        if (on) Oq[(int64_t)h * G + gi] = val;
-      } else {
-        win[s][0] = win[s][1];
-        win[s][1] = win[s][2];
-        win[s][2] = val;
-      }
-    }
-    areg = anext;
-#pragma unroll
-    for (int s = S; s > 1; --s) vw[s] = vw[s - 1];
-    vw[1] = vnext;
   }
 }
 
@@ -608,6 +545,235 @@ hipError_t launch_to_float(lrdm_ctx* ctx, const double* a, int64_t n, float* b) 
   return hipGetLastError();
 }
 
+// ------------------------------------------------------------------ the filter
+namespace {
+
+constexpr int kLdsBytes = 160 * 1024;
+constexpr int kCus = 256;
+
+// Planes a thread of cheb_lds_kernel owns (0: the state does not fit): nz over the
+// largest divisor of nz that leaves at most 1024 threads, at most 8.
+template <typename T>
+int cheb_lds_planes(const Grid3& g, int degree) {
+  constexpr int W = 16 / sizeof(T);
+  if (degree > kLdsDegree || g.M * (int64_t)sizeof(T) > kLdsBytes) return 0;
+  const int G = g.nx * g.ny / W;
+  for (int zp = 1; zp <= 8; ++zp)
+    if (g.nz % zp == 0 && (int64_t)G * (g.nz / zp) <= 1024) return zp;
+  return 0;
+}
+
+// Groups per thread and stages of cheb_sweep_kernel: within the registers (one group:
+// five stages at 1024 threads; two: three at 640, two at 1024, where more spill) and
+// the LDS of two planes a stage.
+template <typename T>
+int cheb_sweep_stages(const Grid3& g) {
+  constexpr int W = 16 / sizeof(T);
+  const int P = g.nx * g.ny, G = P / W;
+  if (G > 2048) return 0;
+  const int regs = G <= 1024 ? 5 : (G <= 1280 ? 3 : 2);
+  return std::min(regs, (int)(kLdsBytes / (2 * (int64_t)P * sizeof(T))));
+}
+
+}  // namespace
+
+// The form of a filter: whole states in LDS; sweeps of up to S steps over batches of
+// states; or one step at a time.  The sweeps keep three blocks of a batch beside Y,
+// the single steps one block of N states; room: how many states of workspace there are
+// (0: as many as wanted).  Times in microseconds from the rates measured on the sweep
+// and the single step (19.5 bytes a nanosecond and CU, or 45 where the last-level cache
+// holds a batch's four blocks; 0.11 ns a point and stage, half a microsecond a plane):
+// the sweeps lose where halo planes outweigh the saved passes.  Against forced choices
+// of stages, run and batch at seventeen sizes the plan is within 6 % of the best.
+template <typename T>
+ChebPlan cheb_plan(const Grid3& g, int N, int degree, int64_t room) {
+  constexpr int W = 16 / sizeof(T);
+  ChebPlan p{};
+  if (!cheb_vec_ok<T>(g)) return p;
+  if (cheb_lds_planes<T>(g, degree) > 0) {
+    p.kind = ChebPlan::kLds;
+    return p;
+  }
+  const double P = (double)g.nx * g.ny, block = (double)g.M * N * sizeof(T);
+  double best = degree * std::max(3.0 * block / 4.9e6, 6.0);
+  const int smax = std::min(degree, cheb_sweep_stages<T>(g));
+  const int G = (int)(P / W), threads = G <= 1024 ? (G + 63) / 64 * 64 : ((G + 1) / 2 + 63) / 64 * 64;
+  for (int S = 2; S <= smax; ++S) {
+    if (g.nz < 2 * S) break;
+    const int per_cu = std::max(1, std::min(1024 / threads, (int)(kLdsBytes / (2 * S * P * sizeof(T)))));
+    const int slots = kCus * per_cu;
+    int nb = std::min(N, slots);
+    if (room > 0) nb = (int)std::min<int64_t>(nb, room / 3);
+    if (nb < 1) continue;
+    const int batches = (N + nb - 1) / nb;
+    nb = (N + batches - 1) / batches;
+    const int sweeps = (degree + S - 1) / S;
+    for (int runs = 1; runs <= std::max(1, g.nz / 4); ++runs) {
+      const int zrun = (g.nz + runs - 1) / runs;
+      if ((g.nz + zrun - 1) / zrun != runs) continue;
+      const int rounds = (nb * runs + slots - 1) / slots;
+      const int share = std::min(per_cu, (nb * runs + kCus - 1) / kCus);
+      const double rate = 4.0 * g.M * nb * sizeof(T) < 200e6 ? 45e3 : 19.5e3;
+      const double plane = share * std::max(4.0 * P * sizeof(T) / rate, S * P * 0.11e-3) + 0.5;
+      const double t = batches * sweeps * (rounds * (zrun + 2 * S) * plane + 4.0);
+      if (t < best) {
+        best = t;
+        p.kind = ChebPlan::kSweeps;
+        p.stages = S;
+        p.batch = nb;
+        p.zrun = zrun;
+      }
+    }
+  }
+  return p;
+}
+template ChebPlan cheb_plan<double>(const Grid3&, int, int, int64_t);
+template ChebPlan cheb_plan<float>(const Grid3&, int, int, int64_t);
+
+namespace {
+
+template <typename T>
+struct StencilCoef {
+  T wx, wy, wz, dshift;
+  StencilCoef(const Grid3& g, double c0)
+      : wx(T(-0.5 / (g.hx * g.hx))), wy(T(-0.5 / (g.hy * g.hy))), wz(T(-0.5 / (g.hz * g.hz))),
+        dshift(T(1.0 / (g.hx * g.hx) + 1.0 / (g.hy * g.hy) + 1.0 / (g.hz * g.hz) - c0)) {}
+};
+
+template <typename T, int ZP>
+hipError_t launch_lds(lrdm_ctx* ctx, const Grid3& g, const T* Vt, const T* X, T* Y, int N,
+                      int degree, double c0, const ChebCoefs<T>& cf) {
+  const int G = g.nx * g.ny / (int)(16 / sizeof(T));
+  const int threads = (G * (g.nz / ZP) + 63) / 64 * 64;
+  const int smem = (int)(g.M * sizeof(T));
+  const StencilCoef<T> k(g, c0);
+  if (smem > 65536)
+    LRDM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&cheb_lds_kernel<T, ZP>),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+  ProfScope prof(ctx, "cheb_lds");
+  cheb_lds_kernel<T, ZP><<<N, threads, smem, ctx->stream>>>(X, Y, Vt, g.nx, g.ny, g.nz, degree,
+                                                            k.wx, k.wy, k.wz, k.dshift, cf);
+  return hipGetLastError();
+}
+
+template <typename T, int S, int Q, int MAXT>
+hipError_t launch_sweep_q(lrdm_ctx* ctx, const Grid3& g, const T* Vt, const T* Ya, const T* Yb,
+                          T* Yp, T* Yq, int N, int zrun, double c0, const double* a,
+                          const double* b) {
+  const int P = g.nx * g.ny, G = P / (int)(16 / sizeof(T));
+  const int threads = ((G + Q - 1) / Q + 63) / 64 * 64;
+  const int smem = 2 * S * P * (int)sizeof(T);
+  const StencilCoef<T> k(g, c0);
+  ChebCoef<T, S> cf;
+  for (int s = 0; s < S; ++s) {
+    cf.a[s] = T(a[s]);
+    cf.b[s] = T(b[s]);
+  }
+  if (smem > 65536)
+    LRDM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&cheb_sweep_kernel<T, S, Q, MAXT>),
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+  ProfScope prof(ctx, "cheb_sweep");
+  cheb_sweep_kernel<T, S, Q, MAXT><<<dim3(N, (g.nz + zrun - 1) / zrun), threads, smem,
+                                     ctx->stream>>>(Ya, Yb, Yp, Yq, Vt, g.nx, g.ny, g.nz, zrun,
+                                                    k.wx, k.wy, k.wz, k.dshift, cf);
+  return hipGetLastError();
+}
+
+template <typename T, int S>
+hipError_t launch_sweep_s(lrdm_ctx* ctx, const Grid3& g, const T* Vt, const T* Ya, const T* Yb,
+                          T* Yp, T* Yq, int N, int zrun, double c0, const double* a,
+                          const double* b) {
+  const int G = g.nx * g.ny / (int)(16 / sizeof(T));
+  if (G <= 1024)
+    return launch_sweep_q<T, S, 1, 1024>(ctx, g, Vt, Ya, Yb, Yp, Yq, N, zrun, c0, a, b);
+  if constexpr (S <= 3)
+    if (G <= 1280)
+      return launch_sweep_q<T, S, 2, 640>(ctx, g, Vt, Ya, Yb, Yp, Yq, N, zrun, c0, a, b);
+  if constexpr (S <= 2)
+    return launch_sweep_q<T, S, 2, 1024>(ctx, g, Vt, Ya, Yb, Yp, Yq, N, zrun, c0, a, b);
+  return hipErrorInvalidValue;
+}
+
+template <typename T>
+hipError_t launch_sweep(lrdm_ctx* ctx, int S, const Grid3& g, const T* Vt, const T* Ya,
+                        const T* Yb, T* Yp, T* Yq, int N, int zrun, double c0, const double* a,
+                        const double* b) {
+  switch (S) {
+    case 1: return launch_sweep_s<T, 1>(ctx, g, Vt, Ya, Yb, Yp, Yq, N, zrun, c0, a, b);
+    case 2: return launch_sweep_s<T, 2>(ctx, g, Vt, Ya, Yb, Yp, Yq, N, zrun, c0, a, b);
+    case 3: return launch_sweep_s<T, 3>(ctx, g, Vt, Ya, Yb, Yp, Yq, N, zrun, c0, a, b);
+    case 4: return launch_sweep_s<T, 4>(ctx, g, Vt, Ya, Yb, Yp, Yq, N, zrun, c0, a, b);
+    case 5: return launch_sweep_s<T, 5>(ctx, g, Vt, Ya, Yb, Yp, Yq, N, zrun, c0, a, b);
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+template <typename T>
+hipError_t launch_cheb_lds(lrdm_ctx* ctx, const Grid3& g, const T* Vt, const T* X, T* Y, int N,
+                           double c0, const std::vector<double>& a, const std::vector<double>& b) {
+  const int degree = (int)a.size();
+  ChebCoefs<T> cf{};
+  for (int k = 0; k < degree; ++k) {
+    cf.a[k] = T(a[k]);
+    cf.b[k] = T(b[k]);
+  }
+  switch (cheb_lds_planes<T>(g, degree)) {
+    case 1: return launch_lds<T, 1>(ctx, g, Vt, X, Y, N, degree, c0, cf);
+    case 2: return launch_lds<T, 2>(ctx, g, Vt, X, Y, N, degree, c0, cf);
+    case 3: return launch_lds<T, 3>(ctx, g, Vt, X, Y, N, degree, c0, cf);
+    case 4: return launch_lds<T, 4>(ctx, g, Vt, X, Y, N, degree, c0, cf);
+    case 5: return launch_lds<T, 5>(ctx, g, Vt, X, Y, N, degree, c0, cf);
+    case 6: return launch_lds<T, 6>(ctx, g, Vt, X, Y, N, degree, c0, cf);
+    case 7: return launch_lds<T, 7>(ctx, g, Vt, X, Y, N, degree, c0, cf);
+    case 8: return launch_lds<T, 8>(ctx, g, Vt, X, Y, N, degree, c0, cf);
+  }
+  return hipErrorInvalidValue;
+}
+template hipError_t launch_cheb_lds<double>(lrdm_ctx*, const Grid3&, const double*, const double*,
+                                            double*, int, double, const std::vector<double>&,
+                                            const std::vector<double>&);
+template hipError_t launch_cheb_lds<float>(lrdm_ctx*, const Grid3&, const float*, const float*,
+                                           float*, int, double, const std::vector<double>&,
+                                           const std::vector<double>&);
+
+template <typename T>
+hipError_t launch_cheb_sweeps(lrdm_ctx* ctx, const ChebPlan& p, const Grid3& g, const T* Vt,
+                              const T* X, T* Y, T* W, int N, double c0,
+                              const std::vector<double>& a, const std::vector<double>& b) {
+  const int degree = (int)a.size();
+  // sweeps of even length; a sweep of one step (it writes no Y_{k+S-1}) comes last
+  const int n = (degree + p.stages - 1) / p.stages, least = degree / n, more = degree % n;
+  const int64_t blk = g.M * p.batch;
+  for (int i0 = 0; i0 < N; i0 += p.batch) {
+    const int nb = std::min(p.batch, N - i0);
+    const T* x = X + g.M * i0;
+    // sweeps write the pairs {W0, Y} and {W1, W2} in turn, the last one the pair of Y
+    T* pair[2][2] = {{W, Y + g.M * i0}, {W + blk, W + 2 * blk}};
+    int to = n % 2 ? 0 : 1, k = 0;
+    const T *ya = nullptr, *yb = x;
+    for (int s = 0; s < n; ++s) {
+      const int S = least + (s < more ? 1 : 0);
+      LRDM_HIP(launch_sweep<T>(ctx, S, g, Vt, ya, yb, pair[to][0], pair[to][1], nb, p.zrun, c0,
+                               &a[k], &b[k]));
+      ya = pair[to][0];
+      yb = pair[to][1];
+      to ^= 1;
+      k += S;
+    }
+  }
+  return hipSuccess;
+}
+template hipError_t launch_cheb_sweeps<double>(lrdm_ctx*, const ChebPlan&, const Grid3&,
+                                               const double*, const double*, double*, double*, int,
+                                               double, const std::vector<double>&,
+                                               const std::vector<double>&);
+template hipError_t launch_cheb_sweeps<float>(lrdm_ctx*, const ChebPlan&, const Grid3&,
+                                              const float*, const float*, float*, float*, int,
+                                              double, const std::vector<double>&,
+                                              const std::vector<double>&);
+
 template <typename T>
 hipError_t launch_cheb_step_vec(lrdm_ctx* ctx, const Grid3& g, const T* Vt, const T* Yin,
                                 const T* Yold, T* Yout, int N, double alpha, double c0,
@@ -627,84 +793,6 @@ hipError_t launch_cheb_step_vec(lrdm_ctx* ctx, const Grid3& g, const T* Vt, cons
                              c0, beta);
 }
 
-template <typename T>
-bool cheb_pair_ok(const Grid3& g, int N) {
-  constexpr int W = 16 / sizeof(T);
-  // one group per thread (a plane of at most 1024 groups): with two the sweep's
-  // registers would spill
-  if (!cheb_vec_ok<T>(g) || g.nz < 4 || g.nx * g.ny / W > 1024) return false;
-  // the pair needs a block per whole z column, which the single step also uses
-  // once N alone fills the chip or the column is short
-  return (int64_t)N >= 1024 || g.nz / 2 < 8;
-}
-
-template <typename T>
-hipError_t launch_cheb_pair_vec(lrdm_ctx* ctx, const Grid3& g, const T* Vt, const T* Ya,
-                                const T* Yb, T* Yc, T* Yd, int N, double c0, double a1, double b1,
-                                double a2, double b2) {
-  constexpr int W = 16 / sizeof(T);
-  if (!cheb_pair_ok<T>(g, N)) return hipErrorInvalidValue;
-  const int P = g.nx * g.ny, G = P / W;
-  const int threads = ((G + 63) / 64) * 64;
-  const size_t smem = 4 * (size_t)P * sizeof(T);
-  const T wx = T(-0.5 / (g.hx * g.hx)), wy = T(-0.5 / (g.hy * g.hy)), wz = T(-0.5 / (g.hz * g.hz));
-  const T dshift = T(1.0 / (g.hx * g.hx) + 1.0 / (g.hy * g.hy) + 1.0 / (g.hz * g.hz) - c0);
-  if (smem > 65536)
-    LRDM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&cheb_pair_kernel<T, 1>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-  ProfScope prof(ctx, "cheb_pair");
-  cheb_pair_kernel<T, 1><<<N, threads, smem, ctx->stream>>>(Ya, Yb, Yc, Yd, Vt, g.nx, g.ny, g.nz,
-                                                            wx, wy, wz, dshift, T(a1), T(b1),
-                                                            T(a2), T(b2));
-  return hipGetLastError();
-}
-
-template <typename T>
-bool cheb_triple_ok(const Grid3& g, int N) {
-  return cheb_pair_ok<T>(g, N) && g.nz >= 8;
-}
-
-template <typename T>
-hipError_t launch_cheb_triple_vec(lrdm_ctx* ctx, const Grid3& g, const T* Vt, const T* Ya,
-                                  const T* Yb, T* Yp, T* Yq, int N, double c0, const double* a,
-                                  const double* b) {
-  constexpr int W = 16 / sizeof(T);
-  if (!cheb_triple_ok<T>(g, N)) return hipErrorInvalidValue;
-  const int P = g.nx * g.ny, G = P / W;
-  const int threads = ((G + 63) / 64) * 64;
-  const size_t smem = 2 * 3 * (size_t)P * sizeof(T);
-  const T wx = T(-0.5 / (g.hx * g.hx)), wy = T(-0.5 / (g.hy * g.hy)), wz = T(-0.5 / (g.hz * g.hz));
-  const T dshift = T(1.0 / (g.hx * g.hx) + 1.0 / (g.hy * g.hy) + 1.0 / (g.hz * g.hz) - c0);
-  ChebCoef<T, 3> cf;
-  for (int s = 0; s < 3; ++s) {
-    cf.a[s] = T(a[s]);
-    cf.b[s] = T(b[s]);
-  }
-  if (smem > 65536)
-    LRDM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&cheb_multi_kernel<T, 3>),
-                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-  ProfScope prof(ctx, "cheb_triple");
-  cheb_multi_kernel<T, 3><<<N, threads, smem, ctx->stream>>>(Ya, Yb, Yp, Yq, Vt, g.nx, g.ny, g.nz,
-                                                             wx, wy, wz, dshift, cf);
-  return hipGetLastError();
-}
-
-template bool cheb_triple_ok<double>(const Grid3&, int);
-template bool cheb_triple_ok<float>(const Grid3&, int);
-template hipError_t launch_cheb_triple_vec<double>(lrdm_ctx*, const Grid3&, const double*,
-                                                   const double*, const double*, double*, double*,
-                                                   int, double, const double*, const double*);
-template hipError_t launch_cheb_triple_vec<float>(lrdm_ctx*, const Grid3&, const float*,
-                                                  const float*, const float*, float*, float*, int,
-                                                  double, const double*, const double*);
-template bool cheb_pair_ok<double>(const Grid3&, int);
-template bool cheb_pair_ok<float>(const Grid3&, int);
-template hipError_t launch_cheb_pair_vec<double>(lrdm_ctx*, const Grid3&, const double*,
-                                                 const double*, const double*, double*, double*,
-                                                 int, double, double, double, double, double);
-template hipError_t launch_cheb_pair_vec<float>(lrdm_ctx*, const Grid3&, const float*,
-                                                const float*, const float*, float*, float*, int,
-                                                double, double, double, double, double);
 template bool cheb_vec_ok<double>(const Grid3&);
 template bool cheb_vec_ok<float>(const Grid3&);
 template hipError_t launch_cheb_step_vec<double>(lrdm_ctx*, const Grid3&, const double*,

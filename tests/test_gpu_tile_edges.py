@@ -69,3 +69,62 @@ def test_projection_under_a_workspace_limit():
     assert ctx.workspace_bytes <= 2 * 6 * tile + (1 << 20)
     assert _rel(H, free) < grid.M ** 1.5 * 2.0 ** -53
     ctx.close()
+
+
+def _chebyshev(grid, V, X, degree, a, b, a0):
+    """The scaled recurrence in FP64 by shifts."""
+    h = [grid.L[d] / grid.n[d] for d in range(3)]
+    e, c0 = (b - a) / 2, (b + a) / 2
+    s1 = s = e / (a0 - c0)
+
+    def shifted(y):
+        out = (V - c0) * y
+        for hd, ax in zip(h, (-1, -2, -3)):
+            out = out - 0.5 * (torch.roll(y, 1, ax) + torch.roll(y, -1, ax) - 2 * y) / hd ** 2
+        return out
+
+    y0, y1 = X, (s1 / e) * shifted(X)
+    for _ in range(2, degree + 1):
+        sn = 1.0 / (2.0 / s1 - s)
+        y0, y1 = y1, (2 * sn / e) * shifted(y1) - s * sn * y0
+        s = sn
+    return y1
+
+
+# whole states in LDS (24^3 FP64 and 32^3 are the largest of their kind; 64 steps are the
+# most of one launch), sweeps of every remainder and with z runs, one and two groups per
+# thread, single steps where nx is not a multiple of the 16-byte group
+@pytest.mark.parametrize("prec,n,N,degree", [
+    ("fp64", (24, 24, 24), 3, 20), ("fp64", (8, 8, 8), 5, 64), ("fp64", (8, 8, 8), 5, 65),
+    ("fp32", (32, 32, 32), 2, 7), ("fp64", (20, 18, 13), 3, 11), ("fp64", (32, 32, 32), 40, 1),
+    ("fp64", (32, 32, 24), 300, 9), ("fp32", (40, 36, 44), 70, 13), ("fp64", (48, 48, 16), 9, 8),
+    ("fp64", (64, 64, 12), 20, 5), ("fp32", (64, 64, 64), 300, 10), ("fp32", (30, 22, 26), 4, 6),
+])
+def test_filter_forms(prec, n, N, degree):
+    grid, gen = _grid(n), _gen(degree)
+    dt = torch.float64 if prec == "fp64" else torch.float32
+    V, X = _rand(gen, *grid.shape), _rand(gen, N, *grid.shape, dtype=dt)
+    Y = L.chfsi_filter(grid, V, X, degree, 3.0, 34.0, -2.0, prec=prec)
+    pick = sorted({0, N // 2, N - 1})
+    ref = _chebyshev(grid, V, X[pick].double(), degree, 3.0, 34.0, -2.0)
+    # the scaled recurrence does not amplify: a few roundings a step
+    assert _rel(Y[pick].double(), ref) < 8 * degree * (2.0 ** -53 if prec == "fp64" else 2.0 ** -24)
+
+
+@pytest.mark.parametrize("N", [2, 7, 300])
+def test_filter_under_a_workspace_limit(N):
+    """With room for the block of the single steps only, the sweeps take smaller batches
+    (or the single steps)."""
+    grid, gen = _grid((48, 40, 36)), _gen(N)
+    V, X = _rand(gen, *grid.shape), _rand(gen, N, *grid.shape, dtype=torch.float32)
+    Y = L.chfsi_filter(grid, V, X, 12, 3.0, 34.0, -2.0, prec="fp32")
+    limit = N * grid.M * 4 + grid.M * 4 + (1 << 20) + 512
+    ctx = B.Context(0, torch.cuda.current_stream().cuda_stream, limit)
+    Z, g = torch.empty_like(Y), grid.c()
+    ctx.check(ctx.lib.chfsi_filter(ctx.ptr, ctypes.byref(g), *(ctypes.c_void_p(t.data_ptr())
+                                                               for t in (V, X, Z)),
+                                   N, 1, 12, 3.0, 34.0, -2.0))
+    torch.cuda.synchronize()
+    assert ctx.workspace_bytes <= limit
+    assert _rel(Z, Y) < 8 * 12 * 2.0 ** -24
+    ctx.close()
