@@ -1594,7 +1594,7 @@ extern "C" lrdm_status lrdm_autotune(lrdm_ctx* ctx, const lrdm_grid* grid, int32
     } kinds[3] = {{batch, arith, true}, {nspin, arith, true}, {1, TN_ARITH_F64, false}};
     for (int k = 0; k < 3; ++k) {
       const Kind& kd = kinds[k];
-      const int h = tn_splits(ntiles * kd.b, g.M);
+      const int h = tn_default_splits(N, g.M, kd.b, kd.arith);
       const int cap = tn_split_cap(ntiles * kd.b, g.M);
       const std::array<int64_t, 5> key{N, g.M, kd.b, kd.arith, kd.weighted ? 1 : 0};
       int best = h, best_v = TN_VAR_DEFAULT;

@@ -371,8 +371,8 @@ __device__ inline void dma16(const void* src, unsigned char* lds) {
   __builtin_amdgcn_global_load_lds(src, (lds_void*)lds, 16, 0, 0);
 }
 
-// This wave's share (2 of 16 copy instructions) of one operand tile: rows
-// [r0, r0+BT) x k in [k0, k0+KT) of the row-major FP32 [nrows][ld] array X.
+// This wave's share (of NW waves) of the copy instructions of one operand tile: rows
+// [r0, r0+ROWS) x k in [k0, k0+KT) of the row-major FP32 [nrows][ld] array X.
 // Chunks with a row >= nrows or k >= kend (kend a multiple of 4) read zeros.
 // Slot permutation of the eight 16-byte chunks of an FP32 tile row (128 bytes):
 // chunk q of row r sits in slot q ^ tile_swizzle(r), so 8 consecutive rows reading
@@ -381,12 +381,13 @@ __device__ inline void dma16(const void* src, unsigned char* lds) {
 // made the FP32 kernels 2 % slower on the device, so this one stays.)
 __device__ inline int tile_swizzle(int r) { return r & 7; }
 
-__device__ inline void dma_tile(const float* __restrict__ X, int64_t ld, int nrows, int64_t r0,
+template <int ROWS, int NW>
+__device__ inline void dma_rows(const float* __restrict__ X, int64_t ld, int nrows, int64_t r0,
                                 int64_t k0, int64_t kend, const float* zeros, unsigned char* tile,
                                 int wid, int lane) {
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int ins = wid * 2 + u;                      // 64 chunks = 8 rows each
+  for (int u = 0; u < ROWS / 8 / NW; ++u) {
+    const int ins = wid * (ROWS / 8 / NW) + u;        // 64 chunks = 8 rows each
     const int r = ins * 8 + (lane >> 3);
     const int q = (lane & 7) ^ tile_swizzle(r);       // logical chunk of slot lane & 7
     const int64_t k = k0 + 4 * q;
@@ -394,6 +395,33 @@ __device__ inline void dma_tile(const float* __restrict__ X, int64_t ld, int nro
     const float* src = (gr < nrows && k < kend) ? X + gr * ld + k : zeros;
     dma16(src, tile + ins * 1024);
   }
+}
+
+// The same copies for K-tiles inside the operand: base[u] is the lane's source of its
+// copy u at k = 0 (rows past nrows read the last row: their products land in rows or
+// points that are never read), so a copy costs one address add.
+template <int ROWS, int NW>
+__device__ inline void dma_bases(const float* __restrict__ X, int64_t ld, int64_t nrows,
+                                 int64_t r0, int wid, int lane,
+                                 const float* (&base)[ROWS / 8 / NW]) {
+#pragma unroll
+  for (int u = 0; u < ROWS / 8 / NW; ++u) {
+    const int r = (wid * (ROWS / 8 / NW) + u) * 8 + (lane >> 3);
+    base[u] = X + min(r0 + r, nrows - 1) * ld + 4 * ((lane & 7) ^ tile_swizzle(r));
+  }
+}
+template <int ROWS, int NW>
+__device__ inline void dma_full(const float* const (&base)[ROWS / 8 / NW], int64_t k0,
+                                unsigned char* tile, int wid) {
+#pragma unroll
+  for (int u = 0; u < ROWS / 8 / NW; ++u)
+    dma16(base[u] + k0, tile + (wid * (ROWS / 8 / NW) + u) * 1024);
+}
+
+__device__ inline void dma_tile(const float* __restrict__ X, int64_t ld, int nrows, int64_t r0,
+                                int64_t k0, int64_t kend, const float* zeros, unsigned char* tile,
+                                int wid, int lane) {
+  dma_rows<BT, PW>(X, ld, nrows, r0, k0, kend, zeros, tile, wid, lane);
 }
 
 // The weights w[k0 .. k0+KT) of one K-tile (16 chunks of two doubles; lanes
@@ -420,16 +448,29 @@ __device__ inline void frag_sw(const unsigned char* tile, int base, int lane, fl
   }
 }
 
-// The wave's operands of one K-tile (rows of its 32 x 64 part), read from LDS
+// The FP32-arithmetic kernels take half a 128 x 128 tile per workgroup: eight waves of
+// 32 x 32 on 64 rows, two workgroups (four waves a SIMD) per CU, the next copies issued
+// behind a K-tile's products.  MFMA-bound at 100 to 106 TFLOP/s of the 155 a loop of
+// products alone reaches: with the copies left out the same loop runs at 141, while
+// one source address for all of them, no FP64 sums or no fragment reads gain 3 to 5 %
+// each.  48^3, 256 states, 8 directions: projection 1199 -> 950 us, back-projection 1303
+// -> 1055 us against eight waves of 32 x 64 on the whole tile (one workgroup a CU).
+constexpr int HR = 64;                    // rows of a workgroup
+constexpr int HW = 8;                     // its waves
+constexpr int NJ = 2;                     // 16-column strips of a wave's 32 x 32 part
+constexpr int HT = HW * 64;               // and threads
+constexpr int HB = HR * KT * 4;           // bytes of its row operand's tile (8 KB)
+
+// The wave's operands of one K-tile (rows of its 32 x 32 part), read from LDS
 // before the next copies are issued: an LDS read after a global->LDS copy would
 // make the compiler wait for every copy in flight.  weight() scales B's column k
 // by w[k] (FP32 product of the rounded weight).
 struct PipeFrag {
-  float a[2][8], b[4][8];
+  float a[2][8], b[NJ][8];
   __device__ inline void load(const unsigned char* At, const unsigned char* Bt, int wr, int wc,
                               int lane) {
     frag_sw<2>(At, wr * 32, lane, a);
-    frag_sw<4>(Bt, wc * 64, lane, b);
+    frag_sw<NJ>(Bt, wc * 16 * NJ, lane, b);
   }
   // wt: the weights of the K-tile in LDS
   __device__ inline void weight(const unsigned char* wt, int lane) {
@@ -445,34 +486,34 @@ struct PipeFrag {
       wf[2 * h + 1] = (float)y[1];
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int e = 0; e < 8; ++e) b[j][e] *= wf[e];
   }
 };
 
-// acc += scale * A B^T over one K-tile of the wave's 32 x 64 part (registers only).
+// acc += scale * A B^T over one K-tile of the wave's 32 x 32 part (registers only).
 template <Core C>
-__device__ inline void kt_step_pipe(PipeFrag& f, double scale, double (&acc)[2][4][4]) {
-  f4 c[2][4];
+__device__ inline void kt_step_pipe(PipeFrag& f, double scale, double (&acc)[2][NJ][4]) {
+  f4 c[2][NJ];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) c[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NJ; ++j) c[i][j] = f4{0.f, 0.f, 0.f, 0.f};
   if constexpr (C == Core::F32) {
 #pragma unroll
     for (int s = 0; s < 8; ++s)
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) c[i][j] = mfma_f32(f.a[i][s], f.b[j][s], c[i][j]);
+        for (int j = 0; j < NJ; ++j) c[i][j] = mfma_f32(f.a[i][s], f.b[j][s], c[i][j]);
   } else {
     constexpr int NP = (C == Core::BF3) ? 3 : 2;
     bf8 pa[2][NP];
 #pragma unroll
     for (int i = 0; i < 2; ++i) split<NP>(f.a[i], pa[i]);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < NJ; ++j) {
       bf8 pb[NP];
       split<NP>(f.b[j], pb);
 #pragma unroll
@@ -491,7 +532,7 @@ __device__ inline void kt_step_pipe(PipeFrag& f, double scale, double (&acc)[2][
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[i][j][v] += scale * (double)c[i][j][v];
 }
@@ -532,10 +573,10 @@ __device__ inline void zero_pipe(double (&acc)[2][4][4]) {
       for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.0;
 }
 
-// tn_sym, pipelined: same grid and partial layout as tn_sym_lp_kernel.  Requires M
-// a multiple of 4 and 16-byte aligned A, B and weight rows.  W: B weighted by w.
-// The body, for workgroup `lin` of the launch's grid (the fused launch of several
-// systems passes each system's own workgroup index).
+// tn_sym, pipelined: partial layout of tn_sym_lp_kernel, two workgroups per tile (rows
+// 0..63, 64..127).  Requires M a multiple of 4 and 16-byte aligned A, B and weight
+// rows.  W: B weighted by w.  The body, for workgroup `lin` of the launch's grid (the
+// fused launch of several systems passes each system's own workgroup index).
 template <Core C, bool W>
 __device__ inline void tn_sym_pipe_body(
     int lin, const float* __restrict__ A, const float* __restrict__ B,
@@ -543,14 +584,17 @@ __device__ inline void tn_sym_pipe_body(
     int64_t kchunk, int nsplit, int batch, const unsigned char* __restrict__ active,
     const float* __restrict__ zeros, double* __restrict__ part) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_pipe[];
-  constexpr int SB = 2 * TB + (W ? 1024 : 0);   // bytes of one stage
+  constexpr int SB = HB + TB + (W ? 1024 : 0);  // bytes of one stage
   const int ntiles = ntb * (ntb + 1) / 2;
-  int group, tile;
-  xcd_map(lin, nsplit * batch, ntiles, group, tile);
+  int group, item;
+  xcd_map(lin, nsplit * batch, 2 * ntiles, group, item);
+  const int tile = item >> 1, half = item & 1;
   const int sp = group % nsplit, b = group / nsplit;
   int ti = 0, rem = tile;
   while (rem >= ntb - ti) { rem -= ntb - ti; ++ti; }
   const int tj = ti + rem;
+  const int r0 = ti * BT + half * HR;
+  if (r0 >= N) return;                          // rows the reduction never reads
   const int c = b % nspin;
   const float* Ac = A + (int64_t)c * N * M;
   const float* Bc = B + (int64_t)c * N * M;
@@ -560,48 +604,66 @@ __device__ inline void tn_sym_pipe_body(
   const int64_t kend = block_active(active, c, ntb, ti, tj) ? min(M, kbeg + kchunk) : kbeg;
   const int nk = kbeg < kend ? (int)((kend - kbeg + KT - 1) / KT) : 0;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int wr = wid >> 1, wc = wid & 1;
+  const int wr = wid >> 2, wc = wid & 3;
+  // the quadrant below the diagonal of a diagonal tile is never read
+  const bool work = !(ti == tj && half == 1 && wc < 2);
   // Every stage issues the same copies (zeros past the end), so the count of
-  // copies in flight per wave is the same at every wait: 4 per stage, plus the
+  // copies in flight per wave is the same at every wait: 3 per stage, plus the
   // weights in wave 0.
+  const float* abase[HR / 8 / HW];
+  const float* bbase[BT / 8 / HW];
+  dma_bases<HR, HW>(Ac, M, N, r0, wid, lane, abase);
+  dma_bases<BT, HW>(Bc, M, N, (int64_t)tj * BT, wid, lane, bbase);
+  const double* wbase = W ? wb + 2 * (lane & 15) : nullptr;
   auto issue = [&](int t) {
     unsigned char* st = smem_pipe + (t % NST) * SB;
     const int64_t k0 = kbeg + (int64_t)t * KT;
+    if (k0 + KT <= kend) {
+      dma_full<HR, HW>(abase, k0, st, wid);
+      dma_full<BT, HW>(bbase, k0, st + HB, wid);
+      if (W && wid == 0) dma16(wbase + k0, st + HB + TB);
+      return;
+    }
     const int64_t ke = t < nk ? kend : k0;
-    dma_tile(Ac, M, N, (int64_t)ti * BT, k0, ke, zeros, st, wid, lane);
-    dma_tile(Bc, M, N, (int64_t)tj * BT, k0, ke, zeros, st + TB, wid, lane);
-    if (W && wid == 0) dma_weights(wb, k0, ke, zeros, st + 2 * TB, lane);
+    dma_rows<HR, HW>(Ac, M, N, r0, k0, ke, zeros, st, wid, lane);
+    dma_rows<BT, HW>(Bc, M, N, (int64_t)tj * BT, k0, ke, zeros, st + HB, wid, lane);
+    if (W && wid == 0) dma_weights(wb, k0, ke, zeros, st + HB + TB, lane);
   };
-  double acc[2][4][4];
-  zero_pipe(acc);
-  issue(0);
-  issue(1);
-  for (int t = 0; t < nk; ++t) {
-    if (W && wid == 0) wait_stage<5>(); else wait_stage<4>();
-    const unsigned char* st = smem_pipe + (t % NST) * SB;
-    PipeFrag f;
-    f.load(st, st + TB, wr, wc, lane);
-    if (W) f.weight(st + 2 * TB, lane);
-    compiler_fence();
-    issue(t + 2);
-    kt_step_pipe<C>(f, 1.0, acc);
-  }
-  wait_stage<0>();
-  double* out = part + (((int64_t)b * nsplit + sp) * ntiles + tile) * (BT * BT);
+  double acc[2][NJ][4];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.0;
+  issue(0);
+  issue(1);
+  for (int t = 0; t < nk; ++t) {
+    if (W && wid == 0) wait_stage<4>(); else wait_stage<3>();
+    const unsigned char* st = smem_pipe + (t % NST) * SB;
+    PipeFrag f;
+    f.load(st, st + HB, wr, wc, lane);
+    if (W) f.weight(st + HB + TB, lane);
+    compiler_fence();
+    if (work) kt_step_pipe<C>(f, 1.0, acc);
+    issue(t + 2);
+  }
+  wait_stage<0>();
+  double* out = part + (((int64_t)b * nsplit + sp) * ntiles + tile) * (BT * BT) + half * HR * BT;
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int row = wr * 32 + i * 16 + 4 * (lane >> 4) + v;
-        const int col = wc * 64 + j * 16 + (lane & 15);
+        const int col = wc * 16 * NJ + j * 16 + (lane & 15);
         out[row * BT + col] = acc[i][j][v];
       }
 }
 
 template <Core C, bool W>
-__global__ __launch_bounds__(PT, 1) void tn_sym_pipe_kernel(
+__global__ __launch_bounds__(HT, 4) void tn_sym_pipe_kernel(
     const float* __restrict__ A, const float* __restrict__ B, const double* __restrict__ w,
     int64_t w_stride, int N, int64_t M, int nspin, int ntb, int64_t kchunk, int nsplit, int batch,
     const unsigned char* __restrict__ active, const float* __restrict__ zeros,
@@ -620,8 +682,8 @@ __device__ inline void backproj_pipe_body(
     const double* __restrict__ sub, const unsigned char* __restrict__ active,
     const float* __restrict__ zeros, double* __restrict__ out) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_pipe[];
-  constexpr int SB = 2 * TB;
-  double* red = reinterpret_cast<double*>(smem_pipe + NST * SB);   // [PW][64]
+  constexpr int SB = HB + TB;
+  double* red = reinterpret_cast<double*>(smem_pipe + NST * SB);   // [HW][16 NJ]
   // 1-D grid: the directions of one block of points run together on one XCD
   int pblk, b;
   xcd_map(lin, (int)((M + BT - 1) / BT), batch, pblk, b);
@@ -631,68 +693,66 @@ __device__ inline void backproj_pipe_body(
   const float* Gb = Gf + (int64_t)b * N * ldk;
   const int64_t p0 = (int64_t)pblk * BT;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int wr = wid >> 1, wc = wid & 1;
-  double dsum[4] = {0.0, 0.0, 0.0, 0.0};
+  const int wr = wid >> 2, wc = wid & 3;
+  const float* pbase[BT / 8 / HW];
+  dma_bases<BT, HW>(ATc, ldk, M, p0, wid, lane, pbase);
+  double dsum[NJ] = {};
   const int nib = (N + BT - 1) / BT;
-  for (int ib = 0; ib < nib; ++ib) {
-    const int i0 = ib * BT;
-    // j runs over the active blocks (blocks.h) of [i0, N): the diagonal block
-    // once, blocks right of it twice
+  // strips of 64 rows; j runs over the active blocks (blocks.h) of [128 ib, N) of the
+  // strip's row block ib: the diagonal block once, blocks right of it twice
+  for (int i0 = 0; i0 < N; i0 += HR) {
+    const int ib = i0 / BT;
     const uint64_t bits = active_row_bits(active, c, nib, ib);
     const int nk = active_ktiles(bits, N, KT);
     if (nk == 0) continue;
+    // every K-tile lies inside [0, ldk); past the last one it is copied again, unused
+    const float* gbase[HR / 8 / HW];
+    dma_bases<HR, HW>(Gb, ldk, N, i0, wid, lane, gbase);
     auto issue = [&](int t) {
       unsigned char* st = smem_pipe + (t % NST) * SB;
       int J;
-      const int64_t j0 = active_ktile(bits, t, KT, J);
-      const int64_t je = t < nk ? ldk : j0;
-      dma_tile(Gb, ldk, N, i0, j0, je, zeros, st, wid, lane);
-      dma_tile(ATc, ldk, (int)M, p0, j0, je, zeros, st + TB, wid, lane);
+      const int64_t j0 = active_ktile(bits, min(t, nk - 1), KT, J);
+      dma_full<HR, HW>(gbase, j0, st, wid);
+      dma_full<BT, HW>(pbase, j0, st + HB, wid);
     };
-    double acc[2][4][4];
-    zero_pipe(acc);
+    double acc[2][NJ][4];
+  #pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.0;
     issue(0);
     issue(1);
     for (int t = 0; t < nk; ++t) {
-      wait_stage<4>();
+      wait_stage<3>();
       const unsigned char* st = smem_pipe + (t % NST) * SB;
       PipeFrag f;
-      f.load(st, st + TB, wr, wc, lane);
+      f.load(st, st + HB, wr, wc, lane);
       compiler_fence();
-      issue(t + 2);
       int J;
       active_ktile(bits, t, KT, J);
       kt_step_pipe<C>(f, J > ib ? 2.0 : 1.0, acc);
+      issue(t + 2);
     }
     wait_stage<0>();   // the copies past the end land before the ring is reused
-    // row-dot with A[i][p]: all 32 reads issued first (indices clamped into
-    // range, out-of-range terms dropped afterwards)
-    float av[2][4][4];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int gi = min(i0 + wr * 32 + i * 16 + 4 * (lane >> 4) + v, N - 1);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int64_t p = min(p0 + wc * 64 + j * 16 + (lane & 15), M - 1);
-          av[i][v][j] = Ac[(int64_t)gi * M + p];
-        }
-      }
+    // row-dot with A[i][p] (indices clamped into range, out-of-range terms dropped)
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int gi = i0 + wr * 32 + i * 16 + 4 * (lane >> 4) + v;
+        const float* row = Ac + (int64_t)min(gi, N - 1) * M;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int64_t p = p0 + wc * 64 + j * 16 + (lane & 15);
-          if (gi < N && p < M) dsum[j] += acc[i][j][v] * (double)av[i][v][j];
+        for (int j = 0; j < NJ; ++j) {
+          const int64_t p = p0 + wc * 16 * NJ + j * 16 + (lane & 15);
+          const float a = row[min(p, M - 1)];
+          if (gi < N && p < M) dsum[j] += acc[i][j][v] * (double)a;
         }
       }
   }
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
+  for (int j = 0; j < NJ; ++j) {
     double v = dsum[j];
     v += __shfl_xor(v, 16, 64);
     v += __shfl_xor(v, 32, 64);
@@ -700,15 +760,12 @@ __device__ inline void backproj_pipe_body(
   }
   if (lane < 16) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) red[wid * 64 + j * 16 + lane] = dsum[j];
+    for (int j = 0; j < NJ; ++j) red[wid * 16 * NJ + j * 16 + lane] = dsum[j];
   }
   __syncthreads();
   if (threadIdx.x < BT) {
     const int col = threadIdx.x;
-    const int wcc = col >> 6, cl = col & 63;
-    double v = 0.0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) v += red[(2 * q + wcc) * 64 + cl];
+    const double v = red[col] + red[BT + col];   // the two row halves
     const int64_t p = p0 + col;
     if (p < M) {
       double r = scale * v;
@@ -719,7 +776,7 @@ __device__ inline void backproj_pipe_body(
 }
 
 template <Core C>
-__global__ __launch_bounds__(PT, 1) void backproj_pipe_kernel(
+__global__ __launch_bounds__(HT, 4) void backproj_pipe_kernel(
     const float* __restrict__ A, const float* __restrict__ AT, const float* __restrict__ Gf,
     int N, int64_t M, int ldk, int nspin, int batch, double scale, const double* __restrict__ sub,
     const unsigned char* __restrict__ active, const float* __restrict__ zeros,
@@ -767,7 +824,7 @@ __device__ inline int fused_system(const int* wg0, int nsys, int bid) {
   return s;
 }
 
-__global__ __launch_bounds__(PT, 1) void tn_sym_fused_kernel(const FusedProj t,
+__global__ __launch_bounds__(HT, 4) void tn_sym_fused_kernel(const FusedProj t,
                                                              const float* __restrict__ zeros) {
   const int s = fused_system(t.wg0, t.nsys, blockIdx.x);
   const int lin = blockIdx.x - t.wg0[s];
@@ -777,7 +834,7 @@ __global__ __launch_bounds__(PT, 1) void tn_sym_fused_kernel(const FusedProj t,
                                     t.active[s], zeros, t.part[s]);
 }
 
-__global__ __launch_bounds__(PT, 1) void backproj_fused_kernel(const FusedBackproj t,
+__global__ __launch_bounds__(HT, 4) void backproj_fused_kernel(const FusedBackproj t,
                                                                const float* __restrict__ zeros) {
   const int s = fused_system(t.wg0, t.nsys, blockIdx.x);
   const int lin = blockIdx.x - t.wg0[s];
@@ -832,23 +889,23 @@ __global__ __launch_bounds__(256) void transpose_pad_kernel(const float* __restr
 // zero in every X_m and are skipped.  1-D grid over (point block, channel) groups
 // of row blocks, the row blocks of one point block together on one XCD (they
 // stage the same tiles of AT).
-__global__ __launch_bounds__(PT, 1) void adj_psi_pipe_kernel(
+__global__ __launch_bounds__(HT, 4) void adj_psi_pipe_kernel(
     const float* __restrict__ Xf, const double* __restrict__ w1, const double* __restrict__ w2,
     int nx, const float* __restrict__ AT, int N, int64_t M, int ldk, int nspin, double scale,
     const unsigned char* __restrict__ active, const float* __restrict__ zeros,
     float* __restrict__ Out) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_pipe[];
-  constexpr int SB = 2 * TB;
+  constexpr int SB = HB + TB;
   const int nrb = (N + BT - 1) / BT;
   const int npb = (int)((M + BT - 1) / BT);
-  int group, ib;
-  xcd_map(blockIdx.x, npb * nspin, nrb, group, ib);
+  int group, strip;                               // strips of 64 rows
+  xcd_map(blockIdx.x, npb * nspin, (N + HR - 1) / HR, group, strip);
   const int pblk = group / nspin, c = group % nspin;
-  const int i0 = ib * BT;
+  const int i0 = strip * HR, ib = i0 / BT;
   const int64_t p0 = (int64_t)pblk * BT;
   const float* ATc = AT + (int64_t)c * M * ldk;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int wr = wid >> 1, wc = wid & 1;
+  const int wr = wid >> 2, wc = wid & 3;
   // K runs over the active blocks J of row block ib (every J, X_m being a full product)
   uint64_t bits = 0;
   for (int J = 0; J < nrb; ++J)
@@ -856,55 +913,66 @@ __global__ __launch_bounds__(PT, 1) void adj_psi_pipe_kernel(
   const int nkm = active_ktiles(bits, N, KT);     // K-tiles per matrix
   const int nmat = 2 * nx;
   const int nk = nmat * nkm;
+  // past the last K-tile it is copied again, unused
+  const float* pbase[BT / 8 / HW];
+  const float* xbase[HR / 8 / HW];
+  dma_bases<BT, HW>(ATc, ldk, M, p0, wid, lane, pbase);
+  dma_bases<HR, HW>(Xf + (int64_t)c * N * ldk, ldk, N, i0, wid, lane, xbase);
+  const int64_t xstride = (int64_t)nspin * N * ldk;   // from one matrix to the next
   auto issue = [&](int t) {
     unsigned char* st = smem_pipe + (t % NST) * SB;
-    const int m = nkm > 0 ? min(t / nkm, nmat - 1) : 0;
+    const int tt = min(t, nk - 1), m = tt / nkm;
     int J;
-    const int64_t j0 = active_ktile(bits, nkm > 0 ? t % nkm : 0, KT, J);
-    const int64_t je = t < nk ? ldk : j0;
-    const float* Xm = Xf + ((int64_t)m * nspin + c) * N * ldk;
-    dma_tile(Xm, ldk, N, i0, j0, je, zeros, st, wid, lane);
-    dma_tile(ATc, ldk, (int)M, p0, j0, je, zeros, st + TB, wid, lane);
+    const int64_t j0 = active_ktile(bits, tt % nkm, KT, J);
+    dma_full<HR, HW>(xbase, m * xstride + j0, st, wid);
+    dma_full<BT, HW>(pbase, j0, st + HB, wid);
   };
-  double acc[2][4][4];
-  zero_pipe(acc);
-  double wcol[4] = {0.0, 0.0, 0.0, 0.0};
-  issue(0);
-  issue(1);
+  double acc[2][NJ][4];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.0;
+  double wcol[NJ] = {};
+  if (nk > 0) {
+    issue(0);
+    issue(1);
+  }
   for (int t = 0; t < nk; ++t) {
     if (t % nkm == 0) {
       // the weights of matrix m for this wave's output columns
       const int m = t / nkm;
       const double* w = (m < nx ? w1 : w2) + ((int64_t)(m % nx) * nspin + c) * M;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int64_t p = p0 + wc * 64 + j * 16 + (lane & 15);
+      for (int j = 0; j < NJ; ++j) {
+        const int64_t p = p0 + wc * 16 * NJ + j * 16 + (lane & 15);
         wcol[j] = p < M ? w[p] : 0.0;
       }
     }
-    wait_stage<4>();
+    wait_stage<3>();
     const unsigned char* st = smem_pipe + (t % NST) * SB;
     PipeFrag f;
-    f.load(st, st + TB, wr, wc, lane);
+    f.load(st, st + HB, wr, wc, lane);
     compiler_fence();
-    issue(t + 2);
-    f4 cc[2][4];
+    f4 cc[2][NJ];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) cc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < NJ; ++j) cc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < 8; ++s)
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) cc[i][j] = mfma_f32(f.a[i][s], f.b[j][s], cc[i][j]);
+        for (int j = 0; j < NJ; ++j) cc[i][j] = mfma_f32(f.a[i][s], f.b[j][s], cc[i][j]);
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
+      for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int v = 0; v < 4; ++v) acc[i][j][v] += wcol[j] * (double)cc[i][j][v];
+    issue(t + 2);
   }
   wait_stage<0>();
   float* Oc = Out + (int64_t)c * N * M;
@@ -914,8 +982,8 @@ __global__ __launch_bounds__(PT, 1) void adj_psi_pipe_kernel(
     for (int v = 0; v < 4; ++v) {
       const int gi = i0 + wr * 32 + i * 16 + 4 * (lane >> 4) + v;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int64_t p = p0 + wc * 64 + j * 16 + (lane & 15);
+      for (int j = 0; j < NJ; ++j) {
+        const int64_t p = p0 + wc * 16 * NJ + j * 16 + (lane & 15);
         if (gi < N && p < M) Oc[(int64_t)gi * M + p] = (float)(scale * acc[i][j][v]);
       }
     }
@@ -1720,12 +1788,12 @@ hipError_t launch_tn_sym<float>(lrdm_ctx* ctx, const float* A, const float* B, c
     tn_reduce_lp_kernel<<<grd2, blk, 0, ctx->stream>>>(part, N, ntb, ns, H);
     return hipGetLastError();
   }
-  const int smem = NST * (2 * TB + (w ? 1024 : 0));
+  const int smem = NST * (HB + TB + (w ? 1024 : 0));
   auto run_pipe = [&](auto kernel) -> hipError_t {
     LRDM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, smem));
-    kernel<<<grd, PT, smem, ctx->stream>>>(A, B, w, w_stride, N, M, nspin, ntb, kchunk, ns, batch,
-                                           active, ctx->zeros, part);
+    kernel<<<2 * grd, HT, smem, ctx->stream>>>(A, B, w, w_stride, N, M, nspin, ntb, kchunk, ns,
+                                               batch, active, ctx->zeros, part);
     return hipGetLastError();
   };
   auto run_staged = [&](auto kernel) -> hipError_t {
@@ -1801,11 +1869,11 @@ hipError_t launch_backproj<float>(lrdm_ctx* ctx, const float* A, const double* G
   LRDM_HIP(hipGetLastError());
   transpose_pad_kernel<<<gt, 256, 0, ctx->stream>>>(A, AT, N, M, ldk);
   LRDM_HIP(hipGetLastError());
-  const int smem = NST * 2 * TB + PW * 64 * (int)sizeof(double);
+  const int smem = NST * (HB + TB) + 2 * BT * (int)sizeof(double);
   LRDM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&backproj_pipe_kernel<Core::F32>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, smem));
   ProfScope prof(ctx, "backproj");
-  backproj_pipe_kernel<Core::F32><<<grd, PT, smem, ctx->stream>>>(
+  backproj_pipe_kernel<Core::F32><<<grd, HT, smem, ctx->stream>>>(
       A, AT, Gf, N, M, ldk, nspin, batch, scale, sub, active, ctx->zeros, out);
   return hipGetLastError();
 }
@@ -1879,13 +1947,13 @@ hipError_t launch_adj_psi<float>(lrdm_ctx* ctx, const double* X1, const double* 
   dim3 gt((unsigned)((M + 63) / 64), (unsigned)(ldk / 64 + (ldk % 64 ? 1 : 0)), nspin);
   transpose_pad_kernel<<<gt, 256, 0, ctx->stream>>>(Psi, AT, N, M, ldk);
   LRDM_HIP(hipGetLastError());
-  const int smem = NST * 2 * TB;
+  const int smem = NST * (HB + TB);
   LRDM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&adj_psi_pipe_kernel),
                                hipFuncAttributeMaxDynamicSharedMemorySize, smem));
-  const unsigned grd = (unsigned)((M + BT - 1) / BT) * (unsigned)((N + BT - 1) / BT) *
+  const unsigned grd = (unsigned)((M + BT - 1) / BT) * (unsigned)((N + HR - 1) / HR) *
                        (unsigned)nspin;
   ProfScope prof(ctx, "adj_psi");
-  adj_psi_pipe_kernel<<<grd, PT, smem, ctx->stream>>>(Xf, w1, w2, nx, AT, N, M, ldk, nspin, scale,
+  adj_psi_pipe_kernel<<<grd, HT, smem, ctx->stream>>>(Xf, w1, w2, nx, AT, N, M, ldk, nspin, scale,
                                                       active, ctx->zeros, Out);
   return hipGetLastError();
 }
@@ -1950,7 +2018,7 @@ bool a16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 }  // namespace
 
 hipError_t launch_tn_sym_fused(lrdm_ctx* ctx, const FusedProjItem* items, int n) {
-  const int smem = NST * (2 * TB + 1024);
+  const int smem = NST * (HB + TB + 1024);
   LRDM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tn_sym_fused_kernel),
                                hipFuncAttributeMaxDynamicSharedMemorySize, smem));
   std::vector<double*> parts(n, nullptr);
@@ -1963,7 +2031,7 @@ hipError_t launch_tn_sym_fused(lrdm_ctx* ctx, const FusedProjItem* items, int n)
     t.wg0[t.nsys] = total;
     {
       ProfScope prof(ctx, "proj");
-      tn_sym_fused_kernel<<<(unsigned)total, PT, smem, ctx->stream>>>(t, ctx->zeros);
+      tn_sym_fused_kernel<<<(unsigned)total, HT, smem, ctx->stream>>>(t, ctx->zeros);
     }
     t = FusedProj{};
     t.nsys = 0;
@@ -1991,7 +2059,7 @@ hipError_t launch_tn_sym_fused(lrdm_ctx* ctx, const FusedProjItem* items, int n)
     parts[k] = static_cast<double*>(ws_take(ctx, tn_part_bytes(it.N, it.M, it.batch, ctx->split_limit)));
     splits[k] = ns;
     const int s = t.nsys++;
-    const int used = ntiles * ns * it.batch;
+    const int used = 2 * ntiles * ns * it.batch;
     t.wg0[s] = total;
     t.used[s] = used;
     t.A[s] = it.A;
@@ -2022,7 +2090,7 @@ hipError_t launch_tn_sym_fused(lrdm_ctx* ctx, const FusedProjItem* items, int n)
 }
 
 hipError_t launch_backproj_fused(lrdm_ctx* ctx, const FusedBackprojItem* items, int n) {
-  const int smem = NST * 2 * TB + PW * 64 * (int)sizeof(double);
+  const int smem = NST * (HB + TB) + 2 * BT * (int)sizeof(double);
   LRDM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&backproj_fused_kernel),
                                hipFuncAttributeMaxDynamicSharedMemorySize, smem));
   FusedBackproj t{};
@@ -2033,7 +2101,7 @@ hipError_t launch_backproj_fused(lrdm_ctx* ctx, const FusedBackprojItem* items, 
     t.wg0[t.nsys] = total;
     {
       ProfScope prof(ctx, "backproj");
-      backproj_fused_kernel<<<(unsigned)total, PT, smem, ctx->stream>>>(t, ctx->zeros);
+      backproj_fused_kernel<<<(unsigned)total, HT, smem, ctx->stream>>>(t, ctx->zeros);
     }
     t = FusedBackproj{};
     t.nsys = 0;

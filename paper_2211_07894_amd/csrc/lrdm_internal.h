@@ -262,7 +262,8 @@ enum { TN_VAR_DEFAULT = 0, TN_VAR_STAGED = 1, TN_VAR_SPLIT = 2 };
 enum { BP_VAR_NARROW = 0, BP_VAR_WIDE = 1 };
 int tn_variant(const lrdm_ctx* ctx, int N, int64_t M, int batch, int arith, bool weighted);
 // The split count a projection launch uses: the autotuned one for this shape if
-// lrdm_autotune chose one, else tn_splits.
+// lrdm_autotune chose one, else the arithmetic's default.
+int tn_default_splits(int N, int64_t M, int batch, int arith);
 int tn_split_count(const lrdm_ctx* ctx, int N, int64_t M, int batch, int arith, bool weighted);
 // T is the storage type of A and B; prec selects the arithmetic (LRDM_FP64: FP64
 // matrix cores on either storage type; LRDM_FP32 / LRDM_BF16X3: FP32 storage only).
