@@ -555,15 +555,21 @@ hipError_t launch_tn_sym_f64(lrdm_ctx* ctx, const SA* A, const SB* B, const doub
   int64_t kchunk = (M + ns - 1) / ns;
   kchunk = (kchunk + KT - 1) / KT * KT;
   double* part = static_cast<double*>(ws_take(ctx, tn_part_bytes(N, M, batch, ctx->split_limit)));
-  if (tn_direct_ok(N, M, batch)) {
-    // the autotuned count, relative to the default one, scales the number of ranges
-    const TnDirectPlan p = tn_direct_plan(N, M, batch, tn_part_bytes(N, M, batch, ctx->split_limit),
-                                          (double)ns / tn_splits(ntiles * batch, M));
-    if (B)
-      return launch_tn_direct<SA, SB>(ctx, p, A, B, w, w_stride, N, M, nspin, batch, part, H, active,
-                                      static_cast<const void*>(A) == static_cast<const void*>(B));
-    return launch_tn_direct<SA, SA>(ctx, p, A, A, w, w_stride, N, M, nspin, batch, part, H, active,
-                                    true);
+  // A block held in FP32 keeps the 128-row tiles and the order of their sums: the basis
+  // an ill-conditioned filtered block is orthonormalised to is rounded to FP32, so that
+  // a Gram matrix off by one rounding moves its Ritz pairs by far more.
+  constexpr bool fp32 = sizeof(SA) == sizeof(float);
+  if constexpr (!fp32) {
+    if (tn_direct_ok(N, M, batch)) {
+      // the autotuned count, relative to the default one, scales the number of ranges
+      const TnDirectPlan p = tn_direct_plan(N, M, batch, tn_part_bytes(N, M, batch, ctx->split_limit),
+                                            (double)ns / tn_splits(ntiles * batch, M));
+      if (B)
+        return launch_tn_direct<SA, SB>(ctx, p, A, B, w, w_stride, N, M, nspin, batch, part, H, active,
+                                        static_cast<const void*>(A) == static_cast<const void*>(B));
+      return launch_tn_direct<SA, SA>(ctx, p, A, A, w, w_stride, N, M, nspin, batch, part, H, active,
+                                      true);
+    }
   }
   const unsigned grd = (unsigned)(ntiles * ns * batch);
   {

@@ -274,13 +274,5 @@ template hipError_t launch_tn_direct<double, double>(lrdm_ctx*, const TnDirectPl
                                                      const double*, const double*, const double*,
                                                      int64_t, int, int64_t, int, int, double*,
                                                      double*, const unsigned char*, bool);
-template hipError_t launch_tn_direct<float, float>(lrdm_ctx*, const TnDirectPlan&, const float*,
-                                                   const float*, const double*, int64_t, int,
-                                                   int64_t, int, int, double*, double*,
-                                                   const unsigned char*, bool);
-template hipError_t launch_tn_direct<float, double>(lrdm_ctx*, const TnDirectPlan&, const float*,
-                                                    const double*, const double*, int64_t, int,
-                                                    int64_t, int, int, double*, double*,
-                                                    const unsigned char*, bool);
 
 }  // namespace lrdm
