@@ -1581,8 +1581,6 @@ extern "C" lrdm_status lrdm_autotune(lrdm_ctx* ctx, const lrdm_grid* grid, int32
     hipError_t e = launch_pattern(ctx, A, (int64_t)nspin * N * g.M, prec == LRDM_FP64);
     if (e == hipSuccess) e = launch_pattern(ctx, w, (int64_t)batch * g.M, true);
     if (e != hipSuccess) return fail_hip(ctx, "lrdm_autotune", e);
-    const int ntb = (N + 127) / 128;
-    const int ntiles = ntb * (ntb + 1) / 2;
     const int arith = prec == LRDM_FP64 ? TN_ARITH_F64
                                         : (prec == LRDM_FP32 ? TN_ARITH_F32 : TN_ARITH_BF16X3);
     // three contractions: the response's projection of all directions, the
@@ -1594,8 +1592,8 @@ extern "C" lrdm_status lrdm_autotune(lrdm_ctx* ctx, const lrdm_grid* grid, int32
     } kinds[3] = {{batch, arith, true}, {nspin, arith, true}, {1, TN_ARITH_F64, false}};
     for (int k = 0; k < 3; ++k) {
       const Kind& kd = kinds[k];
-      const int h = tn_default_splits(N, g.M, kd.b, kd.arith);
-      const int cap = tn_split_cap(ntiles * kd.b, g.M);
+      const int h = tn_default_splits(N, g.M, kd.b, kd.arith, ctx->split_limit);
+      const int cap = tn_range_cap(N, g.M, kd.b, ctx->split_limit);
       const std::array<int64_t, 5> key{N, g.M, kd.b, kd.arith, kd.weighted ? 1 : 0};
       int best = h, best_v = TN_VAR_DEFAULT;
       double best_ms = 1e300;

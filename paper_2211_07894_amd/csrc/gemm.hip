@@ -178,23 +178,50 @@ __global__ __launch_bounds__(256, 2) void tn_sym_f64_kernel(
       }
 }
 
-// H[b][i][j] = sum over splits (fixed order) of the partial tile holding (i, j),
-// i <= j read from the upper tile and mirrored.
-__global__ void tn_reduce_kernel(const double* __restrict__ part, int N, int ntb, int nsplit,
+// H[b][i][j] = H[b][j][i] = the sum over the splits of the partial tile (edge T) holding
+// (i, j), i <= j.  Many splits: eight groups of them in parallel (threadIdx.y), added in
+// a fixed order; few: eight rows per block.
+__global__ __launch_bounds__(256) void tn_reduce_wide_kernel(const double* __restrict__ part,
+                                                             int N, int nt, int T, int nsplit,
+                                                             double* __restrict__ H) {
+  __shared__ double red[8][32];
+  const int b = blockIdx.z, i = blockIdx.y, j = blockIdx.x * 32 + threadIdx.x;
+  if ((int)(blockIdx.x * 32 + 31) < i) return;   // whole block below the diagonal
+  const int ntiles = nt * (nt + 1) / 2;
+  const bool on = j < N && i <= j;
+  double s = 0.0;
+  if (on) {
+    const int ti = i / T, tj = j / T;
+    const int tile = ti * nt - ti * (ti - 1) / 2 + (tj - ti);
+    const double* p = part + ((int64_t)b * nsplit * ntiles + tile) * (T * T) +
+                      (i - ti * T) * T + (j - tj * T);
+    for (int q = threadIdx.y; q < nsplit; q += 8) s += p[(int64_t)q * ntiles * (T * T)];
+  }
+  red[threadIdx.y][threadIdx.x] = s;
+  __syncthreads();
+  if (threadIdx.y == 0 && on) {
+#pragma unroll
+    for (int q = 1; q < 8; ++q) s += red[q][threadIdx.x];
+    H[((int64_t)b * N + i) * N + j] = s;
+    H[((int64_t)b * N + j) * N + i] = s;
+  }
+}
+
+__global__ void tn_reduce_kernel(const double* __restrict__ part, int N, int nt, int T, int nsplit,
                                  double* __restrict__ H) {
   const int b = blockIdx.z;
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   const int i = blockIdx.y * blockDim.y + threadIdx.y;
   if (i >= N || j >= N) return;
   const int ii = min(i, j), jj = max(i, j);
-  const int ti = ii / BT, tj = jj / BT;
+  const int ti = ii / T, tj = jj / T;
   // tile index of (ti, tj) in the upper-triangle enumeration
-  const int tile = ti * ntb - ti * (ti - 1) / 2 + (tj - ti);
-  const int ntiles = ntb * (ntb + 1) / 2;
-  const int r = ii - ti * BT, cc = jj - tj * BT;
+  const int tile = ti * nt - ti * (ti - 1) / 2 + (tj - ti);
+  const int ntiles = nt * (nt + 1) / 2;
+  const double* p = part + ((int64_t)b * nsplit * ntiles + tile) * (T * T) + (ii - ti * T) * T +
+                    (jj - tj * T);
   double s = 0.0;
-  for (int sp = 0; sp < nsplit; ++sp)
-    s += part[(((int64_t)b * nsplit + sp) * ntiles + tile) * (BT * BT) + r * BT + cc];
+  for (int q = 0; q < nsplit; ++q) s += p[(int64_t)q * ntiles * (T * T)];
   H[((int64_t)b * N + i) * N + j] = s;
 }
 
@@ -492,30 +519,56 @@ __global__ __launch_bounds__(256, 2) void adj_psi_f64_kernel(
 
 }  // namespace
 
-size_t tn_part_bytes(int N, int64_t M, int batch, int split_limit) {
+hipError_t launch_tn_reduce(lrdm_ctx* ctx, const double* part, int N, int T, int nsplit, int batch,
+                            double* H, bool in_order) {
+  const int nt = (N + T - 1) / T;
+  if (nsplit >= 16 && !in_order)
+    tn_reduce_wide_kernel<<<dim3((N + 31) / 32, N, batch), dim3(32, 8), 0, ctx->stream>>>(
+        part, N, nt, T, nsplit, H);
+  else
+    tn_reduce_kernel<<<dim3((N + 31) / 32, (N + 7) / 8, batch), dim3(32, 8), 0, ctx->stream>>>(
+        part, N, nt, T, nsplit, H);
+  return hipGetLastError();
+}
+
+// Partial tiles of 128 x 128 a range of points takes, in bytes.
+static size_t tn_range_bytes(int N, int batch) {
   const int ntb = (N + BT - 1) / BT;
-  const int ntiles = ntb * (ntb + 1) / 2;
-  int ns = tn_split_cap(ntiles * batch, M);
-  if (split_limit > 0) ns = std::min(ns, split_limit);
-  const size_t tiles = (size_t)batch * ns * ntiles * BT * BT * sizeof(double);
+  return (size_t)batch * (ntb * (ntb + 1) / 2) * BT * BT * sizeof(double);
+}
+
+// Ranges the partial sums have room for: tn_split_cap, or with a workspace of the
+// preferred size (split_limit 0) as many as fill 96 MiB, each at least 512 points.
+int tn_range_cap(int N, int64_t M, int batch, int split_limit) {
+  const int ntb = (N + BT - 1) / BT;
+  const int cap = tn_split_cap(ntb * (ntb + 1) / 2 * batch, M);
+  if (split_limit > 0) return std::min(cap, split_limit);
+  const int64_t room = (int64_t)(((size_t)96 << 20) / tn_range_bytes(N, batch));
+  return (int)std::max<int64_t>(cap, std::min<int64_t>(room, M / 512));
+}
+
+size_t tn_part_bytes(int N, int64_t M, int batch, int split_limit) {
+  const size_t tiles = tn_range_cap(N, M, batch, split_limit) * tn_range_bytes(N, batch);
   return split_limit > 0 ? tiles : std::max(tiles, tn_direct_bytes(N, M, batch));
 }
 
 // FP32 arithmetic (whose partial sums are grouped by K-tile, so that any count gives the
 // same sums up to the FP64 additions): the count within the workspace whose workgroups,
 // two per tile and two per CU, finish first, each with a fixed cost of twelve K-tiles.
-// 48^3, 256 states, 8 directions: 21
-// ranges (1008 workgroups on 512 slots) take 950 us, 16 (768) take 990.
+// 48^3, 256 states, 8 directions: 21 ranges (1008 workgroups on 512 slots) take 950 us,
+// 16 (768) take 990; 24^3, 32 states, 4 directions: 41 us
+// (512-point ranges), 583 with ranges of at least 2048 points on 128-row tiles.
 // The other arithmetics: tn_splits.
-int tn_default_splits(int N, int64_t M, int batch, int arith) {
+int tn_default_splits(int N, int64_t M, int batch, int arith, int split_limit) {
   const int ntb = (N + BT - 1) / BT;
   const int items = ntb * (ntb + 1) / 2 * batch;
   if (arith != TN_ARITH_F32) return tn_splits(items, M);
-  const int cap = tn_split_cap(items, M);
+  const int cap = tn_range_cap(N, M, batch, split_limit);
+  const int halves = 2 * items - (N - (ntb - 1) * BT <= BT / 2 ? ntb * batch : 0);
   int best = 1;
   double least = 1e300;
   for (int s = 1; s <= cap; ++s) {
-    const double rounds = (double)((2 * (int64_t)items * s + 511) / 512);
+    const double rounds = (double)(((int64_t)halves * s + 511) / 512);
     const double cost = rounds * ((double)((M + KT * s - 1) / (KT * s)) + 12.0);
     if (cost < least) {
       least = cost;
@@ -525,14 +578,37 @@ int tn_default_splits(int N, int64_t M, int batch, int arith) {
   return best;
 }
 
-int tn_split_count(const lrdm_ctx* ctx, int N, int64_t M, int batch, int arith, bool weighted) {
+// Parts each range of a BF16X3 projection with pre-split pieces is cut into: its FP32
+// sums run over groups of 128 points from the range's start, so that a cut between
+// groups leaves them as they are.  One workgroup per tile, part and CU; the cost as above.
+int tn_range_parts(int N, int64_t M, int batch, int nsplit, int64_t kchunk, int split_limit) {
+  const int ntb = (N + BT - 1) / BT;
+  const int64_t wgs = (int64_t)(ntb * (ntb + 1) / 2) * batch * nsplit;
+  const int64_t groups = (kchunk + BT - 1) / BT;
+  const int most = (int)std::min<int64_t>(groups, tn_range_cap(N, M, batch, split_limit) / nsplit);
+  int best = 1;
+  double least = 1e300;
+  for (int q = 1; q <= most; ++q) {
+    const double rounds = (double)((wgs * q + 255) / 256);
+    const double cost = rounds * ((double)((groups + q - 1) / q * (BT / KT)) + 12.0);
+    if (cost < least) {
+      least = cost;
+      best = q;
+    }
+  }
+  return best;
+}
+
+int tn_split_count(const lrdm_ctx* ctx, int N, int64_t M, int batch, int arith, bool weighted,
+                   int order) {
   const int ntb = (N + BT - 1) / BT;
   const int ntiles = ntb * (ntb + 1) / 2;
   const auto it = ctx->tn_tuned.find({N, M, batch, arith, weighted ? 1 : 0});
-  int s = tn_default_splits(N, M, batch, arith);
-  if (it != ctx->tn_tuned.end() && it->second >= 1 && it->second <= tn_split_cap(ntiles * batch, M))
+  int s = tn_default_splits(N, M, batch, order, ctx->split_limit);
+  if (it != ctx->tn_tuned.end() && it->second >= 1 &&
+      it->second <= tn_range_cap(N, M, batch, ctx->split_limit))
     s = it->second;
-  if (ctx->split_limit > 0) s = std::min(s, ctx->split_limit);
+  if (ctx->split_limit > 0) s = std::min(s, std::min(ctx->split_limit, tn_split_cap(ntiles * batch, M)));
   return s;
 }
 
@@ -551,7 +627,7 @@ hipError_t launch_tn_sym_f64(lrdm_ctx* ctx, const SA* A, const SB* B, const doub
                              double* H, const unsigned char* active) {
   const int ntb = (N + BT - 1) / BT;
   const int ntiles = ntb * (ntb + 1) / 2;
-  const int ns = tn_split_count(ctx, N, M, batch, TN_ARITH_F64, w != nullptr);
+  const int ns = tn_split_count(ctx, N, M, batch, TN_ARITH_F64, w != nullptr, TN_ARITH_F64);
   int64_t kchunk = (M + ns - 1) / ns;
   kchunk = (kchunk + KT - 1) / KT * KT;
   double* part = static_cast<double*>(ws_take(ctx, tn_part_bytes(N, M, batch, ctx->split_limit)));
@@ -582,10 +658,7 @@ hipError_t launch_tn_sym_f64(lrdm_ctx* ctx, const SA* A, const SB* B, const doub
                                                                kchunk, ns, batch, active, part);
     LRDM_HIP(hipGetLastError());
   }
-  dim3 blk(32, 8);
-  dim3 grd2((N + 31) / 32, (N + 7) / 8, batch);
-  tn_reduce_kernel<<<grd2, blk, 0, ctx->stream>>>(part, N, ntb, ns, H);
-  return hipGetLastError();
+  return launch_tn_reduce(ctx, part, N, BT, ns, batch, H, fp32);
 }
 template hipError_t launch_tn_sym_f64<double, double>(lrdm_ctx*, const double*, const double*,
                                                       const double*, int64_t, int, int64_t, int,

@@ -322,24 +322,6 @@ __global__ __launch_bounds__(256, 1) void tn_sym_lp_kernel(
       }
 }
 
-// Same fixed-order split sum as the FP64 form.
-__global__ void tn_reduce_lp_kernel(const double* __restrict__ part, int N, int ntb, int nsplit,
-                                    double* __restrict__ H) {
-  const int b = blockIdx.z;
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  const int i = blockIdx.y * blockDim.y + threadIdx.y;
-  if (i >= N || j >= N) return;
-  const int ii = min(i, j), jj = max(i, j);
-  const int ti = ii / BT, tj = jj / BT;
-  const int tile = ti * ntb - ti * (ti - 1) / 2 + (tj - ti);
-  const int ntiles = ntb * (ntb + 1) / 2;
-  const int r = ii - ti * BT, cc = jj - tj * BT;
-  double s = 0.0;
-  for (int q = 0; q < nsplit; ++q)
-    s += part[(((int64_t)b * nsplit + q) * ntiles + tile) * (BT * BT) + r * BT + cc];
-  H[((int64_t)b * N + i) * N + j] = s;
-}
-
 __global__ void to_f32_kernel(const double* __restrict__ x, float* __restrict__ y, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) y[i] = (float)x[i];
@@ -1215,12 +1197,15 @@ __global__ __launch_bounds__(PT, 1) void adj_psi_p3_kernel(
 // Projection, BF16X3, pre-split B: H[b] = (w o A_c) B_c^T with A = B = Psi; A
 // FP32 tiles weighted and split in the kernel, B from the pieces P3
 // [nspin][3][N][M].  Same grid and partial layout as tn_sym_pipe_kernel; M a
-// multiple of 8, aligned rows.
+// multiple of 8, aligned rows.  PARTS: blockIdx.y names a part of kpart points of the
+// range; the form without keeps its 236 registers and the 1 % that the other 12 cost
+// (64^3, 1024 states, 16 directions: 26.3 ms against 26.6).
+template <bool PARTS>
 __global__ __launch_bounds__(PT, 1) void tn_sym_p3_kernel(
     const float* __restrict__ A, const __bf16* __restrict__ P3, const double* __restrict__ w,
-    int64_t w_stride, int N, int64_t M, int nspin, int ntb, int64_t kchunk, int nsplit, int batch,
-    const unsigned char* __restrict__ active, const float* __restrict__ zeros,
-    double* __restrict__ part) {
+    int64_t w_stride, int N, int64_t M, int nspin, int ntb, int64_t kchunk, int nsplit,
+    int64_t kpart, int batch, const unsigned char* __restrict__ active,
+    const float* __restrict__ zeros, double* __restrict__ part) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_pipe[];
   constexpr int SB = TB + 3 * PB + 1024;   // A (FP32), B pieces, weights
   const int ntiles = ntb * (ntb + 1) / 2;
@@ -1236,9 +1221,13 @@ __global__ __launch_bounds__(PT, 1) void tn_sym_p3_kernel(
   const float* Ac = A + (int64_t)c * N * M;
   const __bf16* Pc = P3 + (int64_t)c * 3 * N * M;
   const double* wb = w + (int64_t)b * w_stride;
-  const int64_t kbeg = (int64_t)sp * kchunk;
+  int64_t kbeg = (int64_t)sp * kchunk, kstop = min(M, kbeg + kchunk);
+  if (PARTS) {
+    kbeg += blockIdx.y * kpart;
+    kstop = min(kstop, kbeg + kpart);
+  }
   // an inactive block (blocks.h) keeps a zero partial tile
-  const int64_t kend = block_active(active, c, ntb, ti, tj) ? min(M, kbeg + kchunk) : kbeg;
+  const int64_t kend = block_active(active, c, ntb, ti, tj) ? kstop : kbeg;
   const int nk = kbeg < kend ? (int)((kend - kbeg + KT - 1) / KT) : 0;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const int wr = wid >> 1, wc = wid & 1;
@@ -1331,7 +1320,8 @@ __global__ __launch_bounds__(PT, 1) void tn_sym_p3_kernel(
       flush_pipe(cc, 1.0, acc);
     }
   wait_stage<0>();
-  double* out = part + (((int64_t)b * nsplit + sp) * ntiles + tile) * (BT * BT);
+  double* out = part + ((PARTS ? ((int64_t)b * nsplit + sp) * gridDim.y + blockIdx.y
+                              : (int64_t)b * nsplit + sp) * ntiles + tile) * (BT * BT);
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -1741,22 +1731,22 @@ hipError_t launch_tn_sym<float>(lrdm_ctx* ctx, const float* A, const float* B, c
     return launch_tn_sym_f64<float, float>(ctx, A, B, w, w_stride, N, M, nspin, batch, H, active);
   const int ntb = (N + BT - 1) / BT;
   const int ntiles = ntb * (ntb + 1) / 2;
-  const int ns = tn_split_count(ctx, N, M, batch,
-                                prec == LRDM_BF16X3 ? TN_ARITH_BF16X3 : TN_ARITH_F32, w != nullptr);
-  int64_t kchunk = (M + ns - 1) / ns;
-  kchunk = (kchunk + KT - 1) / KT * KT;
-  double* part = static_cast<double*>(ws_take(ctx, tn_part_bytes(N, M, batch, ctx->split_limit)));
   if (!B) B = A;
   auto a16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
   // the pipelined kernel copies 16-byte chunks of rows: rows must start aligned
   const bool pipe = (M % 4 == 0) && a16(A) && a16(B) && (!w || (a16(w) && w_stride % 2 == 0));
-  const unsigned grd = (unsigned)(ntiles * ns * batch);
+  const int arith = prec == LRDM_BF16X3 ? TN_ARITH_BF16X3 : TN_ARITH_F32;
   // the tile and wave layout lrdm_autotune chose for this shape (default otherwise)
-  const int variant = tn_variant(ctx, N, M, batch,
-                                 prec == LRDM_BF16X3 ? TN_ARITH_BF16X3 : TN_ARITH_F32,
-                                 w != nullptr);
-  if (variant == TN_VAR_DEFAULT && pipe && w && B == A && prec == LRDM_BF16X3 && M % 8 == 0 &&
-      nspin <= 2) {
+  const int variant = tn_variant(ctx, N, M, batch, arith, w != nullptr);
+  const bool p3 = variant == TN_VAR_DEFAULT && pipe && w && B == A && prec == LRDM_BF16X3 &&
+                  M % 8 == 0 && nspin <= 2;
+  const int ns = tn_split_count(ctx, N, M, batch, arith, w != nullptr,
+                                p3 ? TN_ARITH_BF16X3 : TN_ARITH_F32);
+  int64_t kchunk = (M + ns - 1) / ns;
+  kchunk = (kchunk + KT - 1) / KT * KT;
+  double* part = static_cast<double*>(ws_take(ctx, tn_part_bytes(N, M, batch, ctx->split_limit)));
+  const unsigned grd = (unsigned)(ntiles * ns * batch);
+  if (p3) {
     // pieces of Psi once per call (or those the context holds for this block), then
     // the weighted A side split in the kernel
     const lrdm_psi_pieces& pc = ctx->pieces;
@@ -1773,20 +1763,20 @@ hipError_t launch_tn_sym<float>(lrdm_ctx* ctx, const float* A, const float* B, c
       }
       P3 = P;
     }
+    const int parts = tn_range_parts(N, M, batch, ns, kchunk, ctx->split_limit);
+    const int64_t kpart = ((kchunk + BT - 1) / BT + parts - 1) / parts * BT;
     const int smem = NST * (TB + 3 * PB + 1024);
-    LRDM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tn_sym_p3_kernel),
+    const auto kernel = parts > 1 ? tn_sym_p3_kernel<true> : tn_sym_p3_kernel<false>;
+    LRDM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, smem));
     {
       ProfScope prof(ctx, "proj");
-      tn_sym_p3_kernel<<<grd, PT, smem, ctx->stream>>>(A, P3, w, w_stride, N, M, nspin, ntb,
-                                                       kchunk, ns, batch, active, ctx->zeros,
-                                                       part);
+      kernel<<<dim3(grd, parts), PT, smem, ctx->stream>>>(
+          A, P3, w, w_stride, N, M, nspin, ntb, kchunk, ns, kpart, batch, active, ctx->zeros,
+          part);
       LRDM_HIP(hipGetLastError());
     }
-    dim3 blk(32, 8);
-    dim3 grd2((N + 31) / 32, (N + 7) / 8, batch);
-    tn_reduce_lp_kernel<<<grd2, blk, 0, ctx->stream>>>(part, N, ntb, ns, H);
-    return hipGetLastError();
+    return launch_tn_reduce(ctx, part, N, BT, ns * parts, batch, H);
   }
   const int smem = NST * (HB + TB + (w ? 1024 : 0));
   auto run_pipe = [&](auto kernel) -> hipError_t {
@@ -1813,10 +1803,7 @@ hipError_t launch_tn_sym<float>(lrdm_ctx* ctx, const float* A, const float* B, c
       LRDM_HIP(bf ? run_pipe(tn_sym_pipe_kernel<Core::BF3, false>)
                   : run_pipe(tn_sym_pipe_kernel<Core::F32, false>));
   }
-  dim3 blk(32, 8);
-  dim3 grd2((N + 31) / 32, (N + 7) / 8, batch);
-  tn_reduce_lp_kernel<<<grd2, blk, 0, ctx->stream>>>(part, N, ntb, ns, H);
-  return hipGetLastError();
+  return launch_tn_reduce(ctx, part, N, BT, ns, batch, H);
 }
 
 template <>
@@ -2041,11 +2028,22 @@ hipError_t launch_tn_sym_fused(lrdm_ctx* ctx, const FusedProjItem* items, int n)
   const auto order = by_work(items, n, [](const FusedProjItem& it) {
     return (double)it.M * it.N * it.N * it.batch;
   });
+  auto tiles_of = [](const FusedProjItem& it) {
+    const int ntb = (it.N + BT - 1) / BT;
+    return ntb * (ntb + 1) / 2 * it.batch;
+  };
+  // Systems that fill the 512 slots together with ranges as long as tn_split_cap leaves
+  // them keep those: six systems of 32^3 to 56^3 (64 to 512
+  // states) take 36.3 ms, with the shorter ranges 36.6.
+  int64_t filled = 0;
+  for (int k = 0; k < n; ++k)
+    filled += 2 * (int64_t)tiles_of(items[k]) * tn_split_cap(tiles_of(items[k]), items[k].M);
   for (int k : order) {
     const FusedProjItem& it = items[k];
     const int ntb = (it.N + BT - 1) / BT;
     const int ntiles = ntb * (ntb + 1) / 2;
-    const int ns = tn_split_count(ctx, it.N, it.M, it.batch, TN_ARITH_F32, true);
+    int ns = tn_split_count(ctx, it.N, it.M, it.batch, TN_ARITH_F32, true, TN_ARITH_F32);
+    if (filled >= 1024) ns = std::min(ns, tn_split_cap(tiles_of(it), it.M));
     int64_t kchunk = (it.M + ns - 1) / ns;
     kchunk = (kchunk + KT - 1) / KT * KT;
     const bool pipe = it.M % 4 == 0 && a16(it.A) && a16(it.w) &&
@@ -2080,11 +2078,7 @@ hipError_t launch_tn_sym_fused(lrdm_ctx* ctx, const FusedProjItem* items, int n)
   for (int k = 0; k < n; ++k) {
     if (!parts[k]) continue;
     const FusedProjItem& it = items[k];
-    const int ntb = (it.N + BT - 1) / BT;
-    dim3 blk(32, 8);
-    dim3 grd2((it.N + 31) / 32, (it.N + 7) / 8, it.batch);
-    tn_reduce_lp_kernel<<<grd2, blk, 0, ctx->stream>>>(parts[k], it.N, ntb, splits[k], it.H);
-    LRDM_HIP(hipGetLastError());
+    LRDM_HIP(launch_tn_reduce(ctx, parts[k], it.N, BT, splits[k], it.batch, it.H));
   }
   return hipSuccess;
 }

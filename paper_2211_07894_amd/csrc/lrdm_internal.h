@@ -261,10 +261,19 @@ enum { TN_VAR_DEFAULT = 0, TN_VAR_STAGED = 1, TN_VAR_SPLIT = 2 };
 //                 FP32 sums over a whole row block of Gamma
 enum { BP_VAR_NARROW = 0, BP_VAR_WIDE = 1 };
 int tn_variant(const lrdm_ctx* ctx, int N, int64_t M, int batch, int arith, bool weighted);
-// The split count a projection launch uses: the autotuned one for this shape if
-// lrdm_autotune chose one, else the arithmetic's default.
-int tn_default_splits(int N, int64_t M, int batch, int arith);
-int tn_split_count(const lrdm_ctx* ctx, int N, int64_t M, int batch, int arith, bool weighted);
+// The split count a projection launch uses: the autotuned one for this shape and
+// arithmetic if lrdm_autotune chose one, else the default of `order`, the arithmetic
+// whose sums bind the count (TN_ARITH_F32 where FP32 sums end with each K-tile).
+int tn_default_splits(int N, int64_t M, int batch, int order, int split_limit);
+int tn_split_count(const lrdm_ctx* ctx, int N, int64_t M, int batch, int arith, bool weighted,
+                   int order);
+// H [batch][N][N] from the partial tiles [batch][nsplit][upper tiles][T][T]; in_order:
+// added one after the other.
+hipError_t launch_tn_reduce(lrdm_ctx* ctx, const double* part, int N, int T, int nsplit, int batch,
+                            double* H, bool in_order = false);
+// Ranges the partial sums have room for, and the parts a BF16X3 range is cut into.
+int tn_range_cap(int N, int64_t M, int batch, int split_limit);
+int tn_range_parts(int N, int64_t M, int batch, int nsplit, int64_t kchunk, int split_limit);
 // T is the storage type of A and B; prec selects the arithmetic (LRDM_FP64: FP64
 // matrix cores on either storage type; LRDM_FP32 / LRDM_BF16X3: FP32 storage only).
 // active (blocks.h, may be NULL): the tiles of inactive blocks are left at zero.

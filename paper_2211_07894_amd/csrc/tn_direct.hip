@@ -175,34 +175,6 @@ __global__ __launch_bounds__(64 * KW, 2) void tn_direct_kernel(
   }
 }
 
-// H[b][i][j] = H[b][j][i] = sum over the splits of the partial tile holding (i, j),
-// i <= j: eight groups of splits in parallel (threadIdx.y), added in a fixed order.
-__global__ __launch_bounds__(256) void tn_direct_reduce_kernel(const double* __restrict__ part,
-                                                               int N, int nt, int T, int nsplit,
-                                                               double* __restrict__ H) {
-  __shared__ double red[8][32];
-  const int b = blockIdx.z, i = blockIdx.y, j = blockIdx.x * 32 + threadIdx.x;
-  if ((int)(blockIdx.x * 32 + 31) < i) return;   // whole block below the diagonal
-  const int ntiles = nt * (nt + 1) / 2;
-  const bool on = j < N && i <= j;
-  double s = 0.0;
-  if (on) {
-    const int ti = i / T, tj = j / T;
-    const int tile = ti * nt - ti * (ti - 1) / 2 + (tj - ti);
-    const double* p = part + ((int64_t)b * nsplit * ntiles + tile) * (T * T) +
-                      (i - ti * T) * T + (j - tj * T);
-    for (int q = threadIdx.y; q < nsplit; q += 8) s += p[(int64_t)q * ntiles * (T * T)];
-  }
-  red[threadIdx.y][threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.y == 0 && on) {
-#pragma unroll
-    for (int q = 1; q < 8; ++q) s += red[q][threadIdx.x];
-    H[((int64_t)b * N + i) * N + j] = s;
-    H[((int64_t)b * N + j) * N + i] = s;
-  }
-}
-
 }  // namespace
 
 int tn_direct_tile(int N) { return N <= 32 ? 32 : 64; }
@@ -266,9 +238,7 @@ hipError_t launch_tn_direct(lrdm_ctx* ctx, const TnDirectPlan& p, const SA* A, c
     }
     LRDM_HIP(hipGetLastError());
   }
-  tn_direct_reduce_kernel<<<dim3((N + 31) / 32, N, batch), dim3(32, 8), 0, ctx->stream>>>(
-      part, N, nt, p.tile, p.nsplit, H);
-  return hipGetLastError();
+  return launch_tn_reduce(ctx, part, N, p.tile, p.nsplit, batch, H);
 }
 template hipError_t launch_tn_direct<double, double>(lrdm_ctx*, const TnDirectPlan&,
                                                      const double*, const double*, const double*,

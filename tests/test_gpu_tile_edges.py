@@ -71,6 +71,28 @@ def test_projection_under_a_workspace_limit():
     ctx.close()
 
 
+# ranges and parts of ranges at both sides of their lines; a sum of 128 (BF16X3, pieces
+# of 2^-24) or 32 products in FP32 under a FP64 sum is off by at most that many roundings
+# of its terms' absolute sum, again about sqrt(M) times the result
+@pytest.mark.parametrize("prec", ["fp32", "bf16x3"])
+@pytest.mark.parametrize("n,N,nspin,r", [
+    ((8, 8, 8), 16, 1, 1), ((16, 16, 16), 64, 2, 1), ((24, 24, 24), 32, 1, 4),
+    ((25, 24, 23), 65, 1, 2), ((27, 33, 35), 90, 2, 1), ((48, 48, 16), 256, 1, 9),
+    ((40, 40, 40), 129, 1, 1),
+])
+def test_projection_fp32(prec, n, N, nspin, r):
+    grid, gen = _grid(n), _gen(N + r)
+    P = _rand(gen, nspin, N, grid.M, dtype=torch.float32)
+    dV = _rand(gen, r, nspin, grid.M)
+    H = L.projected_perturbation(grid, P, dV, nspin, prec)
+    bound = (32 if prec == "fp32" else 128) * grid.M ** 0.5 * 2.0 ** -24
+    for k in range(r):
+        for c in range(nspin):
+            ref = (P[c].double() * dV[k, c]) @ P[c].double().t()
+            assert _rel(H[k, c], ref) < bound
+            assert torch.equal(H[k, c], H[k, c].t())
+
+
 def _chebyshev(grid, V, X, degree, a, b, a0):
     """The scaled recurrence in FP64 by shifts."""
     h = [grid.L[d] / grid.n[d] for d in range(3)]
