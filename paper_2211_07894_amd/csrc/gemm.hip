@@ -681,6 +681,8 @@ template <>
 hipError_t launch_backproj<double>(lrdm_ctx* ctx, const double* A, const double* G, int N,
                                    int64_t M, int nspin, int batch, lrdm_prec, double scale,
                                    const double* sub, double* out, const unsigned char* active) {
+  if (backproj_direct_ok(N))
+    return launch_backproj_direct(ctx, A, G, N, M, nspin, batch, scale, sub, out, active);
   const unsigned grd = (unsigned)((M + BT - 1) / BT * batch);
   ProfScope prof(ctx, "backproj");
   backproj_f64_kernel<<<grd, 256, 0, ctx->stream>>>(A, G, N, M, nspin, batch, scale, sub, active,

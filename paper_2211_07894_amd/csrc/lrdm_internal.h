@@ -322,6 +322,11 @@ template <typename T>
 hipError_t launch_backproj(lrdm_ctx* ctx, const T* A, const double* G, int N, int64_t M, int nspin,
                            int batch, lrdm_prec prec, double scale, const double* sub,
                            double* out, const unsigned char* active = nullptr);
+// FP64, few states (backproj_direct.hip).
+bool backproj_direct_ok(int N);
+hipError_t launch_backproj_direct(lrdm_ctx* ctx, const double* A, const double* G, int N,
+                                  int64_t M, int nspin, int batch, double scale,
+                                  const double* sub, double* out, const unsigned char* active);
 
 // The FP32-form projection and back-projection of several independent systems,
 // each in one launch over all of them (gemm_lp.hip): H = Psi^T diag(w) Psi per

@@ -219,6 +219,7 @@ inline void global_load_lds(const void* src, void* base, unsigned size) {
 // instruction-scheduling hints: nothing to do on the CPU
 #define __builtin_amdgcn_sched_group_barrier(mask, count, id) ((void)0)
 #define __builtin_amdgcn_sched_barrier(mask) ((void)0)
+#define __builtin_amdgcn_readfirstlane(x) (x)   // of values the wave agrees on
 
 inline void __syncthreads() { lrdm_emu::yield_wait(1); }
 template <typename T>

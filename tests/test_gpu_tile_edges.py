@@ -93,6 +93,43 @@ def test_projection_fp32(prec, n, N, nspin, r):
             assert torch.equal(H[k, c], H[k, c].t())
 
 
+# both sides of every line of the back-projection's rule, short strips and points.  H' is
+# off by M^1.5 u as above, and so is the density its entries add up to; the sums over the
+# N^2 pairs add N^2 u at most
+@pytest.mark.parametrize("n,N,nspin,r", [
+    ((9, 7, 5), 16, 1, 1), ((9, 7, 5), 17, 2, 3), ((16, 16, 16), 32, 1, 2),
+    ((16, 16, 16), 33, 2, 5), ((13, 12, 11), 160, 1, 2), ((13, 12, 11), 161, 2, 1),
+    ((11, 10, 12), 256, 1, 3), ((11, 10, 12), 257, 1, 1), ((12, 12, 12), 512, 1, 2),
+    ((12, 12, 12), 513, 1, 1), ((40, 40, 40), 40, 1, 6),
+])
+def test_response_fp64(n, N, nspin, r):
+    grid, gen = _grid(n), _gen(N + r)
+    P = _rand(gen, nspin, N, grid.M)
+    dV = _rand(gen, r, nspin, grid.M)
+    eps = torch.linspace(-1.0, 0.5, N, device="cuda", dtype=torch.float64)
+    eps = torch.stack([eps + 0.01 * c for c in range(nspin)]).contiguous()
+    kT = 0.05
+    occ = L.Occupation(nspin, kT, float(N if nspin == 1 else N // 2))
+    out, mu, dmu = L.density_response(grid, P, eps, occ, dV, "fp64")
+    dv = 1.0
+    for length, points in zip(grid.L, grid.n):
+        dv *= length / points
+    s = 2.0 if nspin == 1 else 1.0
+    out = out.reshape(r, nspin, grid.M)
+    ref = torch.empty_like(out)
+    for c in range(nspin):
+        y = (eps[c] - mu) / kT
+        f, g = torch.sigmoid(-y), torch.sigmoid(y)
+        z = -(y[:, None] - y[None, :]).abs()
+        phi = torch.where(z == 0, torch.ones_like(z), torch.expm1(z) / z)
+        low = (y[:, None] <= y[None, :])
+        F = -torch.where(low, f[:, None] * g[None, :], f[None, :] * g[:, None]) * phi / kT
+        for k in range(r):
+            G = F * ((P[c] * dV[k, c]) @ P[c].t()) + dmu[k] * torch.diag(f * g / kT)
+            ref[k, c] = s / dv * ((G @ P[c]) * P[c]).sum(0)
+    assert _rel(out, ref) < (4 * grid.M ** 1.5 + N * N) * 2.0 ** -53
+
+
 def _chebyshev(grid, V, X, degree, a, b, a0):
     """The scaled recurrence in FP64 by shifts."""
     h = [grid.L[d] / grid.n[d] for d in range(3)]
