@@ -6,6 +6,8 @@
 // of 2 pi m j / n (m < n/2); for even n the last column (-1)^j / sqrt(n).  The
 // eigenvalue of a column with frequency m is (2 - 2 cos(2 pi m / n)) / h^2.
 // The transform is three passes of a dense n x n matrix along x, y and z.
+#include <algorithm>
+
 #include "lrdm_internal.h"
 
 namespace lrdm {
@@ -18,11 +20,22 @@ __device__ inline int freq_of(int col, int n) {
   return (col + 1) / 2;
 }
 
-// U_d[j][col] and lam_d[col] for the three axes, packed: axis d at offset base_d.
-__global__ void basis_kernel(int n, double h, double* __restrict__ U, double* __restrict__ lam) {
+struct Axes {
+  int n[3];
+  double h[3];
+  double* U[3];     // [n][n]
+  double* lam[3];   // [n]
+};
+
+// U[j][col] and lam[col] of axis blockIdx.z.
+__global__ void basis_kernel(Axes ax) {
+  const int d = blockIdx.z, n = ax.n[d];
+  const double h = ax.h[d];
+  double* __restrict__ U = ax.U[d];
+  double* __restrict__ lam = ax.lam[d];
   const int col = blockIdx.x * blockDim.x + threadIdx.x;
   const int j = blockIdx.y;
-  if (col >= n) return;
+  if (col >= n || j >= n) return;
   const int m = freq_of(col, n);
   double v;
   if (col == 0) {
@@ -134,6 +147,144 @@ __global__ __launch_bounds__(256) void axis_lds_kernel(const double* __restrict_
   }
 }
 
+// Grids of at most kLdsAxis points an axis take three passes over memory instead of eight:
+// x and y forward on whole planes, z forward, the symbol and z back on runs of
+// columns, y and x back on planes.  A pass is a product of the axis basis and the tile,
+// both in LDS, on the FP64 matrix cores (the vector units have the same rate, but a wave
+// reads 8 bytes of LDS per 32 products for them, where an outer product held in registers
+// needs four times that); sizes are padded to 16 with zeros.
+// 64^3, 16 directions: 131 us against 510 with an LDS pass per axis; 48^3, 8 directions
+// 50 against 186; 24^3, 4 directions 20 against 57, most of it the launches (4 for 11).
+typedef double d4 __attribute__((ext_vector_type(4)));
+constexpr int kHartreeThreads = 512;
+constexpr int kTiles = 2;   // of a wave: 16 of a plane's or a run's 64 x 64 at most
+
+__host__ __device__ constexpr int pad16(int n) { return (n + 15) & ~15; }
+// Row strides in LDS: sixteen rows at one column lie in different banks.
+__host__ __device__ constexpr int lds_stride(int n) { return pad16(n) + 2; }
+
+// U into LDS, zero past n.
+__device__ inline void stage_basis(const double* __restrict__ U, int n, double* Us) {
+  const int m = pad16(n), st = lds_stride(n);
+  const int k = threadIdx.x & 63;
+  if (k < m)
+    for (int j = threadIdx.x >> 6; j < m; j += kHartreeThreads / 64)
+      Us[j * st + k] = j < n && k < n ? U[(int64_t)j * n + k] : 0.0;
+}
+
+// Along the rows of T (ROWS: out[l][k] = sum_j coef(j, k) T[l][j]) or its columns
+// (out[k][l] = sum_j coef(j, k) T[j][l]), in place; coef = U[j][k], INV: U[k][j].
+// n along the axis, m16 lines (padded); every thread of the workgroup calls it.
+template <bool ROWS, bool INV>
+__device__ inline void axis_pass(double* T, int st, const double* Us, int n, int m16) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const int col = lane & 15, g = lane >> 4;
+  const int us = lds_stride(n), nk = pad16(n) / 16, tiles = nk * (m16 / 16);
+  d4 acc[kTiles];
+  int tk[kTiles], tl[kTiles];
+#pragma unroll
+  for (int u = 0; u < kTiles; ++u) {
+    const int tile = wid + u * (kHartreeThreads / 64);
+    tl[u] = tile / nk;
+    tk[u] = tile - tl[u] * nk;
+    acc[u] = d4{0.0, 0.0, 0.0, 0.0};
+    if (tile >= tiles) continue;
+    const double* c = INV ? Us + (16 * tk[u] + col) * us + g : Us + g * us + 16 * tk[u] + col;
+    const double* t = ROWS ? T + (16 * tl[u] + col) * st + g : T + g * st + 16 * tl[u] + col;
+    const int cs = INV ? 1 : us, ts = ROWS ? 1 : st;
+#pragma unroll 4
+    for (int j = 0; j < n; j += 4) {
+      const double a = c[j * cs], b = t[j * ts];
+      acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(ROWS ? b : a, ROWS ? a : b, acc[u], 0, 0, 0);
+    }
+  }
+  __syncthreads();   // every read of T is done
+#pragma unroll
+  for (int u = 0; u < kTiles; ++u) {
+    if (wid + u * (kHartreeThreads / 64) >= tiles) continue;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      if (ROWS)
+        T[(16 * tl[u] + 4 * v + g) * st + 16 * tk[u] + col] = acc[u][v];
+      else
+        T[(16 * tk[u] + 4 * v + g) * st + 16 * tl[u] + col] = acc[u][v];
+    }
+  }
+  __syncthreads();
+}
+
+// Plane blockIdx.x of direction blockIdx.y: forward, the sum of in's channels to out
+// [r][M]; INV, in [r][M] to every channel of out.
+template <bool INV>
+__global__ __launch_bounds__(kHartreeThreads) void hartree_plane_kernel(
+    const double* __restrict__ in, int nspin, double* __restrict__ out, int nx, int ny, int64_t M,
+    const double* __restrict__ Ux, const double* __restrict__ Uy) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_hartree[];
+  double* T = reinterpret_cast<double*>(smem_hartree);   // [ny16][st]
+  const int st = lds_stride(nx), ny16 = pad16(ny);
+  double* Us = T + ny16 * st;
+  const int64_t plane = (int64_t)blockIdx.x * nx * ny;
+  const int x = threadIdx.x & 63, y0 = threadIdx.x >> 6;
+  constexpr int DY = kHartreeThreads / 64;
+  stage_basis(INV ? Uy : Ux, INV ? ny : nx, Us);
+  const int nin = INV ? 1 : nspin;
+  const double* src = in + (int64_t)blockIdx.y * nin * M + plane;
+  if (x < pad16(nx))
+    for (int y = y0; y < ny16; y += DY) {
+      double s = 0.0;
+      if (x < nx && y < ny)
+        for (int c = 0; c < nin; ++c) s += src[(int64_t)c * M + y * nx + x];
+      T[y * st + x] = s;
+    }
+  __syncthreads();
+  if (INV) axis_pass<false, true>(T, st, Us, ny, pad16(nx));
+  else axis_pass<true, false>(T, st, Us, nx, ny16);
+  stage_basis(INV ? Ux : Uy, INV ? nx : ny, Us);
+  __syncthreads();
+  if (INV) axis_pass<true, true>(T, st, Us, nx, ny16);
+  else axis_pass<false, false>(T, st, Us, ny, pad16(nx));
+  const int nout = INV ? nspin : 1;
+  double* dst = out + (int64_t)blockIdx.y * nout * M + plane;
+  if (x < nx)
+    for (int y = y0; y < ny; y += DY) {
+      const double v = T[y * st + x];
+      for (int c = 0; c < nout; ++c) dst[(int64_t)c * M + y * nx + x] = v;
+    }
+}
+
+// W columns (points of the plane from blockIdx.x W on) of direction blockIdx.y, in
+// place: z forward, the symbol, z back.
+__global__ __launch_bounds__(kHartreeThreads) void hartree_column_kernel(
+    double* __restrict__ c, int nx, int ny, int nz, int W, const double* __restrict__ Uz,
+    const double* __restrict__ lx, const double* __restrict__ ly, const double* __restrict__ lz) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem_hartree[];
+  double* T = reinterpret_cast<double*>(smem_hartree);   // [nz16][st]
+  const int st = lds_stride(W), nz16 = pad16(nz);
+  double* Us = T + nz16 * st;
+  const int P = nx * ny;
+  const int i = threadIdx.x % W, z0 = threadIdx.x / W, dz = kHartreeThreads / W;
+  const int p = blockIdx.x * W + i;
+  double* col = c + (int64_t)blockIdx.y * P * nz + p;
+  stage_basis(Uz, nz, Us);
+  for (int z = z0; z < nz16; z += dz)
+    T[z * st + i] = z < nz && p < P ? col[(int64_t)z * P] : 0.0;
+  __syncthreads();
+  axis_pass<false, false>(T, st, Us, nz, W);
+  if (p < P) {
+    const int y = p / nx, x = p - y * nx;
+    for (int z = z0; z < nz; z += dz) {
+      const double lam = lx[x] + ly[y] + lz[z];
+      const double four_pi = 12.566370614359172953850573533118;
+      const double v = T[z * st + i];
+      T[z * st + i] = (p == 0 && z == 0) ? 0.0 : v * (four_pi / lam);
+    }
+  }
+  __syncthreads();
+  axis_pass<false, true>(T, st, Us, nz, W);
+  if (p < P)
+    for (int z = z0; z < nz; z += dz) col[(int64_t)z * P] = T[z * st + i];
+}
+
 __global__ void sum_channels_kernel(const double* __restrict__ u, int nspin, int64_t M, int r,
                                     double* __restrict__ out) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -185,14 +336,39 @@ hipError_t launch_hartree(lrdm_ctx* ctx, const Grid3& g, const double* u, int u_
   double* lx = Uz + (int64_t)g.nz * g.nz;
   double* ly = lx + g.nx;
   double* lz = ly + g.ny;
-  basis_kernel<<<dim3((g.nx + 63) / 64, g.nx), 64, 0, ctx->stream>>>(g.nx, g.hx, Ux, lx);
-  basis_kernel<<<dim3((g.ny + 63) / 64, g.ny), 64, 0, ctx->stream>>>(g.ny, g.hy, Uy, ly);
-  basis_kernel<<<dim3((g.nz + 63) / 64, g.nz), 64, 0, ctx->stream>>>(g.nz, g.hz, Uz, lz);
+  const Axes ax{{g.nx, g.ny, g.nz}, {g.hx, g.hy, g.hz}, {Ux, Uy, Uz}, {lx, ly, lz}};
+  const int most = std::max(g.nx, std::max(g.ny, g.nz));
+  basis_kernel<<<dim3((most + 63) / 64, most, 3), 64, 0, ctx->stream>>>(ax);
   LRDM_HIP(hipGetLastError());
   const int64_t total = (int64_t)r * g.M;
   const unsigned blocks = (unsigned)((total + 255) / 256);
   double* a = scratch;
   double* b = scratch + total;
+  if (most <= kLdsAxis && r <= 65535) {
+    const int u16 = std::max(pad16(g.nx) * lds_stride(g.nx), pad16(g.ny) * lds_stride(g.ny));
+    const size_t plane = (size_t)(pad16(g.ny) * lds_stride(g.nx) + u16) * sizeof(double);
+    // runs of 64 columns, or of 16 where those leave CUs without a workgroup
+    const int64_t P = (int64_t)g.nx * g.ny;
+    const int W = (P + 63) / 64 * r >= 256 ? 64 : 16;
+    const size_t run = (size_t)pad16(g.nz) * (lds_stride(W) + lds_stride(g.nz)) * sizeof(double);
+    auto room = [&](auto kernel, size_t bytes) -> hipError_t {
+      return bytes <= 65536 ? hipSuccess
+                            : hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                  (int)bytes);
+    };
+    LRDM_HIP(room(&hartree_plane_kernel<false>, plane));
+    LRDM_HIP(room(&hartree_plane_kernel<true>, plane));
+    LRDM_HIP(room(&hartree_column_kernel, run));
+    const dim3 planes(g.nz, r);
+    hartree_plane_kernel<false><<<planes, kHartreeThreads, plane, ctx->stream>>>(
+        u, u_nspin, a, g.nx, g.ny, g.M, Ux, Uy);
+    hartree_column_kernel<<<dim3((unsigned)((P + W - 1) / W), r), kHartreeThreads, run,
+                            ctx->stream>>>(a, g.nx, g.ny, g.nz, W, Uz, lx, ly, lz);
+    hartree_plane_kernel<true><<<planes, kHartreeThreads, plane, ctx->stream>>>(
+        a, dv_nspin, dV, g.nx, g.ny, g.M, Ux, Uy);
+    return hipGetLastError();
+  }
   // one pass along `axis`: LDS-staged for axes of at most kLdsAxis points
   auto pass = [&](const double* in, double* out, int axis, const double* Ud, int inverse) {
     const int n = axis == 0 ? g.nx : (axis == 1 ? g.ny : g.nz);
