@@ -187,3 +187,38 @@ def test_filter_under_a_workspace_limit(N):
     assert ctx.workspace_bytes <= limit
     assert _rel(Z, Y) < 8 * 12 * 2.0 ** -24
     ctx.close()
+
+
+# planes and columns of every padding, runs of 16 and of 64 columns, an axis past the LDS
+# form; -Lap dV = 4 pi (u - mean): the symbol's largest value is 12 / h^2, its smallest
+# non-zero one (2 pi / L)^2, so that a rounding of dV shows (12 / h^2) (L / 2 pi)^2-fold,
+# and each of the six passes adds n of them at most
+@pytest.mark.parametrize("n,r", [
+    ((5, 7, 9), 2), ((16, 17, 3), 1), ((33, 4, 20), 1), ((64, 5, 18), 2), ((4, 6, 64), 1),
+    ((65, 4, 5), 1), ((20, 20, 20), 40), ((64, 64, 64), 4), ((48, 49, 31), 1),
+])
+def test_hartree_forms(n, r):
+    grid, gen = _grid(n), _gen(sum(n))
+    u = _rand(gen, r, *grid.shape)
+    v = L.hartree_kernel(grid, u).reshape(u.shape)
+    lap, most = torch.zeros_like(v), max(n)
+    for points, length, ax in zip(grid.n, grid.L, (-1, -2, -3)):
+        h = length / points
+        lap += (torch.roll(v, 1, ax) + torch.roll(v, -1, ax) - 2 * v) / h ** 2
+    ref = 4 * torch.pi * (u - u.mean((-3, -2, -1), keepdim=True))
+    assert _rel(-lap, ref) < 6 * most * 12 * (most / 6.28) ** 2 * 2.0 ** -53
+
+
+# one wave a midpoint and four of them, at counts around their passes of 64 and 256
+@pytest.mark.parametrize("count,nspin", [(1, 1), (3, 2), (63, 1), (64, 1), (65, 1), (128, 2),
+                                         (257, 1), (1024, 2)])
+def test_fermi_level(count, nspin):
+    gen = _gen(count)
+    eps = torch.rand((nspin, count), generator=gen, device="cuda", dtype=torch.float64)
+    kT, s = 0.02, 2.0 if nspin == 1 else 1.0
+    ne = 0.4 * s * nspin * count
+    mu = L.fermi_occupations(eps, L.Occupation(nspin, kT, ne))[0]
+    # mu within 2 ulp of where the computed count crosses ne; the count's own rounding is
+    # at most the number of states times 2^-53 of it, the exponent's 50 more
+    got = s * torch.sigmoid((mu - eps) / kT).sum()
+    assert abs(float(got) - ne) < (nspin * count + 200) * 2.0 ** -52 * ne
