@@ -16,6 +16,7 @@
 //   B operand: lane l supplies B[l/16][l%16]   (k, col)
 //   D: lane l, register v holds D[4v + l/16][l%16].
 #include <algorithm>
+#include <type_traits>
 
 #include "blocks.h"
 #include "lrdm_internal.h"
@@ -34,20 +35,22 @@ __device__ inline d4 mfma64(double a, double b, d4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// 16 consecutive elements of storage type S from a 16-byte aligned address.
-__device__ inline void load16(const double* src, double (&v)[16]) {
+// V consecutive elements of storage type S from a 16-byte aligned address.
+template <int V>
+__device__ inline void load_run(const double* src, double (&v)[V]) {
   const double2* s2 = reinterpret_cast<const double2*>(src);
 #pragma unroll
-  for (int q = 0; q < 8; ++q) {
+  for (int q = 0; q < V / 2; ++q) {
     const double2 x = s2[q];
     v[2 * q] = x.x;
     v[2 * q + 1] = x.y;
   }
 }
-__device__ inline void load16(const float* src, float (&v)[16]) {
+template <int V>
+__device__ inline void load_run(const float* src, float (&v)[V]) {
   const float4* s4 = reinterpret_cast<const float4*>(src);
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
+  for (int q = 0; q < V / 4; ++q) {
     const float4 x = s4[q];
     v[4 * q] = x.x;
     v[4 * q + 1] = x.y;
@@ -56,26 +59,27 @@ __device__ inline void load16(const float* src, float (&v)[16]) {
   }
 }
 
-// Stage rows [r0, r0+BT) x cols [k0, k0+KT) of a row-major [nrows][ld] array of
+// Stage rows [r0, r0+T) x cols [k0, k0+KT) of a row-major [nrows][ld] array of
 // storage type S (double or float; the arithmetic is FP64 either way) into
-// S[k][row] (transposed).  Each thread loads 16 consecutive k of one row.
+// S[k][row] (transposed).  Each of 256 threads loads T / 8 consecutive k of one row.
 // Out-of-range elements are zero.  load() only issues the reads, so they stay in
 // flight during the current K-tile's matrix-core work.
-template <typename S>
+template <typename S, int T>
 struct TileLoad {
-  S v[16];
+  static constexpr int V = T / 8, PER = KT / V;   // PER threads a row
+  S v[V];
   __device__ inline void load(const S* __restrict__ X, int64_t ld, int nrows, int r0,
                               int64_t k0, int64_t kend) {
     const int t = threadIdx.x;
-    const int row = t >> 1;
-    const int64_t kb = k0 + (t & 1) * 16;
+    const int row = t / PER;
+    const int64_t kb = k0 + t % PER * V;
     const int gr = r0 + row;
     const bool aligned = (reinterpret_cast<uintptr_t>(X + (int64_t)gr * ld + kb) & 15) == 0;
-    if (gr < nrows && kb + 16 <= kend && aligned) {
-      load16(X + (int64_t)gr * ld + kb, v);
+    if (gr < nrows && kb + V <= kend && aligned) {
+      load_run<V>(X + (int64_t)gr * ld + kb, v);
     } else {
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
+      for (int q = 0; q < V; ++q) {
         const int64_t k = kb + q;
         v[q] = (gr < nrows && k < kend) ? X[(int64_t)gr * ld + k] : (S)0;
       }
@@ -83,31 +87,33 @@ struct TileLoad {
   }
   __device__ inline void store(double* Sm) const {
     const int t = threadIdx.x;
-    const int row = t >> 1;
-    const int kb = (t & 1) * 16;
+    const int row = t / PER;
+    const int kb = t % PER * V;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) Sm[(kb + q) * LDP + row] = (double)v[q];
+    for (int q = 0; q < V; ++q) Sm[(kb + q) * (T + 1) + row] = (double)v[q];
   }
 };
 
 // ------------------------------------------------------------------ tn_sym
 // 1-D grid over (split, batch) groups of upper tiles (xcd_map).  part layout:
-// [batch][split][tile][BT][BT].
-template <typename SA, typename SB>
+// [batch][split][tile][T][T].  An element's chain of sums does not depend on the tile edge T
+// (32, 64 or 128).
+template <typename SA, typename SB, int T>
 __global__ __launch_bounds__(256, 2) void tn_sym_f64_kernel(
     const SA* __restrict__ A, const SB* __restrict__ B, const double* __restrict__ w,
-    int64_t w_stride, int N, int64_t M, int nspin, int ntb, int64_t kchunk, int nsplit, int batch,
+    int64_t w_stride, int N, int64_t M, int nspin, int nt, int64_t kchunk, int nsplit, int batch,
     const unsigned char* __restrict__ active, double* __restrict__ part) {
-  __shared__ double As[KT * LDP];
-  __shared__ double Bs[KT * LDP];
+  constexpr int R = T / 32, LD = T + 1;   // 16-row strips of a wave, LDS pitch
+  __shared__ double As[KT * LD];
+  __shared__ double Bs[KT * LD];
   __shared__ double Ws[KT];   // w over the current K-tile (1 when w is absent)
-  const int ntiles = ntb * (ntb + 1) / 2;
+  const int ntiles = nt * (nt + 1) / 2;
   int group, tile;
   xcd_map(blockIdx.x, nsplit * batch, ntiles, group, tile);
   const int split = group % nsplit, b = group / nsplit;
   // upper-triangle tile index -> (ti, tj), ti <= tj
   int ti = 0, rem = tile;
-  while (rem >= ntb - ti) { rem -= ntb - ti; ++ti; }
+  while (rem >= nt - ti) { rem -= nt - ti; ++ti; }
   const int tj = ti + rem;
   const int c = b % nspin;
   const SA* Ac = A + (int64_t)c * N * M;
@@ -115,15 +121,16 @@ __global__ __launch_bounds__(256, 2) void tn_sym_f64_kernel(
   const double* wb = w ? w + (int64_t)b * w_stride : nullptr;
   const int64_t kbeg = (int64_t)split * kchunk;
   // an inactive block (blocks.h) keeps a zero partial tile
-  const int64_t kend = block_active(active, c, ntb, ti, tj) ? min(M, kbeg + kchunk) : kbeg;
+  const bool on = block_active(active, c, (N + BT - 1) / BT, ti * T / BT, tj * T / BT);
+  const int64_t kend = on ? min(M, kbeg + kchunk) : kbeg;
 
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const int wr = wid >> 1, wc = wid & 1;
-  d4 acc[4][4];
+  d4 acc[R][R];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < R; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+    for (int j = 0; j < R; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
 
   // the weight of B's column k is applied as B is read from LDS (the FP64 product
   // w[k] * B[j][k], as if B had been scaled in memory)
@@ -131,12 +138,12 @@ __global__ __launch_bounds__(256, 2) void tn_sym_f64_kernel(
     const int64_t k = k0 + threadIdx.x;
     return (threadIdx.x < KT && k < kend) ? (wb ? wb[k] : 1.0) : 0.0;
   };
-  TileLoad<SA> la;
-  TileLoad<SB> lb;
+  TileLoad<SA, T> la;
+  TileLoad<SB, T> lb;
   double wn = 0.0;
   if (kbeg < kend) {
-    la.load(Ac, M, N, ti * BT, kbeg, kend);
-    lb.load(Bc, M, N, tj * BT, kbeg, kend);
+    la.load(Ac, M, N, ti * T, kbeg, kend);
+    lb.load(Bc, M, N, tj * T, kbeg, kend);
     wn = wload(kbeg);
   }
   for (int64_t k0 = kbeg; k0 < kend; k0 += KT) {
@@ -146,35 +153,35 @@ __global__ __launch_bounds__(256, 2) void tn_sym_f64_kernel(
     if (threadIdx.x < KT) Ws[threadIdx.x] = wn;
     __syncthreads();
     if (k0 + KT < kend) {
-      la.load(Ac, M, N, ti * BT, k0 + KT, kend);
-      lb.load(Bc, M, N, tj * BT, k0 + KT, kend);
+      la.load(Ac, M, N, ti * T, k0 + KT, kend);
+      lb.load(Bc, M, N, tj * T, k0 + KT, kend);
       wn = wload(k0 + KT);
     }
 #pragma unroll
     for (int kk = 0; kk < KT; kk += 4) {
-      const int kr = (kk + (lane >> 4)) * LDP;
+      const int kr = (kk + (lane >> 4)) * LD;
       const double wk = Ws[kk + (lane >> 4)];
-      double a[4], bb[4];
+      double a[R], bb[R];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[kr + wr * 64 + i * 16 + (lane & 15)];
+      for (int i = 0; i < R; ++i) a[i] = As[kr + wr * (T / 2) + i * 16 + (lane & 15)];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) bb[j] = Bs[kr + wc * 64 + j * 16 + (lane & 15)] * wk;
+      for (int j = 0; j < R; ++j) bb[j] = Bs[kr + wc * (T / 2) + j * 16 + (lane & 15)] * wk;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < R; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = mfma64(a[i], bb[j], acc[i][j]);
+        for (int j = 0; j < R; ++j) acc[i][j] = mfma64(a[i], bb[j], acc[i][j]);
     }
   }
-  double* out = part + (((int64_t)b * nsplit + split) * ntiles + tile) * (BT * BT);
+  double* out = part + (((int64_t)b * nsplit + split) * ntiles + tile) * (T * T);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < R; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < R; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int row = wr * 64 + i * 16 + 4 * v + (lane >> 4);
-        const int col = wc * 64 + j * 16 + (lane & 15);
-        out[row * BT + col] = acc[i][j][v];
+        const int row = wr * (T / 2) + i * 16 + 4 * v + (lane >> 4);
+        const int col = wc * (T / 2) + j * 16 + (lane & 15);
+        out[row * T + col] = acc[i][j][v];
       }
 }
 
@@ -242,7 +249,7 @@ struct RowLoad {
     const bool aligned = (reinterpret_cast<uintptr_t>(X + (int64_t)gr * ld + cb) & 15) == 0;
     fac = factor;
     if (gr < nrows && cb + 16 <= ncols && aligned) {
-      load16(X + (int64_t)gr * ld + cb, v);
+      load_run<16>(X + (int64_t)gr * ld + cb, v);
     } else {
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
@@ -631,9 +638,9 @@ hipError_t launch_tn_sym_f64(lrdm_ctx* ctx, const SA* A, const SB* B, const doub
   int64_t kchunk = (M + ns - 1) / ns;
   kchunk = (kchunk + KT - 1) / KT * KT;
   double* part = static_cast<double*>(ws_take(ctx, tn_part_bytes(N, M, batch, ctx->split_limit)));
-  // A block held in FP32 keeps the 128-row tiles and the order of their sums: the basis
-  // an ill-conditioned filtered block is orthonormalised to is rounded to FP32, so that
-  // a Gram matrix off by one rounding moves its Ritz pairs by far more.
+  // A block held in FP32 keeps one order of its sums (that of this kernel, at any tile edge):
+  // the basis an ill-conditioned filtered block is orthonormalised to is rounded to FP32, so
+  // that a Gram matrix off by one rounding moves its Ritz pairs by far more.
   constexpr bool fp32 = sizeof(SA) == sizeof(float);
   if constexpr (!fp32) {
     if (tn_direct_ok(N, M, batch)) {
@@ -647,18 +654,36 @@ hipError_t launch_tn_sym_f64(lrdm_ctx* ctx, const SA* A, const SB* B, const doub
                                       true);
     }
   }
-  const unsigned grd = (unsigned)(ntiles * ns * batch);
-  {
-    ProfScope prof(ctx, w ? "proj" : "gram");
-    if (B)
-      tn_sym_f64_kernel<SA, SB><<<grd, 256, 0, ctx->stream>>>(A, B, w, w_stride, N, M, nspin, ntb,
-                                                               kchunk, ns, batch, active, part);
-    else
-      tn_sym_f64_kernel<SA, SA><<<grd, 256, 0, ctx->stream>>>(A, A, w, w_stride, N, M, nspin, ntb,
-                                                               kchunk, ns, batch, active, part);
-    LRDM_HIP(hipGetLastError());
+  auto run = [&](auto edge) -> hipError_t {
+    constexpr int T = decltype(edge)::value;
+    const int nt = (N + T - 1) / T;
+    const unsigned grd = (unsigned)(nt * (nt + 1) / 2 * ns * batch);
+    {
+      ProfScope prof(ctx, w ? "proj" : "gram");
+      if (B)
+        tn_sym_f64_kernel<SA, SB, T><<<grd, 256, 0, ctx->stream>>>(
+            A, B, w, w_stride, N, M, nspin, nt, kchunk, ns, batch, active, part);
+      else
+        tn_sym_f64_kernel<SA, SA, T><<<grd, 256, 0, ctx->stream>>>(
+            A, A, w, w_stride, N, M, nspin, nt, kchunk, ns, batch, active, part);
+      LRDM_HIP(hipGetLastError());
+    }
+    return launch_tn_reduce(ctx, part, N, T, ns, batch, H, fp32);
+  };
+  // The largest edge that leaves enough workgroups (eight to a CU; of 64 rows four).
+  // Gram product, edge 128 / 64 / 32: 24^3, 32 states (4 ranges) 1116 / 419 / 155 us;
+  // 48^3, 256 (48 workgroups of 128) 1001 / 352 / 310; 64^3, 200 (640 of 64)
+  // 705 / 534 / 394; 64^3, 512 (640 of 128, 2304 of 64) 1803 / 1395 / 1661; 64^3, 1024
+  // (2304 of 128) 5007 / 4981 / 6517.
+  if constexpr (fp32) {
+    const int64_t each = (int64_t)ns * batch;
+    const int nt = (N + 63) / 64;
+    if (ntiles * each < 2048) {
+      if (nt * (nt + 1) / 2 * each < 1024) return run(std::integral_constant<int, 32>{});
+      return run(std::integral_constant<int, 64>{});
+    }
   }
-  return launch_tn_reduce(ctx, part, N, BT, ns, batch, H, fp32);
+  return run(std::integral_constant<int, BT>{});
 }
 template hipError_t launch_tn_sym_f64<double, double>(lrdm_ctx*, const double*, const double*,
                                                       const double*, int64_t, int, int64_t, int,

@@ -150,6 +150,28 @@ def _chebyshev(grid, V, X, degree, a, b, a0):
     return y1
 
 
+# Gram and Rayleigh products of FP32 blocks on tiles of 32, 64 and 128 rows, at their
+# remainders: the basis is orthonormal to its FP32 rounding and the Ritz values are those
+# of the block's span.  B = L Q with |entries| random: cond(B) is a few, so that N
+# roundings of 2^-24 bound both, relative to the Hamiltonian's largest value
+@pytest.mark.parametrize("n,N", [((8, 8, 8), 16), ((9, 11, 13), 33), ((16, 16, 16), 65),
+                                 ((32, 32, 32), 129), ((64, 64, 32), 300), ((24, 25, 26), 513)])
+def test_ritz_fp32(n, N):
+    grid, gen = _grid(n), _gen(N)
+    V = _rand(gen, *grid.shape)
+    X = _rand(gen, N, grid.M, dtype=torch.float32)
+    Q = torch.linalg.qr(X.double().t())[0].t().contiguous()
+    HQ = _chebyshev(grid, V, Q.reshape(N, *grid.shape), 1, -1.0, 1.0, 1.0).reshape(N, -1)
+    ref = torch.linalg.eigvalsh(HQ @ Q.t())
+    eps = L.subspace_rayleigh_ritz(grid, V, X, prec="fp32")
+    h2 = sum((points / length) ** 2 for points, length in zip(grid.n, grid.L))
+    top = 2 * h2 + float(V.abs().max())
+    assert float((eps.flatten() - ref).abs().max()) < N * 2.0 ** -24 * top
+    S = X.double() @ X.double().t() * float(torch.tensor(grid.L).prod() / grid.M)
+    S = S / S.diagonal().mean()
+    assert float((S - torch.eye(N, device="cuda", dtype=S.dtype)).abs().max()) < N * 2.0 ** -24
+
+
 # whole states in LDS (24^3 FP64 and 32^3 are the largest of their kind; 64 steps are the
 # most of one launch), sweeps of every remainder and with z runs, one and two groups per
 # thread, single steps where nx is not a multiple of the 16-byte group
