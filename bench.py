@@ -360,7 +360,7 @@ def main():
     nblk = hr["active_blocks"]
     executed = {"backproj": products * r * (2.0 * M * 128 * 128 * nblk + 2.0 * M * N),
                 "proj": products * r * 2.0 * M * 128 * 128 * nblk,
-                "cheb_step": work, "cheb_pair": work, "cheb_triple": work}[dom]
+                "cheb_step": work}[dom]
     ex_rate = executed / avg_s / (1e9 if bound == "hbm" else 1e12)
     roofline = dict(kernel=dom, bound=bound, achieved=round(achieved, 3), peak=peak, unit=unit,
                     frac=round(achieved / peak, 4),

@@ -35,7 +35,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 
 # profiling-scope name -> (kernel-name pattern, source file) for each storage form
 KERNELS = {
-    "fp64": {"proj": (r"tn_sym_f64_kernel<double, double>", "gemm.hip"),
+    "fp64": {"proj": (r"tn_sym_f64_kernel<double, double", "gemm.hip"),
              "backproj": (r"backproj_f64_kernel", "gemm.hip"),
              "cheb_step": (r"cheb_vec_kernel<double|cheb_plane_kernel<double, double", "stencil.hip"),
              "cheb_sweep": (r"cheb_sweep_kernel<double", "stencil.hip")},
