@@ -1367,25 +1367,25 @@ lrdm_status run_lowrank(lrdm_ctx* ctx, const Grid3& g, const T* Psi, const doubl
   // w = sum_j y_j t_j - R (Eq. (10)) with its norm and <R, w>
   auto fit = [&](int i) -> hipError_t {
     const double* ti = Tm + (size_t)i * n;
-    LRDM_HIP(launch_dots(ctx, Tm, n, i + 1, ti, n, dv, S + (size_t)i * K, 1, part));
-    LRDM_HIP(launch_dots(ctx, ti, 0, 1, R, n, dv, c + i, 1, part));
+    LRDM_HIP(launch_dots(ctx, DotSet{Tm, n, i + 1, ti, S + (size_t)i * K},
+                         DotSet{ti, 0, 1, R, c + i}, n, dv, part, K));
     LRDM_HIP(launch_lowrank_solve(ctx, S, K, c, i + 1, y, flag));
     LRDM_HIP(launch_combine(ctx, R, -1.0, Tm, n, y, i + 1, 1.0, n, w));
-    LRDM_HIP(launch_dots(ctx, w, 0, 1, w, n, dv, sc + LR_FIT2, 1, part));
-    return launch_dots(ctx, w, 0, 1, R, n, dv, sc + LR_RW, 1, part);
+    return launch_dots(ctx, DotSet{w, 0, 1, w, sc + LR_FIT2}, DotSet{w, 0, 1, R, sc + LR_RW}, n,
+                       dv, part, K);
   };
   // un = v - sum_{k<m} <v, u_k> u_k, twice, and |un|^2, |v|^2
   auto orthogonalise = [&](const double* v, int m, double* un) -> hipError_t {
-    LRDM_HIP(launch_dots(ctx, U, n, m, v, n, dv, gco, 1, part));
+    LRDM_HIP(launch_dots(ctx, DotSet{U, n, m, v, gco}, DotSet{}, n, dv, part, K));
     LRDM_HIP(launch_combine(ctx, v, 1.0, U, n, gco, m, -1.0, n, un));
-    LRDM_HIP(launch_dots(ctx, U, n, m, un, n, dv, gco, 1, part));
+    LRDM_HIP(launch_dots(ctx, DotSet{U, n, m, un, gco}, DotSet{}, n, dv, part, K));
     LRDM_HIP(launch_combine(ctx, un, 1.0, U, n, gco, m, -1.0, n, un));
-    LRDM_HIP(launch_dots(ctx, un, 0, 1, un, n, dv, sc + LR_UNEW2, 1, part));
-    return launch_dots(ctx, v, 0, 1, v, n, dv, sc + LR_V2, 1, part);
+    return launch_dots(ctx, DotSet{un, 0, 1, un, sc + LR_UNEW2}, DotSet{v, 0, 1, v, sc + LR_V2}, n,
+                       dv, part, K);
   };
 
   // ||R||
-  LR_HIP("lowrank norm", launch_dots(ctx, R, 0, 1, R, n, dv, sc + LR_NR2, 1, part));
+  LR_HIP("lowrank norm", launch_dots(ctx, DotSet{R, 0, 1, R, sc + LR_NR2}, DotSet{}, n, dv, part, K));
   LR_HIP("lowrank read", hipMemcpyAsync(h, sc, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
   LR_HIP("lowrank sync", hipStreamSynchronize(ctx->stream));
   if (!std::isfinite(h[LR_NR2])) return fail(ctx, LRDM_ENONFINITE, "||R|| is not finite");

@@ -445,10 +445,17 @@ hipError_t launch_density(lrdm_ctx* ctx, const T* Psi, const double* f, int N, i
                           int nspin, double scale, const double* rho_in, double* out,
                           double* part);
 size_t dots_workspace_bytes(int k);
-// out[j * stride] = scale sum_i A[j][i] x[i] for j < k (rows lda apart), in a fixed
-// order; part: dots_workspace_bytes(k) of scratch.
-hipError_t launch_dots(lrdm_ctx* ctx, const double* A, int64_t lda, int k, const double* x,
-                       int64_t n, double scale, double* out, int stride, double* part);
+// out[j] = scale sum_i A[j][i] x[i] for j < k (rows lda apart), in a fixed order, for
+// one or two sets; part: dots_workspace_bytes(room) of scratch, room >= each set's k.
+struct DotSet {
+  const double* A = nullptr;
+  int64_t lda = 0;
+  int k = 0;
+  const double* x = nullptr;
+  double* out = nullptr;
+};
+hipError_t launch_dots(lrdm_ctx* ctx, const DotSet& first, const DotSet& second, int64_t n,
+                       double scale, double* part, int room);
 // y = beta x + sgn sum_{k < nk} coef[k] A[k] (x may be NULL, y may be x).
 hipError_t launch_combine(lrdm_ctx* ctx, const double* x, double beta, const double* A,
                           int64_t lda, const double* coef, int nk, double sgn, int64_t n,
