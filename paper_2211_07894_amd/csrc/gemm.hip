@@ -561,10 +561,12 @@ size_t tn_part_bytes(int N, int64_t M, int batch, int split_limit) {
 
 // FP32 arithmetic (whose partial sums are grouped by K-tile, so that any count gives the
 // same sums up to the FP64 additions): the count within the workspace whose workgroups,
-// two per tile and two per CU, finish first, each with a fixed cost of twelve K-tiles.
-// 48^3, 256 states, 8 directions: 21 ranges (1008 workgroups on 512 slots) take 950 us,
-// 16 (768) take 990; 24^3, 32 states, 4 directions: 41 us
-// (512-point ranges), 583 with ranges of at least 2048 points on 128-row tiles.
+// two per tile and two per CU, finish first, each with a fixed cost of twelve K-tiles and
+// all of them one range late: workgroups do not start together, so that one or two
+// rounds of long ranges leave a tail, and from about six rounds on it no longer matters.
+// 64^3, 300 states, 3 directions: 18 ranges (1 round) 1839 us, 37 1750, 56 1538, 113 1550;
+// 64^3, 700, 2: 7 ranges 5069, 14 3904, 42 3564; 48^3, 256, 8: 21 888, 64 872; 24^3, 32,
+// 4: 33 us (512-point ranges), 566 with ranges of at least 2048 points on 128-row tiles.
 // The other arithmetics: tn_splits.
 int tn_default_splits(int N, int64_t M, int batch, int arith, int split_limit) {
   const int ntb = (N + BT - 1) / BT;
@@ -576,7 +578,7 @@ int tn_default_splits(int N, int64_t M, int batch, int arith, int split_limit) {
   double least = 1e300;
   for (int s = 1; s <= cap; ++s) {
     const double rounds = (double)(((int64_t)halves * s + 511) / 512);
-    const double cost = rounds * ((double)((M + KT * s - 1) / (KT * s)) + 12.0);
+    const double cost = (rounds + 1.0) * ((double)((M + KT * s - 1) / (KT * s)) + 12.0);
     if (cost < least) {
       least = cost;
       best = s;
@@ -588,16 +590,21 @@ int tn_default_splits(int N, int64_t M, int batch, int arith, int split_limit) {
 // Parts each range of a BF16X3 projection with pre-split pieces is cut into: its FP32
 // sums run over groups of 128 points from the range's start, so that a cut between
 // groups leaves them as they are.  One workgroup per tile, part and CU; the cost as above.
+// Cut only for a tenth or more: the kernel with parts is 1 % slower and writes that many
+// more partial tiles (2700 workgroups a direction set, cut for a predicted 3 %: 0.987x).
 int tn_range_parts(int N, int64_t M, int batch, int nsplit, int64_t kchunk, int split_limit) {
   const int ntb = (N + BT - 1) / BT;
   const int64_t wgs = (int64_t)(ntb * (ntb + 1) / 2) * batch * nsplit;
   const int64_t groups = (kchunk + BT - 1) / BT;
   const int most = (int)std::min<int64_t>(groups, tn_range_cap(N, M, batch, split_limit) / nsplit);
-  int best = 1;
-  double least = 1e300;
-  for (int q = 1; q <= most; ++q) {
+  auto cost_of = [&](int q) {
     const double rounds = (double)((wgs * q + 255) / 256);
-    const double cost = rounds * ((double)((groups + q - 1) / q * (BT / KT)) + 12.0);
+    return rounds * ((double)((groups + q - 1) / q * (BT / KT)) + 12.0);
+  };
+  int best = 1;
+  double least = 0.9 * cost_of(1);
+  for (int q = 2; q <= most; ++q) {
+    const double cost = cost_of(q);
     if (cost < least) {
       least = cost;
       best = q;
