@@ -39,29 +39,36 @@ struct WsOverflow : std::runtime_error {
     if (!(p)) return fail((ctx), LRDM_EINVAL, std::string(name) + " is NULL");  \
   } while (0)
 
+constexpr size_t kWsSlack = 1u << 20;
+
 // Common prologue once arguments are valid: the context must exist, its device
-// becomes current and the workspace holds `bytes`.
-lrdm_status begin(lrdm_ctx* ctx, size_t bytes) {
+// becomes current and the workspace is empty.
+lrdm_status enter(lrdm_ctx* ctx) {
   if (!ctx) return fail(nullptr, LRDM_EINVAL, "ctx is NULL");
   hipError_t e = hipSetDevice(ctx->device);
   if (e != hipSuccess) return fail_hip(ctx, "hipSetDevice", e);
   ctx->ws_top = 0;
-  return lrdm::ws_reserve(ctx, bytes + (1u << 20));
+  ctx->split_limit = 0;
+  return LRDM_OK;
 }
 
-// begin() for a call whose projections prefer more partial sums than they need:
-// bytes(0) where the context can hold it, else (a workspace limit, a capture, no
-// memory) bytes(kLeanSplits).
+// enter(), with a workspace of `bytes`.
+lrdm_status begin(lrdm_ctx* ctx, size_t bytes) {
+  const lrdm_status st = enter(ctx);
+  return st == LRDM_OK ? lrdm::ws_reserve(ctx, bytes + kWsSlack) : st;
+}
+
+// begin() for a call that prefers a larger workspace than it needs: bytes(0) where the
+// context has or gets it (ws_prefer), else bytes(kLeanSplits).
 template <typename F>
 lrdm_status begin_sized(lrdm_ctx* ctx, F&& bytes) {
-  if (ctx) ctx->split_limit = 0;
-  const size_t want = bytes(0), least = bytes(lrdm::kLeanSplits);
-  lrdm_status st = begin(ctx, want);
-  if (st == LRDM_ENOMEM && least < want) {
-    ctx->split_limit = lrdm::kLeanSplits;
-    st = begin(ctx, least);
-  }
-  return st;
+  const lrdm_status st = enter(ctx);
+  if (st != LRDM_OK) return st;
+  const size_t want = bytes(0) + kWsSlack, least = bytes(lrdm::kLeanSplits) + kWsSlack;
+  if (least >= want) return lrdm::ws_reserve(ctx, want);
+  if (lrdm::ws_prefer(ctx, want, least)) return LRDM_OK;
+  ctx->split_limit = lrdm::kLeanSplits;
+  return lrdm::ws_reserve(ctx, least);
 }
 
 // Epilogue: in checking mode wait for the stream and turn device status words
@@ -140,11 +147,43 @@ lrdm_status ws_reserve(lrdm_ctx* ctx, size_t bytes) {
   }
   e = hipMalloc(&ctx->ws, bytes);
   if (e != hipSuccess) {
+    (void)hipGetLastError();           // reported here: not by the next launch
     ctx->ws = nullptr;
     return fail(ctx, LRDM_ENOMEM, std::string("hipMalloc of workspace: ") + hipGetErrorString(e));
   }
   ctx->ws_cap = bytes;
   return LRDM_OK;
+}
+
+bool ws_prefer(lrdm_ctx* ctx, size_t want, size_t least) {
+  if (want <= ctx->ws_cap) return true;
+  if (ctx->ws_cap < least) {
+    // the workspace is replaced in any case
+    const lrdm_status st = ws_reserve(ctx, want);
+    ctx->ws_refused = st == LRDM_ENOMEM ? want : SIZE_MAX;
+    return st == LRDM_OK;
+  }
+  // It is enough as it is, and is given up only for a larger one in hand; what the
+  // device has refused once is not asked for again by every call.  Both blocks count
+  // against the limit while they coexist.
+  if (want >= ctx->ws_refused || (ctx->limit && want + ctx->ws_cap > ctx->limit)) return false;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
+    return false;
+  void* larger = nullptr;
+  if (hipMalloc(&larger, want) != hipSuccess) {
+    (void)hipGetLastError();
+    ctx->ws_refused = want;
+    return false;
+  }
+  if (hipStreamSynchronize(ctx->stream) != hipSuccess) {
+    (void)hipFree(larger);
+    return false;
+  }
+  (void)hipFree(ctx->ws);
+  ctx->ws = larger;
+  ctx->ws_cap = want;
+  return true;
 }
 
 void* ws_take(lrdm_ctx* ctx, size_t bytes) {
@@ -1575,8 +1614,10 @@ extern "C" lrdm_status lrdm_autotune(lrdm_ctx* ctx, const lrdm_grid* grid, int32
   } release{{&A, reinterpret_cast<void**>(&w), reinterpret_cast<void**>(&H)}};
   if (hipMalloc(&A, (size_t)nspin * N * g.M * el) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&w), (size_t)batch * g.M * sizeof(double)) != hipSuccess ||
-      hipMalloc(reinterpret_cast<void**>(&H), (size_t)batch * N * N * sizeof(double)) != hipSuccess)
+      hipMalloc(reinterpret_cast<void**>(&H), (size_t)batch * N * N * sizeof(double)) != hipSuccess) {
+    (void)hipGetLastError();
     return fail(ctx, LRDM_ENOMEM, "lrdm_autotune: scratch allocation failed");
+  }
   return guarded(ctx, [&]() -> lrdm_status {
     hipError_t e = launch_pattern(ctx, A, (int64_t)nspin * N * g.M, prec == LRDM_FP64);
     if (e == hipSuccess) e = launch_pattern(ctx, w, (int64_t)batch * g.M, true);

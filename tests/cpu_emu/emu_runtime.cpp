@@ -43,7 +43,17 @@ lrdm_emu_switch:
 .size lrdm_emu_switch, .-lrdm_emu_switch
 )");
 
+// The device's state, for tests of the shared library.
+extern "C" void lrdm_emu_device(size_t refuse_from, int capturing) {
+  lrdm_emu::device.refuse = refuse_from;
+  lrdm_emu::device.capturing = capturing != 0;
+}
+extern "C" long lrdm_emu_mallocs() { return lrdm_emu::device.mallocs; }
+extern "C" long lrdm_emu_frees() { return lrdm_emu::device.frees; }
+
 namespace lrdm_emu {
+
+Device device;
 
 thread_local Block* cur = nullptr;
 thread_local Fiber* cur_fiber = nullptr;

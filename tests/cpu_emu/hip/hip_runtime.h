@@ -267,15 +267,35 @@ struct lrdm_emu_event {
   std::chrono::steady_clock::time_point t;
 };
 inline const char* hipGetErrorString(hipError_t e) { return e == hipSuccess ? "no error" : "emulated error"; }
-inline hipError_t hipGetLastError() { return hipSuccess; }
+namespace lrdm_emu {
+// The device's memory and stream as a test sets them (emu_runtime.cpp).
+struct Device {
+  size_t refuse = SIZE_MAX;          // allocations of this size and more fail
+  long mallocs = 0, frees = 0;       // allocations made and given back
+  bool capturing = false;            // created streams are being captured
+  hipError_t last = hipSuccess;      // the error hipGetLastError reports and clears
+};
+extern Device device;
+}  // namespace lrdm_emu
+inline hipError_t hipGetLastError() {
+  const hipError_t e = lrdm_emu::device.last;
+  lrdm_emu::device.last = hipSuccess;
+  return e;
+}
 inline hipError_t hipSetDevice(int) { return hipSuccess; }
 inline hipError_t hipMalloc(void** p, size_t n) {
-  *p = std::malloc(n ? n : 1);
-  return *p ? hipSuccess : hipErrorOutOfMemory;
+  *p = n < lrdm_emu::device.refuse ? std::malloc(n ? n : 1) : nullptr;
+  if (!*p) return lrdm_emu::device.last = hipErrorOutOfMemory;
+  ++lrdm_emu::device.mallocs;
+  return hipSuccess;
 }
 template <typename T>
 inline hipError_t hipMalloc(T** p, size_t n) { return hipMalloc(reinterpret_cast<void**>(p), n); }
-inline hipError_t hipFree(void* p) { std::free(p); return hipSuccess; }
+inline hipError_t hipFree(void* p) {
+  if (p) ++lrdm_emu::device.frees;
+  std::free(p);
+  return hipSuccess;
+}
 inline hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) { std::memmove(d, s, n); return hipSuccess; }
 inline hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { std::memmove(d, s, n); return hipSuccess; }
 inline hipError_t hipMemset(void* d, int v, size_t n) { std::memset(d, v, n); return hipSuccess; }
@@ -291,8 +311,8 @@ inline hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
 }
 inline hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 inline hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
-inline hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* c) {
-  *c = hipStreamCaptureStatusNone;
+inline hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus* c) {
+  *c = s && lrdm_emu::device.capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
   return hipSuccess;
 }
 inline hipError_t hipDeviceSynchronize() { return hipSuccess; }

@@ -1,0 +1,111 @@
+"""The workspace's growth, on the CPU build of the library, whose device memory a test
+can make refuse allocations from a size on."""
+import ctypes
+import os
+
+import numpy as np
+import pytest
+
+from paper_2211_07894_amd import lrdm as B
+from tests.cpu_emu import build_emu
+
+ANY = ctypes.c_size_t(-1).value
+
+
+@pytest.fixture(scope="module")
+def lib():
+    if not os.path.exists(build_emu.CLANG):
+        pytest.skip("needs the host clang of ROCm")
+    lib = ctypes.CDLL(build_emu.build("", shared=True))
+    vp, i32 = ctypes.c_void_p, ctypes.c_int32
+    lib.lrdm_create.argtypes = [ctypes.POINTER(vp), ctypes.c_int, vp, ctypes.c_size_t]
+    lib.lrdm_destroy.argtypes = [vp]
+    lib.lrdm_projected_perturbation.argtypes = [vp, ctypes.POINTER(B.c_grid), vp, i32, i32, vp,
+                                                i32, ctypes.c_int, vp]
+    lib.lrdm_workspace_bytes.argtypes = lib.lrdm_last_error.argtypes = [vp]
+    lib.lrdm_workspace_bytes.restype = ctypes.c_size_t
+    lib.lrdm_last_error.restype = ctypes.c_char_p
+    lib.lrdm_emu_device.argtypes = [ctypes.c_size_t, ctypes.c_int]
+    lib.lrdm_emu_mallocs.restype = lib.lrdm_emu_frees.restype = ctypes.c_long
+    yield lib
+    lib.lrdm_emu_device(ANY, 0)
+
+
+class Calls:
+    """FP64 projections of one context: the preferred partial sums grow with the points,
+    the least ones much less."""
+
+    def __init__(self, lib, stream=0, limit=0):
+        self.lib, self.ctx = lib, ctypes.c_void_p()
+        lib.lrdm_emu_device(ANY, 0)
+        assert lib.lrdm_create(ctypes.byref(self.ctx), 0, stream, limit) == 0
+
+    def __enter__(self):
+        return self
+
+    def __exit__(self, *_):
+        self.lib.lrdm_emu_device(ANY, 0)
+        self.lib.lrdm_destroy(self.ctx)
+
+    def device(self, refuse_from=ANY, capturing=0):
+        self.lib.lrdm_emu_device(refuse_from, capturing)
+
+    @property
+    def bytes(self):
+        return self.lib.lrdm_workspace_bytes(self.ctx)
+
+    def moves(self):
+        return self.lib.lrdm_emu_mallocs(), self.lib.lrdm_emu_frees()
+
+    def project(self, n, N=3, r=1):
+        rng = np.random.default_rng(n[0] + N)
+        M = n[0] * n[1] * n[2]
+        P, dV = rng.standard_normal((N, M)), rng.standard_normal((r, M))
+        H = np.zeros((r, N, N))
+        g = B.c_grid()
+        for d in range(3):
+            g.n[d], g.L[d] = n[d], 0.4 * n[d]
+        p = lambda a: a.ctypes.data_as(ctypes.c_void_p)  # noqa: E731
+        st = self.lib.lrdm_projected_perturbation(self.ctx, ctypes.byref(g), p(P), N, 1, p(dV), r,
+                                                  0, p(H))
+        assert st == 0, self.lib.lrdm_last_error(self.ctx)
+        ref = np.einsum("im,rm,jm->rij", P, dV, P)
+        # an FP64 sum of M terms: M u of their absolute sum, about sqrt(M) times the result
+        assert np.abs(H - ref).max() < M ** 1.5 * 2.0 ** -53 * np.abs(ref).max()
+
+
+def preferred(lib, n, **kw):
+    with Calls(lib) as c:
+        c.project(n, **kw)
+        return c.bytes
+
+
+def test_a_refused_preferred_size_costs_one_attempt(lib):
+    """Equal calls on a device that holds the least workspace but not the preferred one:
+    all succeed, and only the first allocates."""
+    n = (24, 24, 24)
+    with Calls(lib) as c:
+        c.device(refuse_from=preferred(lib, n))
+        c.project(n)
+        held, moves = c.bytes, c.moves()
+        for _ in range(3):
+            c.project(n)
+            assert (c.bytes, c.moves()) == (held, moves)
+        # a call that needs more asks for what it prefers again
+        c.device()
+        c.project((32, 32, 32), r=40)
+        assert c.bytes == preferred(lib, (32, 32, 32), r=40)
+
+
+def test_growth_for_a_preferred_size_keeps_the_workspace_until_it_succeeds(lib):
+    """A workspace that already covers the least size is not given up for one the device
+    cannot give."""
+    small, large = (12, 12, 12), (24, 24, 24)
+    most = preferred(lib, large)
+    with Calls(lib) as c:
+        c.project(small, r=8)
+        held, moves = c.bytes, c.moves()
+        assert held < most
+        c.device(refuse_from=held + 1)
+        c.project(large)
+        assert (c.bytes, c.moves()) == (held, moves)
