@@ -49,6 +49,7 @@ lrdm_status enter(lrdm_ctx* ctx) {
   if (e != hipSuccess) return fail_hip(ctx, "hipSetDevice", e);
   ctx->ws_top = 0;
   ctx->split_limit = 0;
+  if (lrdm::capturing(ctx)) ctx->ws_captured = true;
   return LRDM_OK;
 }
 
@@ -124,10 +125,18 @@ Grid3 make_grid3(const lrdm_grid* g) {
   return r;
 }
 
+bool capturing(const lrdm_ctx* ctx) {
+  if (!ctx->stream) return false;      // the default stream cannot be captured
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess)
+    return cap != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return false;
+}
+
 lrdm_status ws_reserve(lrdm_ctx* ctx, size_t bytes) {
   if (bytes <= ctx->ws_cap) return LRDM_OK;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
+  if (capturing(ctx))
     return fail(ctx, LRDM_ENOMEM,
                 "the workspace would have to grow during stream capture: make the same call once "
                 "before capturing");
@@ -152,6 +161,7 @@ lrdm_status ws_reserve(lrdm_ctx* ctx, size_t bytes) {
     return fail(ctx, LRDM_ENOMEM, std::string("hipMalloc of workspace: ") + hipGetErrorString(e));
   }
   ctx->ws_cap = bytes;
+  ctx->ws_captured = false;
   return LRDM_OK;
 }
 
@@ -163,12 +173,11 @@ bool ws_prefer(lrdm_ctx* ctx, size_t want, size_t least) {
     ctx->ws_refused = st == LRDM_ENOMEM ? want : SIZE_MAX;
     return st == LRDM_OK;
   }
-  // It is enough as it is, and is given up only for a larger one in hand; what the
-  // device has refused once is not asked for again by every call.  Both blocks count
-  // against the limit while they coexist.
-  if (want >= ctx->ws_refused || (ctx->limit && want + ctx->ws_cap > ctx->limit)) return false;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(ctx->stream, &cap) == hipSuccess && cap != hipStreamCaptureStatusNone)
+  // It is enough as it is, and is given up only for a larger one in hand, never once a
+  // graph may hold its address; what the device has refused once is not asked for again
+  // by every call.  Both blocks count against the limit while they coexist.
+  if (ctx->ws_captured || want >= ctx->ws_refused ||
+      (ctx->limit && want + ctx->ws_cap > ctx->limit))
     return false;
   void* larger = nullptr;
   if (hipMalloc(&larger, want) != hipSuccess) {

@@ -38,6 +38,7 @@ struct lrdm_ctx {
   void* ws = nullptr;        // device workspace
   size_t ws_cap = 0;
   size_t ws_top = 0;         // bump pointer inside one call
+  bool ws_captured = false;  // a call was captured with the present workspace
   size_t ws_refused = SIZE_MAX;  // preferred size the device could not give (ws_prefer)
   int checks = 0;
   int fermi_depth = 0;       // 0: exact divided differences; T > 0: recursive expansion
@@ -93,6 +94,8 @@ inline size_t prec_bytes(lrdm_prec p) { return p == LRDM_FP64 ? 8 : 4; }
 lrdm_status ws_reserve(lrdm_ctx* ctx, size_t bytes);
 inline size_t ws_align(size_t b) { return (b + 255) & ~size_t(255); }
 void* ws_take(lrdm_ctx* ctx, size_t bytes);
+// Whether the context's stream is being captured into a graph.
+bool capturing(const lrdm_ctx* ctx);
 // Whether the workspace holds `want`, grown to it where that can be had (no limit, capture
 // or refused allocation in the way).  A workspace that covers `least` is kept otherwise.
 bool ws_prefer(lrdm_ctx* ctx, size_t want, size_t least);

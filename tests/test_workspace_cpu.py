@@ -109,3 +109,23 @@ def test_growth_for_a_preferred_size_keeps_the_workspace_until_it_succeeds(lib):
         c.device(refuse_from=held + 1)
         c.project(large)
         assert (c.bytes, c.moves()) == (held, moves)
+
+
+def test_a_captured_workspace_is_kept(lib):
+    """A call captured into a graph holds the workspace's address: calls that could run
+    within it do not move it afterwards, whatever size they prefer."""
+    small, large = (12, 12, 12), (24, 24, 24)
+    most = preferred(lib, large)
+    with Calls(lib, stream=1) as c:
+        c.project(small, r=8)
+        held, moves = c.bytes, c.moves()
+        assert held < most
+        c.device(capturing=1)
+        c.project(small, r=8)
+        c.device()
+        c.project(large)
+        assert (c.bytes, c.moves()) == (held, moves)
+    with Calls(lib, stream=1) as c:    # nothing captured: it grows
+        c.project(small, r=8)
+        c.project(large)
+        assert c.bytes == most
