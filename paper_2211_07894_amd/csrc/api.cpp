@@ -1643,7 +1643,7 @@ extern "C" lrdm_status lrdm_autotune(lrdm_ctx* ctx, const lrdm_grid* grid, int32
     for (int k = 0; k < 3; ++k) {
       const Kind& kd = kinds[k];
       const int h = tn_default_splits(N, g.M, kd.b, kd.arith, ctx->split_limit);
-      const int cap = tn_range_cap(N, g.M, kd.b, ctx->split_limit);
+      const int cap = tn_range_cap(N, g.M, kd.b, kd.arith, ctx->split_limit);
       const std::array<int64_t, 5> key{N, g.M, kd.b, kd.arith, kd.weighted ? 1 : 0};
       int best = h, best_v = TN_VAR_DEFAULT;
       double best_ms = 1e300;

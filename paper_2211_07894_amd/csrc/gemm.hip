@@ -544,19 +544,22 @@ static size_t tn_range_bytes(int N, int batch) {
   return (size_t)batch * (ntb * (ntb + 1) / 2) * BT * BT * sizeof(double);
 }
 
-// Ranges the partial sums have room for: tn_split_cap, or with a workspace of the
-// preferred size (split_limit 0) as many as fill 96 MiB, each at least 512 points.
-int tn_range_cap(int N, int64_t M, int batch, int split_limit) {
+// Ranges the partial sums have room for: tn_split_cap, or for the forms that use more
+// (FP32 and BF16X3) with a workspace of the preferred size (split_limit 0) as many as
+// fill 96 MiB, each at least 512 points.
+int tn_range_cap(int N, int64_t M, int batch, int order, int split_limit) {
   const int ntb = (N + BT - 1) / BT;
   const int cap = tn_split_cap(ntb * (ntb + 1) / 2 * batch, M);
   if (split_limit > 0) return std::min(cap, split_limit);
+  if (order == TN_ARITH_F64 || order == TN_ORDERED_F64) return cap;
   const int64_t room = (int64_t)(((size_t)96 << 20) / tn_range_bytes(N, batch));
   return (int)std::max<int64_t>(cap, std::min<int64_t>(room, M / 512));
 }
 
-size_t tn_part_bytes(int N, int64_t M, int batch, int split_limit) {
-  const size_t tiles = tn_range_cap(N, M, batch, split_limit) * tn_range_bytes(N, batch);
-  return split_limit > 0 ? tiles : std::max(tiles, tn_direct_bytes(N, M, batch));
+size_t tn_part_bytes(int N, int64_t M, int batch, int order, int split_limit) {
+  const size_t tiles = tn_range_cap(N, M, batch, order, split_limit) * tn_range_bytes(N, batch);
+  return split_limit > 0 || order != TN_ARITH_F64 ? tiles
+                                                  : std::max(tiles, tn_direct_bytes(N, M, batch));
 }
 
 // FP32 arithmetic (whose partial sums are grouped by K-tile, so that any count gives the
@@ -568,11 +571,11 @@ size_t tn_part_bytes(int N, int64_t M, int batch, int split_limit) {
 // 64^3, 700, 2: 7 ranges 5069, 14 3904, 42 3564; 48^3, 256, 8: 21 888, 64 872; 24^3, 32,
 // 4: 33 us (512-point ranges), 566 with ranges of at least 2048 points on 128-row tiles.
 // The other arithmetics: tn_splits.
-int tn_default_splits(int N, int64_t M, int batch, int arith, int split_limit) {
+int tn_default_splits(int N, int64_t M, int batch, int order, int split_limit) {
   const int ntb = (N + BT - 1) / BT;
   const int items = ntb * (ntb + 1) / 2 * batch;
-  if (arith != TN_ARITH_F32) return tn_splits(items, M);
-  const int cap = tn_range_cap(N, M, batch, split_limit);
+  if (order != TN_ARITH_F32) return tn_splits(items, M);
+  const int cap = tn_range_cap(N, M, batch, order, split_limit);
   const int halves = 2 * items - (N - (ntb - 1) * BT <= BT / 2 ? ntb * batch : 0);
   int best = 1;
   double least = 1e300;
@@ -596,7 +599,8 @@ int tn_range_parts(int N, int64_t M, int batch, int nsplit, int64_t kchunk, int 
   const int ntb = (N + BT - 1) / BT;
   const int64_t wgs = (int64_t)(ntb * (ntb + 1) / 2) * batch * nsplit;
   const int64_t groups = (kchunk + BT - 1) / BT;
-  const int most = (int)std::min<int64_t>(groups, tn_range_cap(N, M, batch, split_limit) / nsplit);
+  const int most = (int)std::min<int64_t>(
+      groups, tn_range_cap(N, M, batch, TN_ARITH_BF16X3, split_limit) / nsplit);
   auto cost_of = [&](int q) {
     const double rounds = (double)((wgs * q + 255) / 256);
     return rounds * ((double)((groups + q - 1) / q * (BT / KT)) + 12.0);
@@ -620,7 +624,7 @@ int tn_split_count(const lrdm_ctx* ctx, int N, int64_t M, int batch, int arith, 
   const auto it = ctx->tn_tuned.find({N, M, batch, arith, weighted ? 1 : 0});
   int s = tn_default_splits(N, M, batch, order, ctx->split_limit);
   if (it != ctx->tn_tuned.end() && it->second >= 1 &&
-      it->second <= tn_range_cap(N, M, batch, ctx->split_limit))
+      it->second <= tn_range_cap(N, M, batch, order, ctx->split_limit))
     s = it->second;
   if (ctx->split_limit > 0) s = std::min(s, std::min(ctx->split_limit, tn_split_cap(ntiles * batch, M)));
   return s;
@@ -632,7 +636,8 @@ int tn_variant(const lrdm_ctx* ctx, int N, int64_t M, int batch, int arith, bool
 }
 
 size_t tn_workspace_bytes(int N, int64_t M, int batch, lrdm_prec prec, int split_limit) {
-  return ws_align(tn_part_bytes(N, M, batch, split_limit)) + tn_split_bytes(N, M, prec);
+  const int order = prec == LRDM_FP64 ? TN_ARITH_F64 : TN_ARITH_F32;
+  return ws_align(tn_part_bytes(N, M, batch, order, split_limit)) + tn_split_bytes(N, M, prec);
 }
 
 template <typename SA, typename SB>
@@ -641,18 +646,20 @@ hipError_t launch_tn_sym_f64(lrdm_ctx* ctx, const SA* A, const SB* B, const doub
                              double* H, const unsigned char* active) {
   const int ntb = (N + BT - 1) / BT;
   const int ntiles = ntb * (ntb + 1) / 2;
-  const int ns = tn_split_count(ctx, N, M, batch, TN_ARITH_F64, w != nullptr, TN_ARITH_F64);
+  constexpr bool fp32 = sizeof(SA) == sizeof(float);
+  constexpr int order = fp32 ? TN_ORDERED_F64 : TN_ARITH_F64;
+  const int ns = tn_split_count(ctx, N, M, batch, TN_ARITH_F64, w != nullptr, order);
   int64_t kchunk = (M + ns - 1) / ns;
   kchunk = (kchunk + KT - 1) / KT * KT;
-  double* part = static_cast<double*>(ws_take(ctx, tn_part_bytes(N, M, batch, ctx->split_limit)));
+  const size_t room = tn_part_bytes(N, M, batch, order, ctx->split_limit);
+  double* part = static_cast<double*>(ws_take(ctx, room));
   // A block held in FP32 keeps one order of its sums (that of this kernel, at any tile edge):
   // the basis an ill-conditioned filtered block is orthonormalised to is rounded to FP32, so
   // that a Gram matrix off by one rounding moves its Ritz pairs by far more.
-  constexpr bool fp32 = sizeof(SA) == sizeof(float);
   if constexpr (!fp32) {
     if (tn_direct_ok(N, M, batch)) {
       // the autotuned count, relative to the default one, scales the number of ranges
-      const TnDirectPlan p = tn_direct_plan(N, M, batch, tn_part_bytes(N, M, batch, ctx->split_limit),
+      const TnDirectPlan p = tn_direct_plan(N, M, batch, room,
                                             (double)ns / tn_splits(ntiles * batch, M));
       if (B)
         return launch_tn_direct<SA, SB>(ctx, p, A, B, w, w_stride, N, M, nspin, batch, part, H, active,

@@ -1744,7 +1744,7 @@ hipError_t launch_tn_sym<float>(lrdm_ctx* ctx, const float* A, const float* B, c
                                 p3 ? TN_ARITH_BF16X3 : TN_ARITH_F32);
   int64_t kchunk = (M + ns - 1) / ns;
   kchunk = (kchunk + KT - 1) / KT * KT;
-  double* part = static_cast<double*>(ws_take(ctx, tn_part_bytes(N, M, batch, ctx->split_limit)));
+  double* part = static_cast<double*>(ws_take(ctx, tn_part_bytes(N, M, batch, TN_ARITH_F32, ctx->split_limit)));
   const unsigned grd = (unsigned)(ntiles * ns * batch);
   if (p3) {
     // pieces of Psi once per call (or those the context holds for this block), then
@@ -2054,7 +2054,8 @@ hipError_t launch_tn_sym_fused(lrdm_ctx* ctx, const FusedProjItem* items, int n)
                                     it.batch, LRDM_FP32, it.H, it.active));
       continue;
     }
-    parts[k] = static_cast<double*>(ws_take(ctx, tn_part_bytes(it.N, it.M, it.batch, ctx->split_limit)));
+    parts[k] = static_cast<double*>(
+        ws_take(ctx, tn_part_bytes(it.N, it.M, it.batch, TN_ARITH_F32, ctx->split_limit)));
     splits[k] = ns;
     const int s = t.nsys++;
     const int used = 2 * ntiles * ns * it.batch;

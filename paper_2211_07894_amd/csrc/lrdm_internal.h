@@ -228,7 +228,7 @@ hipError_t launch_recursive_multiplier(lrdm_ctx* ctx, const double* eps, const d
 constexpr int kLeanSplits = 1 << 30;
 size_t tn_workspace_bytes(int N, int64_t M, int batch, lrdm_prec prec, int split_limit = 0);
 size_t tn_split_bytes(int N, int64_t M, lrdm_prec prec);
-size_t tn_part_bytes(int N, int64_t M, int batch, int split_limit = 0);
+size_t tn_part_bytes(int N, int64_t M, int batch, int order, int split_limit = 0);
 // Split count of the K = M contraction: enough blocks to fill 256 CUs several
 // times over, with each split at least 4096 grid points long.
 inline int tn_splits(int tiles_x_batch, int64_t M) {
@@ -251,7 +251,9 @@ size_t noalloc_scratch_bytes();
 hipError_t noalloc_scratch(int device, void** out);
 
 // Arithmetic of a projection contraction, part of the autotuner's key.
-enum { TN_ARITH_F64 = 0, TN_ARITH_F32 = 1, TN_ARITH_BF16X3 = 2 };
+// TN_ORDERED_F64 (not in a key): FP64 arithmetic on an FP32 block, which keeps one order of
+// its sums.
+enum { TN_ARITH_F64 = 0, TN_ARITH_F32 = 1, TN_ARITH_BF16X3 = 2, TN_ORDERED_F64 = 3 };
 // Kernel variants of the FP32-storage projection (tile and wave layout):
 //  TN_VAR_DEFAULT  8 waves of 32 x 64 on a 128 x 128 tile, operands copied to LDS
 //                  through a three-stage ring (BF16X3: Psi's pieces split once
@@ -270,7 +272,8 @@ enum { BP_VAR_NARROW = 0, BP_VAR_WIDE = 1 };
 int tn_variant(const lrdm_ctx* ctx, int N, int64_t M, int batch, int arith, bool weighted);
 // The split count a projection launch uses: the autotuned one for this shape and
 // arithmetic if lrdm_autotune chose one, else the default of `order`, the arithmetic
-// whose sums bind the count (TN_ARITH_F32 where FP32 sums end with each K-tile).
+// whose sums bind the count and its room (TN_ARITH_F32 where FP32 sums end with each
+// K-tile).
 int tn_default_splits(int N, int64_t M, int batch, int order, int split_limit);
 int tn_split_count(const lrdm_ctx* ctx, int N, int64_t M, int batch, int arith, bool weighted,
                    int order);
@@ -279,7 +282,7 @@ int tn_split_count(const lrdm_ctx* ctx, int N, int64_t M, int batch, int arith, 
 hipError_t launch_tn_reduce(lrdm_ctx* ctx, const double* part, int N, int T, int nsplit, int batch,
                             double* H, bool in_order = false);
 // Ranges the partial sums have room for, and the parts a BF16X3 range is cut into.
-int tn_range_cap(int N, int64_t M, int batch, int split_limit);
+int tn_range_cap(int N, int64_t M, int batch, int order, int split_limit);
 int tn_range_parts(int N, int64_t M, int batch, int nsplit, int64_t kchunk, int split_limit);
 // T is the storage type of A and B; prec selects the arithmetic (LRDM_FP64: FP64
 // matrix cores on either storage type; LRDM_FP32 / LRDM_BF16X3: FP32 storage only).

@@ -552,7 +552,8 @@ size_t rr_workspace_bytes(int N, int64_t M, lrdm_prec prec, int split_limit) {
   inner = std::max(inner, 2 * ws_align((size_t)Np * Np * sizeof(double)) +
                               ws_align((size_t)(nb / 2) * JS * JS * 8) + ws_align(256) +
                               ws_align((size_t)Np * 4) + ws_align(kFrobBlocks * sizeof(double)));
-  inner = std::max(inner, ws_align(tn_workspace_bytes(N, M, 1, prec, split_limit)));
+  const int order = prec == LRDM_FP64 ? TN_ARITH_F64 : TN_ORDERED_F64;
+  inner = std::max(inner, ws_align(tn_part_bytes(N, M, 1, order, split_limit)));
   if (prec == LRDM_BF16X3) inner = std::max(inner, rotate_bf16x3_bytes(N, M));
   return b + inner;
 }
@@ -1035,7 +1036,8 @@ size_t rr_bloch_workspace_bytes(int N, int64_t M, lrdm_prec prec, int split_limi
   inner = std::max(inner, 2 * ws_align((size_t)Np * Np * sizeof(double)) +
                               ws_align((size_t)(nb / 2) * JS * JS * 8) + ws_align(256) +
                               ws_align((size_t)Np * 4) + ws_align(kFrobBlocks * sizeof(double)));
-  inner = std::max(inner, ws_align(tn_workspace_bytes(n2, 2 * M, 1, prec, split_limit)));
+  const int order = prec == LRDM_FP64 ? TN_ARITH_F64 : TN_ORDERED_F64;
+  inner = std::max(inner, ws_align(tn_part_bytes(n2, 2 * M, 1, order, split_limit)));
   return b + inner;
 }
 

@@ -32,8 +32,8 @@ def lib():
 
 
 class Calls:
-    """FP64 projections of one context: the preferred partial sums grow with the points,
-    the least ones much less."""
+    """Projections of one context: the preferred partial sums grow with the points, the
+    least ones much less."""
 
     def __init__(self, lib, stream=0, limit=0):
         self.lib, self.ctx = lib, ctypes.c_void_p()
@@ -57,21 +57,24 @@ class Calls:
     def moves(self):
         return self.lib.lrdm_emu_mallocs(), self.lib.lrdm_emu_frees()
 
-    def project(self, n, N=3, r=1):
+    def project(self, n, N=40, r=1, prec="fp64"):
         rng = np.random.default_rng(n[0] + N)
         M = n[0] * n[1] * n[2]
         P, dV = rng.standard_normal((N, M)), rng.standard_normal((r, M))
+        P = P.astype(np.float64 if prec == "fp64" else np.float32)
         H = np.zeros((r, N, N))
         g = B.c_grid()
         for d in range(3):
             g.n[d], g.L[d] = n[d], 0.4 * n[d]
         p = lambda a: a.ctypes.data_as(ctypes.c_void_p)  # noqa: E731
         st = self.lib.lrdm_projected_perturbation(self.ctx, ctypes.byref(g), p(P), N, 1, p(dV), r,
-                                                  0, p(H))
+                                                  B.PREC[prec], p(H))
         assert st == 0, self.lib.lrdm_last_error(self.ctx)
-        ref = np.einsum("im,rm,jm->rij", P, dV, P)
-        # an FP64 sum of M terms: M u of their absolute sum, about sqrt(M) times the result
-        assert np.abs(H - ref).max() < M ** 1.5 * 2.0 ** -53 * np.abs(ref).max()
+        ref = (P[None].astype(np.float64) * dV[:, None]) @ P.astype(np.float64).T
+        # a sum of M terms in FP64 (of K-tiles of 32 in FP32): M u (32 u) of their absolute
+        # sum, about sqrt(M) times the result
+        bound = M * 2.0 ** -53 if prec == "fp64" else 32 * 2.0 ** -24
+        assert np.abs(H - ref).max() < M ** 0.5 * bound * np.abs(ref).max()
 
 
 def preferred(lib, n, **kw):
@@ -93,8 +96,8 @@ def test_a_refused_preferred_size_costs_one_attempt(lib):
             assert (c.bytes, c.moves()) == (held, moves)
         # a call that needs more asks for what it prefers again
         c.device()
-        c.project((32, 32, 32), r=40)
-        assert c.bytes == preferred(lib, (32, 32, 32), r=40)
+        c.project((32, 32, 32), r=10)
+        assert c.bytes == preferred(lib, (32, 32, 32), r=10)
 
 
 def test_growth_for_a_preferred_size_keeps_the_workspace_until_it_succeeds(lib):
@@ -103,7 +106,7 @@ def test_growth_for_a_preferred_size_keeps_the_workspace_until_it_succeeds(lib):
     small, large = (12, 12, 12), (24, 24, 24)
     most = preferred(lib, large)
     with Calls(lib) as c:
-        c.project(small, r=8)
+        c.project(small, r=4)
         held, moves = c.bytes, c.moves()
         assert held < most
         c.device(refuse_from=held + 1)
@@ -117,15 +120,24 @@ def test_a_captured_workspace_is_kept(lib):
     small, large = (12, 12, 12), (24, 24, 24)
     most = preferred(lib, large)
     with Calls(lib, stream=1) as c:
-        c.project(small, r=8)
+        c.project(small, r=4)
         held, moves = c.bytes, c.moves()
         assert held < most
         c.device(capturing=1)
-        c.project(small, r=8)
+        c.project(small, r=4)
         c.device()
         c.project(large)
         assert (c.bytes, c.moves()) == (held, moves)
     with Calls(lib, stream=1) as c:    # nothing captured: it grows
-        c.project(small, r=8)
+        c.project(small, r=4)
         c.project(large)
         assert c.bytes == most
+
+
+def test_fp32_projection_holds_its_own_partial_sums_only(lib):
+    """128 x 128 tiles of ranges of 512 points and more; the 64-row tiles of the FP64 form
+    would take twice that here."""
+    n, N = (24, 24, 24), 200
+    ranges, tiles = 24 ** 3 // 512, 3
+    most = ranges * tiles * 128 * 128 * 8 + (1 << 20) + 256
+    assert preferred(lib, n, N=N, prec="fp32") <= most
