@@ -2028,22 +2028,13 @@ hipError_t launch_tn_sym_fused(lrdm_ctx* ctx, const FusedProjItem* items, int n)
   const auto order = by_work(items, n, [](const FusedProjItem& it) {
     return (double)it.M * it.N * it.N * it.batch;
   });
-  auto tiles_of = [](const FusedProjItem& it) {
-    const int ntb = (it.N + BT - 1) / BT;
-    return ntb * (ntb + 1) / 2 * it.batch;
-  };
-  // Systems that fill the 512 slots together with ranges as long as tn_split_cap leaves
-  // them keep those: six systems of 32^3 to 56^3 (64 to 512
-  // states) take 36.3 ms, with the shorter ranges 36.6.
-  int64_t filled = 0;
-  for (int k = 0; k < n; ++k)
-    filled += 2 * (int64_t)tiles_of(items[k]) * tn_split_cap(tiles_of(items[k]), items[k].M);
   for (int k : order) {
     const FusedProjItem& it = items[k];
     const int ntb = (it.N + BT - 1) / BT;
     const int ntiles = ntb * (ntb + 1) / 2;
-    int ns = tn_split_count(ctx, it.N, it.M, it.batch, TN_ARITH_F32, true, TN_ARITH_F32);
-    if (filled >= 1024) ns = std::min(ns, tn_split_cap(tiles_of(it), it.M));
+    // the count of a call of its own, so that the sums are its too (six systems of 32^3 to
+    // 56^3, 64 to 512 states: long ranges for all, as they fill the chip together, save 1 %)
+    const int ns = tn_split_count(ctx, it.N, it.M, it.batch, TN_ARITH_F32, true, TN_ARITH_F32);
     int64_t kchunk = (it.M + ns - 1) / ns;
     kchunk = (kchunk + KT - 1) / KT * KT;
     const bool pipe = it.M % 4 == 0 && a16(it.A) && a16(it.w) &&
