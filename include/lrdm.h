@@ -374,8 +374,12 @@ typedef struct {
  * round-robin on four streams owned by the context, forked from and joined back
  * to the context's stream, so they run concurrently; a caller that captures the
  * context's stream into a HIP graph gets the whole batch as one graph.  The
- * workspace (one region per system) must already be large enough when the call
- * is captured: make the same call once before capturing, else LRDM_ENOMEM.
+ * workspace (one region per stream; in the FP32 form one set of launches serves
+ * up to 16 systems at a time, and all hold their copies) must already be large
+ * enough when the call is captured: make the same call once before capturing, else
+ * LRDM_ENOMEM.  With the workspace that both prefer, a system's results are those of
+ * density_response to the bit; under a limit that only one of them fits, the
+ * projection's FP64 sums may be grouped otherwise.
  * Every system is validated as in density_response before anything is
  * launched; outputs of different systems must not overlap. */
 lrdm_status density_response_batched(lrdm_ctx* ctx, const lrdm_system* sys, int32_t nsys,

@@ -4,7 +4,9 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <new>
+#include <numeric>
 #include <stdexcept>
 #include <string>
 
@@ -711,13 +713,52 @@ size_t backward_bytes(int N, int64_t M, int r, int ns, lrdm_prec prec, int split
          ws_align((size_t)batch * M * 8) + ws_align(scratch) + 4096;
 }
 
+// What a response holds beside the scratch of its projection and back-projection.
+size_t response_state_bytes(int N, int r, int ns) {
+  return ws_align(8) + ws_align((size_t)r * 8) + 3 * ws_align((size_t)ns * N * 8) +
+         block_mask_bytes(N, ns) + ws_align((size_t)ns * N * N * 8) +
+         ws_align((size_t)r * ns * N * N * 8);
+}
+
 size_t response_bytes(int N, int64_t M, int r, int ns, lrdm_prec prec, int split_limit = 0) {
   const int batch = r * ns;
-  return ws_align(8) + ws_align((size_t)r * 8) + 3 * ws_align((size_t)ns * N * 8) +
-         block_mask_bytes(N, ns) +
-         ws_align((size_t)ns * N * N * 8) + ws_align((size_t)batch * N * N * 8) +
-         ws_align(tn_bytes(N, M, batch, prec, split_limit)) +
+  return response_state_bytes(N, r, ns) + ws_align(tn_bytes(N, M, batch, prec, split_limit)) +
          backproj_workspace_bytes(N, M, ns, batch, prec);
+}
+
+// Whether a batch's projections and back-projections share launches (else its systems go
+// round-robin over the aux streams).
+bool batch_fused(const lrdm_ctx* ctx, lrdm_prec prec) {
+  return prec == LRDM_FP32 && ctx->fermi_depth == 0;
+}
+
+// A fused batch: every system's state, then the partial sums of the largest systems
+// of one launch, and in their place the back-projections' copies.
+size_t fused_batch_bytes(const lrdm_system* sys, int nsys, lrdm_prec prec, int split_limit) {
+  size_t state = 0, copies = 0, sums = 0;
+  std::vector<size_t> part(nsys);
+  for (int s = 0; s < nsys; ++s) {
+    const int N = sys[s].N, r = sys[s].r, ns = sys[s].occ.nspin;
+    const int64_t M = grid_points(&sys[s].grid);
+    state += response_state_bytes(N, r, ns);
+    copies += backproj_workspace_bytes(N, M, ns, r * ns, prec);
+    part[s] = ws_align(tn_bytes(N, M, r * ns, prec, split_limit));
+  }
+  std::sort(part.begin(), part.end(), std::greater<size_t>());
+  for (int s = 0; s < std::min(nsys, kMaxFused); ++s) sums += part[s];
+  return state + std::max(sums, copies);
+}
+
+// One region per aux stream, for the largest of its systems: they run one after another.
+std::array<size_t, kAuxStreams> batch_regions(const lrdm_system* sys, int nsys, lrdm_prec prec,
+                                              int split_limit) {
+  std::array<size_t, kAuxStreams> bytes{};
+  for (int s = 0; s < nsys; ++s)
+    bytes[s % kAuxStreams] = std::max(
+        bytes[s % kAuxStreams],
+        ws_align(response_bytes(sys[s].N, grid_points(&sys[s].grid), sys[s].r, sys[s].occ.nspin,
+                                prec, split_limit)));
+  return bytes;
 }
 
 }  // namespace
@@ -1180,15 +1221,19 @@ extern "C" lrdm_status density_response_batched(lrdm_ctx* ctx, const lrdm_system
     LRDM_NONNULL(ctx, y.dV, "sys[].dV");
     LRDM_NONNULL(ctx, y.drho, "sys[].drho");
   }
-  lrdm_status st = begin_sized(ctx, [&](int sl) {
-    size_t total = 0;
-    for (int s = 0; s < nsys; ++s)
-      total += ws_align(response_bytes(sys[s].N, grid_points(&sys[s].grid), sys[s].r,
-                                       sys[s].occ.nspin, prec, sl));
-    return total;
-  });
+  if (!ctx) return fail(nullptr, LRDM_EINVAL, "ctx is NULL");
+  lrdm_status st;
+  try {
+    st = begin_sized(ctx, [&](int sl) {
+      if (batch_fused(ctx, prec)) return fused_batch_bytes(sys, nsys, prec, sl);
+      const auto bytes = batch_regions(sys, nsys, prec, sl);
+      return std::accumulate(bytes.begin(), bytes.end(), size_t(0));
+    });
+  } catch (const std::bad_alloc&) {
+    return fail(ctx, LRDM_ENOMEM, "host allocation failed");
+  }
   if (st != LRDM_OK) return st;
-  if (prec == LRDM_FP32 && ctx->fermi_depth == 0) {
+  if (batch_fused(ctx, prec)) {
     // the systems' projections in one launch, then their back-projections in one
     // launch, on the context's stream (the small per-system steps in between)
     return guarded(ctx, [&]() -> lrdm_status {
@@ -1228,15 +1273,22 @@ extern "C" lrdm_status density_response_batched(lrdm_ctx* ctx, const lrdm_system
     for (int k = 0; e == hipSuccess && k < K; ++k)
       e = hipStreamWaitEvent(ctx->aux[k], ctx->fork_join[0], 0);
     if (e != hipSuccess) return fail_hip(ctx, "batched fork", e);
-    struct Restore {              // ctx->stream is main again however the loop ends
+    struct Restore {              // stream and workspace are whole again however the loop ends
       lrdm_ctx* c;
       hipStream_t s;
-      ~Restore() { c->stream = s; }
-    } restore{ctx, main};
+      size_t cap;
+      ~Restore() {
+        c->stream = s;
+        c->ws_cap = cap;
+      }
+    } restore{ctx, main, ctx->ws_cap};
+    const auto bytes = batch_regions(sys, nsys, prec, ctx->split_limit);
     for (int s = 0; s < nsys; ++s) {
       const lrdm_system& y = sys[s];
       const Grid3 g = make_grid3(&y.grid);
       ctx->stream = ctx->aux[s % K];
+      ctx->ws_top = std::accumulate(bytes.begin(), bytes.begin() + s % K, size_t(0));
+      ctx->ws_cap = ctx->ws_top + bytes[s % K];
       e = (prec == LRDM_FP64)
           ? run_response<double>(ctx, g, static_cast<const double*>(y.Psi), y.eps, y.N, &y.occ,
                                  y.dV, y.r, prec, nullptr, y.drho, y.mu, y.dmu)

@@ -772,8 +772,6 @@ __global__ __launch_bounds__(HT, 4) void backproj_pipe_kernel(
 // independent systems: system s owns workgroups [wg0[s], wg0[s+1]) (each range
 // a multiple of the XCD count, so that a system's own XCD grouping holds; the
 // padding workgroups exit at once), with its operands passed by value.
-constexpr int kMaxFused = 16;
-
 struct FusedProj {
   int nsys;
   int wg0[kMaxFused + 1];
@@ -2008,11 +2006,11 @@ hipError_t launch_tn_sym_fused(lrdm_ctx* ctx, const FusedProjItem* items, int n)
   const int smem = NST * (HB + TB + 1024);
   LRDM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&tn_sym_fused_kernel),
                                hipFuncAttributeMaxDynamicSharedMemorySize, smem));
-  std::vector<double*> parts(n, nullptr);
-  std::vector<int> splits(n, 0);
+  const size_t mark = ctx->ws_top;
   FusedProj t{};
-  t.nsys = 0;
+  int system[kMaxFused];      // of the launch being filled
   int total = 0;
+  // one launch and its reductions; the next launch's partial sums take their place
   auto flush = [&]() -> hipError_t {
     if (t.nsys == 0) return hipSuccess;
     t.wg0[t.nsys] = total;
@@ -2020,16 +2018,35 @@ hipError_t launch_tn_sym_fused(lrdm_ctx* ctx, const FusedProjItem* items, int n)
       ProfScope prof(ctx, "proj");
       tn_sym_fused_kernel<<<(unsigned)total, HT, smem, ctx->stream>>>(t, ctx->zeros);
     }
+    LRDM_HIP(hipGetLastError());
+    for (int s = 0; s < t.nsys; ++s) {
+      const FusedProjItem& it = items[system[s]];
+      LRDM_HIP(launch_tn_reduce(ctx, t.part[s], it.N, BT, t.nsplit[s], it.batch, it.H));
+    }
     t = FusedProj{};
-    t.nsys = 0;
     total = 0;
-    return hipGetLastError();
+    ctx->ws_top = mark;
+    return hipSuccess;
   };
   const auto order = by_work(items, n, [](const FusedProjItem& it) {
     return (double)it.M * it.N * it.N * it.batch;
   });
+  auto pipe = [&](const FusedProjItem& it) {
+    return it.M % 4 == 0 && a16(it.A) && a16(it.w) &&
+           tn_variant(ctx, it.N, it.M, it.batch, TN_ARITH_F32, true) == TN_VAR_DEFAULT;
+  };
+  // a system the copy engine cannot stage, or tuned to another layout of tiles and
+  // waves, goes alone
   for (int k : order) {
     const FusedProjItem& it = items[k];
+    if (pipe(it)) continue;
+    LRDM_HIP(launch_tn_sym<float>(ctx, it.A, nullptr, it.w, it.M, it.N, it.M, it.nspin, it.batch,
+                                  LRDM_FP32, it.H, it.active));
+    ctx->ws_top = mark;
+  }
+  for (int k : order) {
+    const FusedProjItem& it = items[k];
+    if (!pipe(it)) continue;
     const int ntb = (it.N + BT - 1) / BT;
     const int ntiles = ntb * (ntb + 1) / 2;
     // the count of a call of its own, so that the sums are its too (six systems of 32^3 to
@@ -2037,24 +2054,15 @@ hipError_t launch_tn_sym_fused(lrdm_ctx* ctx, const FusedProjItem* items, int n)
     const int ns = tn_split_count(ctx, it.N, it.M, it.batch, TN_ARITH_F32, true, TN_ARITH_F32);
     int64_t kchunk = (it.M + ns - 1) / ns;
     kchunk = (kchunk + KT - 1) / KT * KT;
-    const bool pipe = it.M % 4 == 0 && a16(it.A) && a16(it.w) &&
-                      tn_variant(ctx, it.N, it.M, it.batch, TN_ARITH_F32, true) == TN_VAR_DEFAULT;
-    if (!pipe) {      // a system the copy engine cannot stage, or tuned to another layout
-      // of tiles and waves, goes alone
-      LRDM_HIP(launch_tn_sym<float>(ctx, it.A, nullptr, it.w, it.M, it.N, it.M, it.nspin,
-                                    it.batch, LRDM_FP32, it.H, it.active));
-      continue;
-    }
-    parts[k] = static_cast<double*>(
-        ws_take(ctx, tn_part_bytes(it.N, it.M, it.batch, TN_ARITH_F32, ctx->split_limit)));
-    splits[k] = ns;
     const int s = t.nsys++;
     const int used = 2 * ntiles * ns * it.batch;
+    system[s] = k;
     t.wg0[s] = total;
     t.used[s] = used;
     t.A[s] = it.A;
     t.w[s] = it.w;
-    t.part[s] = parts[k];
+    t.part[s] = static_cast<double*>(
+        ws_take(ctx, tn_part_bytes(it.N, it.M, it.batch, TN_ARITH_F32, ctx->split_limit)));
     t.active[s] = it.active;
     t.M[s] = it.M;
     t.kchunk[s] = kchunk;
@@ -2066,13 +2074,7 @@ hipError_t launch_tn_sym_fused(lrdm_ctx* ctx, const FusedProjItem* items, int n)
     total += (used + 7) / 8 * 8;
     if (t.nsys == kMaxFused) LRDM_HIP(flush());
   }
-  LRDM_HIP(flush());
-  for (int k = 0; k < n; ++k) {
-    if (!parts[k]) continue;
-    const FusedProjItem& it = items[k];
-    LRDM_HIP(launch_tn_reduce(ctx, parts[k], it.N, BT, splits[k], it.batch, it.H));
-  }
-  return hipSuccess;
+  return flush();
 }
 
 hipError_t launch_backproj_fused(lrdm_ctx* ctx, const FusedBackprojItem* items, int n) {

@@ -341,8 +341,9 @@ hipError_t launch_backproj_direct(lrdm_ctx* ctx, const double* A, const double* 
 // The FP32-form projection and back-projection of several independent systems,
 // each in one launch over all of them (gemm_lp.hip): H = Psi^T diag(w) Psi per
 // direction and channel of each item, and out = scale * sum_ij Psi_i G_ij Psi_j,
-// skipping the blocks each item's `active` marks inactive.  The per-system
-// partial sums, FP32 copies and transposes come from the workspace.
+// skipping the blocks each item's `active` marks inactive.  The partial sums of one
+// launch's systems (given back), FP32 copies and transposes come from the workspace.
+constexpr int kMaxFused = 16;   // systems of one launch
 struct FusedProjItem {
   const float* A;          // Psi [nspin][N][M]
   const double* w;         // dV [batch][M]

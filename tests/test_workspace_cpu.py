@@ -22,6 +22,7 @@ def lib():
     lib.lrdm_destroy.argtypes = [vp]
     lib.lrdm_projected_perturbation.argtypes = [vp, ctypes.POINTER(B.c_grid), vp, i32, i32, vp,
                                                 i32, ctypes.c_int, vp]
+    lib.density_response_batched.argtypes = [vp, ctypes.POINTER(B.c_system), i32, ctypes.c_int]
     lib.lrdm_workspace_bytes.argtypes = lib.lrdm_last_error.argtypes = [vp]
     lib.lrdm_workspace_bytes.restype = ctypes.c_size_t
     lib.lrdm_last_error.restype = ctypes.c_char_p
@@ -75,6 +76,35 @@ class Calls:
         # sum, about sqrt(M) times the result
         bound = M * 2.0 ** -53 if prec == "fp64" else 32 * 2.0 ** -24
         assert np.abs(H - ref).max() < M ** 0.5 * bound * np.abs(ref).max()
+
+    def batch(self, count, n=(16, 16, 16), N=6, prec="fp64"):
+        """`count` systems of one size, which differ in their fields."""
+        rng = np.random.default_rng(count)
+        M = n[0] * n[1] * n[2]
+        sy, keep = (B.c_system * count)(), []
+        g = B.c_grid()
+        for d in range(3):
+            g.n[d], g.L[d] = n[d], 0.4 * n[d]
+        P = np.linalg.qr(rng.standard_normal((M, N)))[0].T
+        P = np.ascontiguousarray(P, dtype=np.float64 if prec == "fp64" else np.float32)
+        eps = np.linspace(-1.0, 0.5, N)
+        p = lambda a: a.ctypes.data_as(ctypes.c_void_p)  # noqa: E731
+        occ = B.c_occ(1, 0.05, float(N))
+        for k in range(count):
+            dV, drho, mu, dmu = rng.standard_normal((1, M)), np.zeros((1, M)), np.zeros(1), np.zeros(1)
+            keep.append((dV, drho))
+            sy[k] = B.c_system(g, p(P), p(eps), N, occ, p(dV), 1, p(drho), p(mu), p(dmu))
+            keep.append((mu, dmu))
+        st = self.lib.density_response_batched(self.ctx, sy, count, B.PREC[prec])
+        assert st == 0, self.lib.lrdm_last_error(self.ctx)
+        # each system against itself alone: to the bit
+        for k in range(count):
+            dV, drho = keep[2 * k]
+            got = drho.copy()
+            drho[:] = np.nan
+            one = (B.c_system * 1)(sy[k])
+            assert self.lib.density_response_batched(self.ctx, one, 1, B.PREC[prec]) == 0
+            assert np.array_equal(got, drho)
 
 
 def preferred(lib, n, **kw):
@@ -141,3 +171,17 @@ def test_fp32_projection_holds_its_own_partial_sums_only(lib):
     ranges, tiles = 24 ** 3 // 512, 3
     most = ranges * tiles * 128 * 128 * 8 + (1 << 20) + 256
     assert preferred(lib, n, N=N, prec="fp32") <= most
+
+
+def test_batch_workspace_is_bounded(lib):
+    """Systems that run one after another on a stream share its region, and the fused form's
+    partial sums (1 MiB a system here) are those of one launch of 16."""
+    held = {}
+    for prec in ("fp64", "fp32"):
+        for count in (4, 18, 34):
+            with Calls(lib) as c:
+                c.batch(count, prec=prec)
+                held[prec, count] = c.bytes
+    assert held["fp64", 34] == held["fp64", 4]
+    copies = 4096 * 32 * 4 + (1 << 16)          # Psi transposed, Gamma and the N x N matrices
+    assert held["fp32", 34] - held["fp32", 18] <= 16 * copies
