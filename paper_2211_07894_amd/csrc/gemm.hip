@@ -570,10 +570,27 @@ size_t tn_part_bytes(int N, int64_t M, int batch, int order, int split_limit) {
 // 64^3, 300 states, 3 directions: 18 ranges (1 round) 1839 us, 37 1750, 56 1538, 113 1550;
 // 64^3, 700, 2: 7 ranges 5069, 14 3904, 42 3564; 48^3, 256, 8: 21 888, 64 872; 24^3, 32,
 // 4: 33 us (512-point ranges), 566 with ranges of at least 2048 points on 128-row tiles.
-// The other arithmetics: tn_splits.
+// The other forms: tn_splits.
 int tn_default_splits(int N, int64_t M, int batch, int order, int split_limit) {
   const int ntb = (N + BT - 1) / BT;
   const int items = ntb * (ntb + 1) / 2 * batch;
+  if (order == TN_STAGED_LP) {
+    // Staged through registers (rows at any address): a workgroup per tile and CU, so that
+    // the long ranges of tn_splits can fill a round that the count above overfills: 27 x 33 x
+    // 35, 800 states, 2 channels, 4 ranges (224 workgroups) 1390 us, 10 1645; 129 states, 1
+    // channel, 4 ranges 1394, 60 108 (FP32).  Groups of tiles that divide among the XCDs stay
+    // on one each (xcd.h).
+    auto cost = [&](int s) {
+      const int64_t groups = (int64_t)s * batch;
+      const int64_t rounds = groups % 8 == 0 ? (groups / 8 * (items / batch) + 31) / 32
+                                             : (groups * (items / batch) + 255) / 256;
+      return rounds * (double)((M + KT * s - 1) / (KT * s) + 6);
+    };
+    const int ring = tn_default_splits(N, M, batch, TN_ARITH_F32, split_limit);
+    const int lengthy = std::min(tn_splits(items, M),
+                                 tn_range_cap(N, M, batch, order, split_limit));
+    return cost(lengthy) < 0.95 * cost(ring) ? lengthy : ring;
+  }
   if (order != TN_ARITH_F32) return tn_splits(items, M);
   const int cap = tn_range_cap(N, M, batch, order, split_limit);
   const int halves = 2 * items - (N - (ntb - 1) * BT <= BT / 2 ? ntb * batch : 0);

@@ -1721,6 +1721,16 @@ size_t tn_split_bytes(int N, int64_t M, lrdm_prec prec) {
   return prec == LRDM_BF16X3 ? ws_align((size_t)2 * 3 * N * M * sizeof(__bf16)) : 0;
 }
 
+// The ring kernels copy 16-byte chunks of rows: rows must start aligned; Psi's pieces have
+// rows of half that, one or two channels and Psi on both sides.
+int tn_lp_order(int arith, int variant, bool weighted, bool same, bool aligned, int64_t M,
+                int nspin) {
+  if (variant == TN_VAR_STAGED || M % 4 != 0 || !aligned) return TN_STAGED_LP;
+  const bool pieces = arith == TN_ARITH_BF16X3 && variant == TN_VAR_DEFAULT && weighted && same &&
+                      M % 8 == 0 && nspin <= 2;
+  return pieces ? TN_ARITH_BF16X3 : TN_ARITH_F32;
+}
+
 template <>
 hipError_t launch_tn_sym<float>(lrdm_ctx* ctx, const float* A, const float* B, const double* w,
                                 int64_t w_stride, int N, int64_t M, int nspin, int batch,
@@ -1731,20 +1741,17 @@ hipError_t launch_tn_sym<float>(lrdm_ctx* ctx, const float* A, const float* B, c
   const int ntiles = ntb * (ntb + 1) / 2;
   if (!B) B = A;
   auto a16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-  // the pipelined kernel copies 16-byte chunks of rows: rows must start aligned
-  const bool pipe = (M % 4 == 0) && a16(A) && a16(B) && (!w || (a16(w) && w_stride % 2 == 0));
+  const bool aligned = a16(A) && a16(B) && (!w || (a16(w) && w_stride % 2 == 0));
   const int arith = prec == LRDM_BF16X3 ? TN_ARITH_BF16X3 : TN_ARITH_F32;
   // the tile and wave layout lrdm_autotune chose for this shape (default otherwise)
   const int variant = tn_variant(ctx, N, M, batch, arith, w != nullptr);
-  const bool p3 = variant == TN_VAR_DEFAULT && pipe && w && B == A && prec == LRDM_BF16X3 &&
-                  M % 8 == 0 && nspin <= 2;
-  const int ns = tn_split_count(ctx, N, M, batch, arith, w != nullptr,
-                                p3 ? TN_ARITH_BF16X3 : TN_ARITH_F32);
+  const int order = tn_lp_order(arith, variant, w != nullptr, B == A, aligned, M, nspin);
+  const int ns = tn_split_count(ctx, N, M, batch, arith, w != nullptr, order);
   int64_t kchunk = (M + ns - 1) / ns;
   kchunk = (kchunk + KT - 1) / KT * KT;
   double* part = static_cast<double*>(ws_take(ctx, tn_part_bytes(N, M, batch, TN_ARITH_F32, ctx->split_limit)));
   const unsigned grd = (unsigned)(ntiles * ns * batch);
-  if (p3) {
+  if (order == TN_ARITH_BF16X3) {
     // pieces of Psi once per call (or those the context holds for this block), then
     // the weighted A side split in the kernel
     const lrdm_psi_pieces& pc = ctx->pieces;
@@ -1792,7 +1799,7 @@ hipError_t launch_tn_sym<float>(lrdm_ctx* ctx, const float* A, const float* B, c
   {
     ProfScope prof(ctx, w ? "proj" : "gram");
     const bool bf = (prec == LRDM_BF16X3);
-    if (variant == TN_VAR_STAGED || !pipe)
+    if (order == TN_STAGED_LP)
       LRDM_HIP(bf ? run_staged(tn_sym_lp_kernel<Core::BF3>) : run_staged(tn_sym_lp_kernel<Core::F32>));
     else if (w)
       LRDM_HIP(bf ? run_pipe(tn_sym_pipe_kernel<Core::BF3, true>)

@@ -185,3 +185,26 @@ def test_batch_workspace_is_bounded(lib):
     assert held["fp64", 34] == held["fp64", 4]
     copies = 4096 * 32 * 4 + (1 << 16)          # Psi transposed, Gamma and the N x N matrices
     assert held["fp32", 34] - held["fp32", 18] <= 16 * copies
+
+
+@pytest.mark.parametrize("M", [27 * 33 * 35, 45 ** 3, 63 * 61 * 63])
+@pytest.mark.parametrize("N,batch", [(40, 1), (90, 2), (129, 60), (257, 1), (400, 8), (800, 2)])
+def test_staged_ranges_fill_the_rounds(lib, M, N, batch):
+    """The count of a projection staged through registers, one workgroup per tile and CU: no
+    more rounds of workgroups, times K-tiles and a fixed cost of 6, than the longest ranges
+    take (groups of tiles that divide among the eight dies stay on one each)."""
+    splits = lib._ZN4lrdm17tn_default_splitsEiliii
+    cap = lib._ZN4lrdm12tn_range_capEiliii
+    for f in (splits, cap):
+        f.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_int]
+    tiles = -(-N // 128) * (-(-N // 128) + 1) // 2
+
+    def cost(s):
+        whole = s * batch % 8 == 0
+        rounds = -(-(s * batch // 8 * tiles) // 32) if whole else -(-s * batch * tiles // 256)
+        return rounds * (-(-M // (32 * s)) + 6)
+
+    long_ranges, staged = 0, 4
+    got = splits(N, M, batch, staged, 0)
+    assert 1 <= got <= cap(N, M, batch, staged, 0)
+    assert cost(got) <= cost(splits(N, M, batch, long_ranges, 0)) / 0.95
