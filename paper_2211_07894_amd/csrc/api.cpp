@@ -1694,12 +1694,17 @@ extern "C" lrdm_status lrdm_autotune(lrdm_ctx* ctx, const lrdm_grid* grid, int32
     } kinds[3] = {{batch, arith, true}, {nspin, arith, true}, {1, TN_ARITH_F64, false}};
     for (int k = 0; k < 3; ++k) {
       const Kind& kd = kinds[k];
-      const int h = tn_default_splits(N, g.M, kd.b, kd.arith, ctx->split_limit);
-      const int cap = tn_range_cap(N, g.M, kd.b, kd.arith, ctx->split_limit);
+      // the form a layout takes on this shape, and with it the count without tuning
+      auto order_of = [&](int v) -> int {
+        if (kd.arith == TN_ARITH_F64) return prec == LRDM_FP64 ? TN_ARITH_F64 : TN_ORDERED_F64;
+        return tn_lp_order(kd.arith, v, kd.weighted, true, true, g.M, nspin);
+      };
+      auto default_of = [&](int v) {
+        return tn_default_splits(N, g.M, kd.b, order_of(v), ctx->split_limit);
+      };
       const std::array<int64_t, 5> key{N, g.M, kd.b, kd.arith, kd.weighted ? 1 : 0};
-      int best = h, best_v = TN_VAR_DEFAULT;
+      int best = default_of(TN_VAR_DEFAULT), best_v = TN_VAR_DEFAULT;
       double best_ms = 1e300;
-      const int cand[4] = {h / 4, h / 2, h, 2 * h};
       // tile and wave layouts: one kernel for FP64 arithmetic, two for FP32,
       // three for BF16X3 (variants of TN_VAR_*)
       const int nvar = kd.arith == TN_ARITH_F64 ? 1 : (kd.arith == TN_ARITH_F32 ? 2 : 3);
@@ -1708,6 +1713,9 @@ extern "C" lrdm_status lrdm_autotune(lrdm_ctx* ctx, const lrdm_grid* grid, int32
           if (timings) timings[(k * 3 + v) * 4 + c] = 0.0;
       for (int v = 0; v < nvar; ++v)
       for (int c = 0; c < 4; ++c) {
+        const int h = default_of(v);
+        const int cap = tn_range_cap(N, g.M, kd.b, order_of(v), ctx->split_limit);
+        const int cand[4] = {h / 4, h / 2, h, 2 * h};
         const int s = cand[c];
         if (s < 1 || s > cap || (c > 0 && s == cand[c - 1])) continue;
         ctx->tn_variant[key] = v;

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import paper_2211_07894_amd as L
+from paper_2211_07894_amd import lrdm as B
 
 pytestmark = pytest.mark.gpu
 
@@ -46,3 +47,29 @@ def test_batch_sums_as_single_calls(prec):
             ref = L.density_response(s["grid"], s["Psi"], s["eps"], s["occ"], s["dV"], prec=prec)
             for got, want in zip((drho, mu, dmu), ref):
                 assert torch.equal(got, want)
+
+
+def _time(f, reps=10):
+    f()
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    a.record()
+    for _ in range(reps):
+        f()
+    b.record()
+    b.synchronize()
+    return a.elapsed_time(b) / reps
+
+
+# rows that cannot be copied in 16-byte chunks: the tuner tries the count an untuned call
+# takes, 60 ranges here (80 us; counts up to 8 take 460 us and more)
+@pytest.mark.parametrize("prec", ["fp32", "bf16x3"])
+def test_autotune_keeps_the_untuned_count_in_reach(prec):
+    n, N = (27, 33, 35), 90
+    grid, gen = _grid(n), _gen(1)
+    P, dV = _rand(gen, 2, N, grid.M, dtype=torch.float32), _rand(gen, 1, 2, grid.M)
+    call = lambda: L.projected_perturbation(grid, P, dV, 2, prec)  # noqa: E731
+    B.release_contexts()
+    untuned = _time(call)
+    L.autotune(grid, N, 2, 1, prec)
+    assert _time(call) < 2 * untuned
+    B.release_contexts()
