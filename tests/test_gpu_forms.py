@@ -73,3 +73,52 @@ def test_autotune_keeps_the_untuned_count_in_reach(prec):
     L.autotune(grid, N, 2, 1, prec)
     assert _time(call) < 2 * untuned
     B.release_contexts()
+
+
+def _chebyshev(grid, V, X, degree, a, b, a0):
+    """The scaled recurrence in FP64 by shifts."""
+    h = [grid.L[d] / grid.n[d] for d in range(3)]
+    e, c0 = (b - a) / 2, (b + a) / 2
+    s1 = s = e / (a0 - c0)
+
+    def shifted(y):
+        out = (V - c0) * y
+        for hd, ax in zip(h, (-1, -2, -3)):
+            out = out - 0.5 * (torch.roll(y, 1, ax) + torch.roll(y, -1, ax) - 2 * y) / hd ** 2
+        return out
+
+    y0, y1 = X, (s1 / e) * shifted(X)
+    for _ in range(2, degree + 1):
+        sn = 1.0 / (2.0 / s1 - s)
+        y0, y1 = y1, (2 * sn / e) * shifted(y1) - s * sn * y0
+        s = sn
+    return y1
+
+
+FORMS = ("cheb_step", "cheb_sweep", "cheb_lds")
+
+
+# the form the filter's plan takes, by its launches: a single step gains nothing from LDS,
+# more steps of states that fit it do
+@pytest.mark.parametrize("prec,n,N,degree,form,launches", [
+    ("fp64", (24, 24, 24), 40, 1, "cheb_step", 1), ("fp64", (24, 24, 24), 40, 2, "cheb_lds", 1),
+    ("fp32", (32, 32, 32), 5, 1, "cheb_step", 1), ("fp32", (32, 32, 32), 5, 64, "cheb_lds", 1),
+])
+def test_filter_takes_the_form_of_its_plan(prec, n, N, degree, form, launches):
+    grid, gen = _grid(n), _gen(degree)
+    dt = torch.float64 if prec == "fp64" else torch.float32
+    V, X = _rand(gen, *grid.shape), _rand(gen, N, *grid.shape, dtype=dt)
+    ctx = B.context(0)
+    for name in FORMS:
+        ctx.profile_read(name)
+    ctx.profile(True)
+    Y = L.chfsi_filter(grid, V, X, degree, 3.0, 34.0, -2.0, prec=prec)
+    ctx.profile(False)
+    ran = {name: ctx.profile_read(name)[1] for name in FORMS}
+    assert {name for name in FORMS if ran[name]} == {form}, ran
+    assert launches is None or ran[form] == launches, ran
+    pick = sorted({0, N // 2, N - 1})
+    ref = _chebyshev(grid, V, X[pick].double(), degree, 3.0, 34.0, -2.0)
+    # the scaled recurrence does not amplify: a few roundings a step
+    err = float((Y[pick].double() - ref).norm() / ref.norm())
+    assert err < 8 * degree * (2.0 ** -53 if prec == "fp64" else 2.0 ** -24)
