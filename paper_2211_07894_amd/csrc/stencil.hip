@@ -551,6 +551,14 @@ namespace {
 constexpr int kLdsBytes = 160 * 1024;
 constexpr int kCus = 256;
 
+// z runs of a single step: enough blocks for the chip (N * runs >= ~1024) but runs of
+// >= 8 planes.
+int cheb_step_runs(const Grid3& g, int N) {
+  int runs = 1;
+  while ((int64_t)N * runs < 1024 && g.nz / (runs * 2) >= 8) runs *= 2;
+  return runs;
+}
+
 // Planes a thread of cheb_lds_kernel owns (0: the state does not fit): nz over the
 // largest divisor of nz that leaves at most 1024 threads, at most 8.
 template <typename T>
@@ -596,7 +604,10 @@ ChebPlan cheb_plan(const Grid3& g, int N, int degree, int64_t room) {
     return p;
   }
   const double P = (double)g.nx * g.ny, block = (double)g.M * N * sizeof(T);
-  double best = degree * std::max(3.0 * block / 4.9e6, 6.0);
+  // a single step takes as long as its longest run of planes however few the states
+  const int step_planes = (g.nz + cheb_step_runs(g, N) - 1) / cheb_step_runs(g, N);
+  double best = degree * std::max(3.0 * block / 4.9e6,
+                                  2.0 + step_planes * (0.3 + 27e-6 * P * sizeof(T)));
   const int smax = std::min(degree, cheb_sweep_stages<T>(g));
   const int G = (int)(P / W), threads = G <= 1024 ? (G + 63) / 64 * 64 : ((G + 1) / 2 + 63) / 64 * 64;
   for (int S = 2; S <= smax; ++S) {
@@ -783,9 +794,7 @@ hipError_t launch_cheb_step_vec(lrdm_ctx* ctx, const Grid3& g, const T* Vt, cons
   const int G = g.nx * g.ny / W;
   if (!cheb_vec_ok<T>(g)) return hipErrorInvalidValue;
   const int threads = G <= 1024 ? ((G + 63) / 64) * 64 : 1024;
-  // z runs: enough blocks for the chip (N * runs >= ~1024) but runs of >= 8 planes
-  int runs = 1;
-  while ((int64_t)N * runs < 1024 && g.nz / (runs * 2) >= 8) runs *= 2;
+  const int runs = cheb_step_runs(g, N);
   const int zrun = (g.nz + runs - 1) / runs;
   if (G <= threads)
     return launch_vec<T, T, 1>(ctx, "cheb_step", g, Vt, Yin, Yold, Yout, N, threads, zrun, alpha,

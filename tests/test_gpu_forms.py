@@ -99,10 +99,12 @@ FORMS = ("cheb_step", "cheb_sweep", "cheb_lds")
 
 
 # the form the filter's plan takes, by its launches: a single step gains nothing from LDS,
-# more steps of states that fit it do
+# more steps of states that fit it do; few states of short columns, whose single steps take
+# as long as a column
 @pytest.mark.parametrize("prec,n,N,degree,form,launches", [
     ("fp64", (24, 24, 24), 40, 1, "cheb_step", 1), ("fp64", (24, 24, 24), 40, 2, "cheb_lds", 1),
     ("fp32", (32, 32, 32), 5, 1, "cheb_step", 1), ("fp32", (32, 32, 32), 5, 64, "cheb_lds", 1),
+    ("fp32", (64, 64, 12), 1, 20, "cheb_sweep", None), ("fp64", (48, 40, 13), 8, 5, "cheb_sweep", None),
 ])
 def test_filter_takes_the_form_of_its_plan(prec, n, N, degree, form, launches):
     grid, gen = _grid(n), _gen(degree)
