@@ -276,6 +276,47 @@ void scenario_chfsi(lrdm_ctx* ctx, lrdm_grid g, int N, int degree, lrdm_prec pre
   check(lrdm_hartree_kernel(ctx, &g, u.data(), dV.data(), 2), ctx, "hartree_kernel");
 }
 
+// The filter's sweeps of a plan, whatever cheb_plan would choose, against its single steps:
+// one and two groups a thread, runs of planes and batches that do not divide, a last sweep
+// of one step.  Exactly plan.states(N) states of workspace, so that the sanitizer sees any
+// access past them.
+template <typename T>
+void scenario_sweeps(lrdm_ctx* ctx, lrdm_grid gr, int N, int degree, int stages, int batch, int zrun) {
+  const lrdm::Grid3 g = lrdm::make_grid3(&gr);
+  const auto Vd = randv((size_t)g.M, 3, 0.5), Xd = randv((size_t)N * g.M, 4);
+  const std::vector<T> V(Vd.begin(), Vd.end()), X(Xd.begin(), Xd.end());
+  std::vector<double> a(degree), b(degree);
+  for (int k = 0; k < degree; ++k) {
+    a[k] = k == 0 ? 0.06 : 0.11;
+    b[k] = k == 0 ? 0.0 : -0.7;
+  }
+  const double c0 = 9.0;
+  lrdm::ChebPlan plan;
+  plan.kind = lrdm::ChebPlan::kSweeps;
+  plan.stages = stages;
+  plan.batch = batch;
+  plan.zrun = zrun;
+  std::vector<T> Y(X.size()), W((size_t)plan.states(N) * g.M), old, now(X.size()), cur = X;
+  hipError_t e = lrdm::launch_cheb_sweeps<T>(ctx, plan, g, V.data(), X.data(), Y.data(), W.data(), N,
+                                             c0, a, b);
+  for (int k = 0; k < degree && e == hipSuccess; ++k) {
+    e = lrdm::launch_cheb_step_vec<T>(ctx, g, V.data(), cur.data(), k ? old.data() : nullptr,
+                                      now.data(), N, a[k], c0, b[k]);
+    old = cur;
+    cur = now;
+  }
+  double num = 0, den = 0;
+  for (size_t i = 0; i < Y.size(); ++i) {
+    num += ((double)Y[i] - cur[i]) * ((double)Y[i] - cur[i]);
+    den += (double)cur[i] * cur[i];
+  }
+  const double d = std::sqrt(num / den), bound = sizeof(T) == 8 ? 1e-14 : 1e-5;
+  std::printf("%s sweeps of %d steps, %dx%dx%d, N=%d, %d stages, batch %d, runs of %d: off by %.1e\n",
+              e == hipSuccess && d < bound ? "ok  " : "FAIL", degree, g.nx, g.ny, g.nz, N, stages,
+              batch, zrun, d);
+  if (e != hipSuccess || !(d < bound)) ++failures;
+}
+
 // ChFSI of one k-point: the Bloch filter, then the complex Rayleigh-Ritz; the Ritz
 // vectors must be orthonormal and diagonalise H_k in the complex product.
 void scenario_rr_bloch(lrdm_ctx* ctx, lrdm_grid g, int N, int degree) {
@@ -653,6 +694,14 @@ int main(int argc, char** argv) {
     scenario_response(ctx, grid(7, 9, 11, 0.5), 70, 2, 1, LRDM_FP32);
     scenario_chfsi(ctx, grid(10, 9, 8, 0.45), 150, 5, LRDM_FP32);
     scenario_chfsi(ctx, grid(12, 12, 12, 0.45), 130, 4, LRDM_BF16X3);
+  }
+  if (which == "all" || which == "sweep") {
+    scenario_sweeps<double>(ctx, grid(20, 18, 11, 0.4), 3, 13, 5, 2, 4);
+    scenario_sweeps<float>(ctx, grid(20, 18, 13, 0.4), 2, 7, 4, 2, 13);
+    scenario_sweeps<double>(ctx, grid(48, 48, 7, 0.4), 2, 8, 3, 1, 3);      // 1152 groups
+    scenario_sweeps<float>(ctx, grid(80, 60, 7, 0.4), 1, 5, 3, 1, 7);       // 1200
+    scenario_sweeps<double>(ctx, grid(64, 64, 5, 0.4), 2, 5, 2, 2, 2);      // 2048
+    scenario_sweeps<float>(ctx, grid(16, 16, 10, 0.4), 2, 1, 5, 2, 10);
   }
   if (which == "all" || which == "adj") {
     scenario_backward(ctx, grid(20, 18, 13, 0.4), 150, 1, 2, LRDM_FP64);

@@ -100,11 +100,17 @@ FORMS = ("cheb_step", "cheb_sweep", "cheb_lds")
 
 # the form the filter's plan takes, by its launches: a single step gains nothing from LDS,
 # more steps of states that fit it do; few states of short columns, whose single steps take
-# as long as a column
+# as long as a column; sweeps with one group a thread, with two in up to three stages
+# (planes of 1024 to 1280 groups; in one batch and in two) and in two stages (up to 2048),
+# with a sweep of one step at the end; single steps where nx is odd
 @pytest.mark.parametrize("prec,n,N,degree,form,launches", [
     ("fp64", (24, 24, 24), 40, 1, "cheb_step", 1), ("fp64", (24, 24, 24), 40, 2, "cheb_lds", 1),
     ("fp32", (32, 32, 32), 5, 1, "cheb_step", 1), ("fp32", (32, 32, 32), 5, 64, "cheb_lds", 1),
     ("fp32", (64, 64, 12), 1, 20, "cheb_sweep", None), ("fp64", (48, 40, 13), 8, 5, "cheb_sweep", None),
+    ("fp64", (32, 32, 32), 300, 10, "cheb_sweep", None),
+    ("fp64", (48, 48, 48), 128, 7, "cheb_sweep", 3), ("fp64", (48, 48, 48), 300, 9, "cheb_sweep", 6),
+    ("fp64", (64, 64, 64), 128, 5, "cheb_sweep", 3), ("fp64", (60, 56, 50), 128, 7, "cheb_sweep", 4),
+    ("fp64", (31, 32, 34), 300, 3, "cheb_step", 2),
 ])
 def test_filter_takes_the_form_of_its_plan(prec, n, N, degree, form, launches):
     grid, gen = _grid(n), _gen(degree)
