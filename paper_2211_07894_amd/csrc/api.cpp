@@ -515,8 +515,7 @@ hipError_t run_filter(lrdm_ctx* ctx, const Grid3& g, const double* V, const T* X
   }
   // the vectorised forms read V in the storage type
   auto aligned = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-  const bool vec = cheb_vec_ok<T>(g) && aligned(X) && aligned(Y) &&
-                   (sizeof(T) == sizeof(float) || aligned(V));
+  const bool vec = cheb_vec_ok<T>(g) && aligned(X) && aligned(Y);
   const T* Vt = nullptr;
   if (vec) {
     if constexpr (sizeof(T) == sizeof(double)) {

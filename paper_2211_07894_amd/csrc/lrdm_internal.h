@@ -138,7 +138,7 @@ struct ChebPlan {
 template <typename T>
 ChebPlan cheb_plan(const Grid3& g, int N, int degree, int64_t room);
 // Y = the recurrence Y_{k+1} = a[k] (H - c0) Y_k + b[k] Y_{k-1} (b[0] = 0) from
-// Y_0 = X over all of a and b, with V in the storage type (Vt) and 16-byte aligned
+// Y_0 = X over all of a and b, with V in the storage type (Vt) and 16-byte aligned state
 // blocks: whole states in LDS, or sweeps with W of plan.states(N) states.
 template <typename T>
 hipError_t launch_cheb_lds(lrdm_ctx* ctx, const Grid3& g, const T* Vt, const T* X, T* Y, int N,

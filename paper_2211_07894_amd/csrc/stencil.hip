@@ -165,6 +165,11 @@ hipError_t launch_stencil(lrdm_ctx* ctx, const Grid3& g, const double* V, const 
 
 template <typename T, int W>
 using vec_t = T __attribute__((ext_vector_type(W)));
+// The same at any address of an element: V in double is the caller's.
+template <typename T, int W>
+struct Unaligned {
+  typedef vec_t<T, W> type __attribute__((aligned(sizeof(T))));
+};
 
 // Vectorised step; W points per 16-byte group of the input type TI, Q groups per
 // thread; arithmetic, V and Yout in T (T = TI for the recurrence, T = double for
@@ -186,7 +191,8 @@ __global__ __launch_bounds__(1024) void cheb_vec_kernel(const TI* __restrict__ Y
   const VI* yin = reinterpret_cast<const VI*>(Yin) + (int64_t)blockIdx.x * MG;
   const VI* yold = Yold ? reinterpret_cast<const VI*>(Yold) + (int64_t)blockIdx.x * MG : nullptr;
   V* yout = reinterpret_cast<V*>(Yout) + (int64_t)blockIdx.x * MG;
-  const V* vg = reinterpret_cast<const V*>(Vt);
+  using VU = typename Unaligned<T, W>::type;
+  const VU* vg = reinterpret_cast<const VU*>(Vt);
   const V zero = V(T(0));
   // Yin planes z-1 .. z+2, Yold and V planes z, z+1 of each owned group
   V prev[Q], cur[Q], next[Q], ahead[Q], o0[Q], o1[Q], v0[Q], v1[Q];
@@ -335,7 +341,8 @@ __global__ __launch_bounds__(1024) void cheb_lds_kernel(const T* __restrict__ X,
   const int64_t base = (int64_t)blockIdx.x * G * nz;
   const V* in = reinterpret_cast<const V*>(X) + base;
   V* out = reinterpret_cast<V*>(Y) + base;
-  const V* vg = reinterpret_cast<const V*>(Vt);
+  using VU = typename Unaligned<T, W>::type;
+  const VU* vg = reinterpret_cast<const VU*>(Vt);
   V cur[ZP], old[ZP];
 #pragma unroll
   for (int j = 0; j < ZP; ++j) {
@@ -433,7 +440,8 @@ __global__ __launch_bounds__(MAXT) void cheb_sweep_kernel(const T* __restrict__ 
   const V* B = reinterpret_cast<const V*>(Yb) + base;
   V* Op = reinterpret_cast<V*>(Yp) + base;
   V* Oq = reinterpret_cast<V*>(Yq) + base;
-  const V* vg = reinterpret_cast<const V*>(Vt);
+  using VU = typename Unaligned<T, W>::type;
+  const VU* vg = reinterpret_cast<const VU*>(Vt);
   const V zero = V(T(0));
   auto wrap = [&](int z) { return z < 0 ? z + nz : (z >= nz ? z - nz : z); };
   bool on[Q];

@@ -130,3 +130,21 @@ def test_filter_takes_the_form_of_its_plan(prec, n, N, degree, form, launches):
     # the scaled recurrence does not amplify: a few roundings a step
     err = float((Y[pick].double() - ref).norm() / ref.norm())
     assert err < 8 * degree * (2.0 ** -53 if prec == "fp64" else 2.0 ** -24)
+
+
+# V may lie at any address of a double: the same form, to the bit
+@pytest.mark.parametrize("n,N,degree,form", [
+    ((16, 16, 16), 20, 6, "cheb_lds"), ((48, 48, 48), 128, 6, "cheb_sweep"),
+    ((24, 24, 24), 40, 1, "cheb_step"),
+])
+def test_filter_with_V_at_any_address(n, N, degree, form):
+    grid, gen = _grid(n), _gen(degree)
+    V = _rand(gen, grid.M + 1)
+    X = _rand(gen, N, *grid.shape)
+    ctx = B.context(0)
+    ctx.profile_read(form)
+    ctx.profile(True)
+    Y = L.chfsi_filter(grid, V[1:], X, degree, 3.0, 34.0, -2.0)
+    ctx.profile(False)
+    assert ctx.profile_read(form)[1] > 0
+    assert torch.equal(Y, L.chfsi_filter(grid, V[1:].clone(), X, degree, 3.0, 34.0, -2.0))
