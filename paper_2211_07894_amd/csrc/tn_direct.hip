@@ -179,14 +179,19 @@ __global__ __launch_bounds__(64 * KW, 2) void tn_direct_kernel(
 
 int tn_direct_tile(int N) { return N <= 32 ? 32 : 64; }
 
-// Up to 384 states the 64-row tiles win at any size (no padding to 128 rows); beyond,
-// only where 128-row tiles and ranges of 4096 points leave workgroup slots of the
-// chip (two per CU) empty.
+// Up to 384 states the 64-row tiles win at any size (no padding to 128 rows), but for the
+// last 16, which 128-row tiles pad little, where rows are a multiple of 2 MB apart and the
+// 16 that a load reads fall together (384 states, 64^3: 1 direction 1028 us against 1228, 2
+// 1961 against 2001, 4 3747 against 3616, 16 14516 against 13750; 60^3, 16 directions 9886
+// against 10511; 368 states, 64^3, 16 directions 13823 against 13835); beyond, only where
+// 128-row tiles and ranges of 4096 points leave workgroup slots of the chip (two per CU)
+// empty.
 bool tn_direct_ok(int N, int64_t M, int batch) {
-  if (N <= 384) return true;
+  if (N <= 368) return true;
   const int nt = (N + kBlockEdge - 1) / kBlockEdge;
   const int items = nt * (nt + 1) / 2 * batch;
-  return (int64_t)items * tn_splits(items, M) < 384;
+  const int64_t wgs = (int64_t)items * tn_splits(items, M);
+  return N <= 384 ? wgs < 1024 || M % (1 << 18) != 0 : wgs < 384;
 }
 
 // 64 ranges of points (of at least 192 points): at 48^3 and 256 states 32, 64 and 128

@@ -208,3 +208,14 @@ def test_staged_ranges_fill_the_rounds(lib, M, N, batch):
     got = splits(N, M, batch, staged, 0)
     assert 1 <= got <= cap(N, M, batch, staged, 0)
     assert cost(got) <= cost(splits(N, M, batch, long_ranges, 0)) / 0.95
+
+
+def test_fp64_tiles_of_rows_megabytes_apart(lib):
+    """Tiles of 64 rows up to 384 states, but not for the last 16 where rows lie 2 MB apart
+    and 128-row tiles fill the chip."""
+    direct = lib._ZN4lrdm12tn_direct_okEili
+    direct.argtypes, direct.restype = [ctypes.c_int, ctypes.c_int64, ctypes.c_int], ctypes.c_bool
+    for N, M, batch, want in [(384, 64 ** 3, 8, False), (384, 60 ** 3, 8, True),
+                              (368, 64 ** 3, 8, True), (384, 64 ** 3, 1, True),
+                              (385, 60 ** 3, 8, False), (1024, 24 ** 3, 1, True)]:
+        assert direct(N, M, batch) == want, (N, M, batch)
