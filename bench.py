@@ -334,10 +334,12 @@ def main():
         # diag(dV) Psi and the back-projection sum_ij Psi_i Gamma_ij Psi_j are
         # symmetric in (i, j), M N^2 flops per direction each (the dense
         # equivalent, 2 M N^2, is reported beside it); a single filter step
-        # moves 3 M N s bytes
+        # moves 3 M N s bytes, a sweep of several steps reads two blocks of its
+        # batch and writes two (one workgroup a state and CU at this grid)
         "backproj": ("mfma", r * 1.0 * M * N * N),
         "proj": ("mfma", r * 1.0 * M * N * N),
         "cheb_step": ("hbm", 3.0 * M * N * s_bytes + 8.0 * M),
+        "cheb_sweep": ("hbm", 4.0 * M * min(N, 256) * s_bytes + 8.0 * M),
     }
     dense_equiv = {"backproj": r * (2.0 * M * N * N + 2.0 * M * N), "proj": r * 2.0 * M * N * N}
     dom = max(per_launch, key=lambda k: hr["kernels"][k][0])
@@ -360,7 +362,7 @@ def main():
     nblk = hr["active_blocks"]
     executed = {"backproj": products * r * (2.0 * M * 128 * 128 * nblk + 2.0 * M * N),
                 "proj": products * r * 2.0 * M * 128 * 128 * nblk,
-                "cheb_step": work}[dom]
+                "cheb_step": work, "cheb_sweep": work}[dom]
     ex_rate = executed / avg_s / (1e9 if bound == "hbm" else 1e12)
     roofline = dict(kernel=dom, bound=bound, achieved=round(achieved, 3), peak=peak, unit=unit,
                     frac=round(achieved / peak, 4),

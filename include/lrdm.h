@@ -522,14 +522,15 @@ lrdm_status lrdm_lowrank_step(lrdm_ctx* ctx, const lrdm_grid* grid, const void* 
  * point ranges whose FP64 partial sums are added afterwards): the response's
  * projection of r*nspin directions, the single-direction projection of
  * lrdm_lowrank_step, and the unweighted Gram product of subspace_rayleigh_ritz
- * (FP64 arithmetic).  Layouts (variants): 0, eight waves of 32 x 64 on a
- * 128 x 128 tile with the operands copied to LDS through a three-stage ring
- * (BF16X3: the unweighted operand split into its pieces once per call); 1, four
- * waves of 64 x 64 on the same tile with the operands staged through
- * registers; 2 (BF16X3 only), the ring kernel splitting both operands itself.
- * FP64 arithmetic has layout 0 only, FP32 layouts 0 and 1.  Each candidate
- * (layout, count of 1/4, 1/2, 1 and 2 times the default within 1..the
- * workspace's cap) is timed (one warm-up, three timed launches, hipEvents) on
+ * (FP64 arithmetic).  Layouts (variants): 0, the operands copied to LDS through
+ * a three-stage ring, FP32 eight waves of 32 x 32 on half a 128 x 128 tile,
+ * BF16X3 of 32 x 64 on a whole one (the unweighted operand split into its pieces
+ * once per call); 1, four waves of 64 x 64 on a tile with the operands staged
+ * through registers; 2 (BF16X3 only), the FP32 ring kernel splitting both operands
+ * itself.  Rows that do not start 16-byte aligned go through layout 1 whatever is
+ * chosen.  FP64 arithmetic has layout 0 only, FP32 layouts 0 and 1.  Each
+ * candidate (layout, count of 1/4, 1/2, 1 and 2 times the one that layout takes
+ * untuned, within 1..the workspace's cap) is timed (one warm-up, three timed launches, hipEvents) on
  * scratch blocks the call allocates and frees, and the fastest is kept on this
  * context for later calls of the same shape (the batched FP32 response sends a
  * system whose shape is tuned to layout 1 to its own launch).  splits and

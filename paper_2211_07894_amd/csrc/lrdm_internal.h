@@ -236,8 +236,8 @@ inline int tn_splits(int tiles_x_batch, int64_t M) {
   while (tiles_x_batch * s < 2048 && M / (2 * s) >= 4096) s *= 2;
   return s;
 }
-// The largest split count the partial-sum workspace is sized for: twice the
-// default, as long as each split keeps at least 2048 grid points.
+// The largest split count that the partial sums of a lean workspace hold (of a preferred
+// one: tn_range_cap): twice that, as long as each split keeps at least 2048 grid points.
 inline int tn_split_cap(int tiles_x_batch, int64_t M) {
   const int h = tn_splits(tiles_x_batch, M);
   int c = 2 * h;

@@ -310,11 +310,12 @@ struct ChebCoef {
 // of every point in LDS for the x and y neighbours, Y_k and Y_{k-1} of the
 // thread's own points in registers, so that a state is read once and written once.
 // Thread t owns group t % G of the plane on the ZP planes from (t / G) ZP (ZP divides nz; the z
-// neighbours come from its own registers, across its ends from LDS).  What bounds it
-// is LDS: about 34 bytes a point and step.  Each element is formed as the single
-// step forms it.  24^3 in FP64, degree 20: 32 states 147 -> 80 us,
-// 256 states 295 -> 96 us (single steps before; one workgroup a state, so 32 states
-// leave most of the chip idle: 4 us a step).
+// neighbours come from its own registers, across its ends from LDS).  Each element is
+// formed as the single step forms it.  A step of 24^3 in FP64 takes a workgroup 9100 cycles:
+// 3700 for the 34 bytes a point it moves through LDS, 2500 of FP64 instructions, the
+// rest latency between its two barriers (3.5 waves a SIMD).  Degree 20: 32 states 147 -> 76 us,
+// 256 states 295 -> 89 us (single steps before; one workgroup a state, so 32 states leave
+// most of the chip idle).
 constexpr int kLdsDegree = 64;     // steps one launch takes (coefficients by value)
 template <typename T>
 struct ChebCoefs {
@@ -406,8 +407,10 @@ __global__ __launch_bounds__(1024) void cheb_lds_kernel(const T* __restrict__ X,
 
 // S recurrence steps in one sweep over a run of z planes of one state, out of place:
 // stage 0 is Y_k (Yb), stage -1 Y_{k-1} (Ya, NULL for k = 0: the first step has no
-// Y_{k-1}), stage s = 1 .. S is Y_{k+s}, each element formed as the single step forms
-// it.  Only the last two stages are written (stage S-1 to Yp, stage S to Yq; the next
+// Y_{k-1}), stage s = 1 .. S is Y_{k+s}, each element formed by the single step's
+// operations (the compiler fuses the last sum the other way round, beta o rounded first, so
+// that the outputs agree to rounding, not to the bit: held to one order the two-group form
+// spills more and 24^3 through LDS takes 3 % longer).  Only the last two stages are written (stage S-1 to Yp, stage S to Yq; the next
 // sweep's inputs), so S steps move 4 M N s bytes, plus 2 S halo planes a run.
 // At iteration h stage s is formed on plane h - s: the plane above is stage s-1's
 // newest value (formed in this iteration), its own plane and the one below are
@@ -599,8 +602,14 @@ int cheb_sweep_stages(const Grid3& g) {
 // (0: as many as wanted).  Times in microseconds from the rates measured on the sweep
 // and the single step (19.5 bytes a nanosecond and CU, or 45 where the last-level cache
 // holds a batch's four blocks; 0.11 ns a point and stage, half a microsecond a plane):
-// the sweeps lose where halo planes outweigh the saved passes.  Against forced choices
-// of stages, run and batch at seventeen sizes the plan is within 6 % of the best.
+// the sweeps lose where halo planes outweigh the saved passes.  Against forced choices of
+// stages and run at seventeen sizes of 7 to 20 planes and more, degree 20, the plan is within
+// 8 % of the best from 128 states on; with few states up to 25 % off (64 x 64 x 12 in FP32, one
+// state: 92 us against 74).  Whole states in LDS are taken wherever they fit.  From 128 states
+// on they beat the best sweeps at every size (24^3 in FP64 81 us against 95, 256 states 89
+// against 135; 32^3 in FP32 93 against 100), and small ones at any count (16^3 24 against 40,
+// 24^3 in FP32 43 against 56); of the largest, up to some 60 states would go faster in sweeps
+// (24^3 in FP64, 32 states, 78 against 58; 32^3 in FP32 87 against 66), which the rule leaves.
 template <typename T>
 ChebPlan cheb_plan(const Grid3& g, int N, int degree, int64_t room) {
   constexpr int W = 16 / sizeof(T);
@@ -820,8 +829,6 @@ template hipError_t launch_cheb_step_vec<float>(lrdm_ctx*, const Grid3&, const f
                                                 const float*, const float*, float*, int, double,
                                                 double, double);
 
-namespace {
-}  // namespace
 
 template <typename T>
 hipError_t launch_cheb_step(lrdm_ctx* ctx, const Grid3& g, const double* V, const T* Yin,

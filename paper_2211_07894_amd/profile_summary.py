@@ -33,20 +33,27 @@ import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 
-# profiling-scope name -> (kernel-name pattern, source file) for each storage form
+# profiling-scope name -> (kernel-name pattern, source file) for each storage form, with the
+# kernel of the larger sizes first where there are two
+FILTER = {
+    t: {"cheb_step": [(rf"cheb_vec_kernel<{t}|cheb_plane_kernel<{t}, {t}", "stencil.hip")],
+        "cheb_sweep": [(rf"cheb_sweep_kernel<{t}", "stencil.hip")],
+        "cheb_lds": [(rf"cheb_lds_kernel<{t}", "stencil.hip")]}
+    for t in ("double", "float")
+}
 KERNELS = {
-    "fp64": {"proj": (r"tn_sym_f64_kernel<double, double", "gemm.hip"),
-             "backproj": (r"backproj_f64_kernel", "gemm.hip"),
-             "cheb_step": (r"cheb_vec_kernel<double|cheb_plane_kernel<double, double", "stencil.hip"),
-             "cheb_sweep": (r"cheb_sweep_kernel<double", "stencil.hip")},
-    "fp32": {"proj": (r"tn_sym_pipe_kernel<.*true>", "gemm_lp.hip"),
-             "backproj": (r"backproj_pipe_kernel", "gemm_lp.hip"),
-             "cheb_step": (r"cheb_vec_kernel<float|cheb_plane_kernel<float, float", "stencil.hip"),
-             "cheb_sweep": (r"cheb_sweep_kernel<float", "stencil.hip")},
-    "bf16x3": {"proj": (r"tn_sym_p3_kernel|tn_sym_pipe_kernel<.*true>", "gemm_lp.hip"),
-               "backproj": (r"backproj_p3w_kernel|backproj_p3_kernel|backproj_pipe_kernel", "gemm_lp.hip"),
-               "cheb_step": (r"cheb_vec_kernel<float|cheb_plane_kernel<float, float", "stencil.hip"),
-               "cheb_sweep": (r"cheb_sweep_kernel<float", "stencil.hip")},
+    "fp64": {"proj": [(r"tn_sym_f64_kernel<double, double", "gemm.hip"),
+                      (r"tn_direct_kernel<double, double, \d+, true", "tn_direct.hip")],
+             "backproj": [(r"backproj_f64_kernel", "gemm.hip"),
+                          (r"backproj_direct_kernel", "backproj_direct.hip")],
+             **FILTER["double"]},
+    "fp32": {"proj": [(r"tn_sym_pipe_kernel<.*true>", "gemm_lp.hip")],
+             "backproj": [(r"backproj_pipe_kernel", "gemm_lp.hip")],
+             **FILTER["float"]},
+    "bf16x3": {"proj": [(r"tn_sym_p3_kernel|tn_sym_pipe_kernel<.*true>", "gemm_lp.hip")],
+               "backproj": [(r"backproj_p3w_kernel|backproj_p3_kernel|backproj_pipe_kernel",
+                             "gemm_lp.hip")],
+               **FILTER["float"]},
 }
 CALIBRATION_BYTES = 1 << 30
 
@@ -136,12 +143,15 @@ def traffic(fetch_csv, write_csv, form, workload, command):
         factor = CALIBRATION_BYTES / (kib * 1024.0)   # true bytes per counted byte
         data[counter] = (disp, factor, kib)
     table = KERNELS[form]
-    for scope, (pat, src) in table.items():
-        per = {}
-        for counter, (disp, factor, _) in data.items():
-            vals = [v for n, v in disp.values() if re.search(pat, short(n))]
-            if vals:
-                per[counter] = statistics.median(vals) * 1024.0 * factor
+    for scope, kernels in table.items():
+        for pat, src in kernels:
+            per = {}
+            for counter, (disp, factor, _) in data.items():
+                vals = [v for n, v in disp.values() if re.search(pat, short(n))]
+                if vals:
+                    per[counter] = statistics.median(vals) * 1024.0 * factor
+            if len(per) == 2:
+                break
         if len(per) == 2:
             recs.append({
                 "kernel": scope, "workload": workload, "form": form, "source": src,
