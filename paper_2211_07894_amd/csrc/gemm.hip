@@ -574,12 +574,12 @@ size_t tn_part_bytes(int N, int64_t M, int batch, int order, int split_limit) {
 int tn_default_splits(int N, int64_t M, int batch, int order, int split_limit) {
   const int ntb = (N + BT - 1) / BT;
   const int items = ntb * (ntb + 1) / 2 * batch;
-  if (order == TN_STAGED_LP) {
-    // Staged through registers (rows at any address): a workgroup per tile and CU, so that
-    // the long ranges of tn_splits can fill a round that the count above overfills: 27 x 33 x
-    // 35, 800 states, 2 channels, 4 ranges (224 workgroups) 1390 us, 10 1645; 129 states, 1
-    // channel, 4 ranges 1394, 60 108 (FP32).  Groups of tiles that divide among the XCDs stay
-    // on one each (xcd.h).
+  if (order == TN_STAGED_LP || order == TN_SPLIT_LP) {
+    // Staged through registers (rows at any address), or BF16X3 splitting both operands: a
+    // workgroup per tile and CU, so that the long ranges of tn_splits can fill a round that
+    // the count above overfills: 27 x 33 x 35, 800 states, 2 channels, 4 ranges (224
+    // workgroups) 1390 us, 10 1645; 129 states, 1 channel, 4 ranges 1394, 60 108 (FP32).
+    // Groups of tiles that divide among the XCDs stay on one each (xcd.h).
     auto cost = [&](int s) {
       const int64_t groups = (int64_t)s * batch;
       const int64_t rounds = groups % 8 == 0 ? (groups / 8 * (items / batch) + 31) / 32
@@ -589,7 +589,7 @@ int tn_default_splits(int N, int64_t M, int batch, int order, int split_limit) {
     const int ring = tn_default_splits(N, M, batch, TN_ARITH_F32, split_limit);
     const int lengthy = std::min(tn_splits(items, M),
                                  tn_range_cap(N, M, batch, order, split_limit));
-    return cost(lengthy) < 0.95 * cost(ring) ? lengthy : ring;
+    return cost(lengthy) <= (order == TN_SPLIT_LP ? 1.0 : 0.95) * cost(ring) ? lengthy : ring;
   }
   if (order != TN_ARITH_F32) return tn_splits(items, M);
   const int cap = tn_range_cap(N, M, batch, order, split_limit);

@@ -443,16 +443,17 @@ constexpr int NJ = 2;                     // 16-column strips of a wave's 32 x 3
 constexpr int HT = HW * 64;               // and threads
 constexpr int HB = HR * KT * 4;           // bytes of its row operand's tile (8 KB)
 
-// The wave's operands of one K-tile (rows of its 32 x 32 part), read from LDS
+// The wave's operands of one K-tile (rows of its 32 x (16 J) part), read from LDS
 // before the next copies are issued: an LDS read after a global->LDS copy would
 // make the compiler wait for every copy in flight.  weight() scales B's column k
 // by w[k] (FP32 product of the rounded weight).
+template <int J>
 struct PipeFrag {
-  float a[2][8], b[NJ][8];
+  float a[2][8], b[J][8];
   __device__ inline void load(const unsigned char* At, const unsigned char* Bt, int wr, int wc,
                               int lane) {
     frag_sw<2>(At, wr * 32, lane, a);
-    frag_sw<NJ>(Bt, wc * 16 * NJ, lane, b);
+    frag_sw<J>(Bt, wc * 16 * J, lane, b);
   }
   // wt: the weights of the K-tile in LDS
   __device__ inline void weight(const unsigned char* wt, int lane) {
@@ -468,34 +469,34 @@ struct PipeFrag {
       wf[2 * h + 1] = (float)y[1];
     }
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
+    for (int j = 0; j < J; ++j)
 #pragma unroll
       for (int e = 0; e < 8; ++e) b[j][e] *= wf[e];
   }
 };
 
-// acc += scale * A B^T over one K-tile of the wave's 32 x 32 part (registers only).
-template <Core C>
-__device__ inline void kt_step_pipe(PipeFrag& f, double scale, double (&acc)[2][NJ][4]) {
-  f4 c[2][NJ];
+// acc += scale * A B^T over one K-tile of the wave's 32 x (16 J) part (registers only).
+template <Core C, int J>
+__device__ inline void kt_step_pipe(PipeFrag<J>& f, double scale, double (&acc)[2][J][4]) {
+  f4 c[2][J];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) c[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < J; ++j) c[i][j] = f4{0.f, 0.f, 0.f, 0.f};
   if constexpr (C == Core::F32) {
 #pragma unroll
     for (int s = 0; s < 8; ++s)
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) c[i][j] = mfma_f32(f.a[i][s], f.b[j][s], c[i][j]);
+        for (int j = 0; j < J; ++j) c[i][j] = mfma_f32(f.a[i][s], f.b[j][s], c[i][j]);
   } else {
     constexpr int NP = (C == Core::BF3) ? 3 : 2;
     bf8 pa[2][NP];
 #pragma unroll
     for (int i = 0; i < 2; ++i) split<NP>(f.a[i], pa[i]);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
+    for (int j = 0; j < J; ++j) {
       bf8 pb[NP];
       split<NP>(f.b[j], pb);
 #pragma unroll
@@ -514,7 +515,7 @@ __device__ inline void kt_step_pipe(PipeFrag& f, double scale, double (&acc)[2][
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
+    for (int j = 0; j < J; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[i][j][v] += scale * (double)c[i][j][v];
 }
@@ -555,22 +556,27 @@ __device__ inline void zero_pipe(double (&acc)[2][4][4]) {
       for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.0;
 }
 
-// tn_sym, pipelined: partial layout of tn_sym_lp_kernel, two workgroups per tile (rows
-// 0..63, 64..127).  Requires M a multiple of 4 and 16-byte aligned A, B and weight
-// rows.  W: B weighted by w.  The body, for workgroup `lin` of the launch's grid (the
+// tn_sym, pipelined: partial layout of tn_sym_lp_kernel.  HALF: two workgroups per tile
+// (rows 0..63, 64..127), the FP32 form.  BF16X3, which splits both operands here, takes
+// whole tiles, waves of 32 x 64 and one workgroup a CU, where half tiles would share CUs: they
+// split the columns twice (50 x 50 x 49, 512 states, 8 directions 3.0 ms against 4.7; 48^3, zone
+// response of 256 states, 4 k-points, 8 directions 20.5 against 25.4).  Requires M a multiple of 4 and 16-byte aligned A, B and weight rows.  W: B
+// weighted by w.  The body, for workgroup `lin` of the launch's grid (the
 // fused launch of several systems passes each system's own workgroup index).
-template <Core C, bool W>
+template <Core C, bool W, bool HALF>
 __device__ inline void tn_sym_pipe_body(
     int lin, const float* __restrict__ A, const float* __restrict__ B,
     const double* __restrict__ w, int64_t w_stride, int N, int64_t M, int nspin, int ntb,
     int64_t kchunk, int nsplit, int batch, const unsigned char* __restrict__ active,
     const float* __restrict__ zeros, double* __restrict__ part) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_pipe[];
-  constexpr int SB = HB + TB + (W ? 1024 : 0);  // bytes of one stage
+  constexpr int ROWS = HALF ? HR : BT, J = HALF ? NJ : 4, COLS = HALF ? 4 : 2;  // waves a row
+  constexpr int RB = ROWS * KT * 4;             // bytes of the row operand's tile
+  constexpr int SB = RB + TB + (W ? 1024 : 0);  // bytes of one stage
   const int ntiles = ntb * (ntb + 1) / 2;
   int group, item;
-  xcd_map(lin, nsplit * batch, 2 * ntiles, group, item);
-  const int tile = item >> 1, half = item & 1;
+  xcd_map(lin, nsplit * batch, HALF ? 2 * ntiles : ntiles, group, item);
+  const int tile = HALF ? item >> 1 : item, half = HALF ? item & 1 : 0;
   const int sp = group % nsplit, b = group / nsplit;
   int ti = 0, rem = tile;
   while (rem >= ntb - ti) { rem -= ntb - ti; ++ti; }
@@ -586,71 +592,73 @@ __device__ inline void tn_sym_pipe_body(
   const int64_t kend = block_active(active, c, ntb, ti, tj) ? min(M, kbeg + kchunk) : kbeg;
   const int nk = kbeg < kend ? (int)((kend - kbeg + KT - 1) / KT) : 0;
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int wr = wid >> 2, wc = wid & 3;
+  const int wr = wid / COLS, wc = wid % COLS;
   // the quadrant below the diagonal of a diagonal tile is never read
-  const bool work = !(ti == tj && half == 1 && wc < 2);
+  const bool work = !(HALF && ti == tj && half == 1 && wc < 2);
   // Every stage issues the same copies (zeros past the end), so the count of
-  // copies in flight per wave is the same at every wait: 3 per stage, plus the
+  // copies in flight per wave is the same at every wait: 3 or 4 per stage, plus the
   // weights in wave 0.
-  const float* abase[HR / 8 / HW];
+  constexpr int COPIES = (ROWS + BT) / 8 / HW;
+  const float* abase[ROWS / 8 / HW];
   const float* bbase[BT / 8 / HW];
-  dma_bases<HR, HW>(Ac, M, N, r0, wid, lane, abase);
+  dma_bases<ROWS, HW>(Ac, M, N, r0, wid, lane, abase);
   dma_bases<BT, HW>(Bc, M, N, (int64_t)tj * BT, wid, lane, bbase);
   const double* wbase = W ? wb + 2 * (lane & 15) : nullptr;
   auto issue = [&](int t) {
     unsigned char* st = smem_pipe + (t % NST) * SB;
     const int64_t k0 = kbeg + (int64_t)t * KT;
-    if (k0 + KT <= kend) {
-      dma_full<HR, HW>(abase, k0, st, wid);
-      dma_full<BT, HW>(bbase, k0, st + HB, wid);
-      if (W && wid == 0) dma16(wbase + k0, st + HB + TB);
+    if (HALF && k0 + KT <= kend) {
+      dma_full<ROWS, HW>(abase, k0, st, wid);
+      dma_full<BT, HW>(bbase, k0, st + RB, wid);
+      if (W && wid == 0) dma16(wbase + k0, st + RB + TB);
       return;
     }
     const int64_t ke = t < nk ? kend : k0;
-    dma_rows<HR, HW>(Ac, M, N, r0, k0, ke, zeros, st, wid, lane);
-    dma_rows<BT, HW>(Bc, M, N, (int64_t)tj * BT, k0, ke, zeros, st + HB, wid, lane);
-    if (W && wid == 0) dma_weights(wb, k0, ke, zeros, st + HB + TB, lane);
+    dma_rows<ROWS, HW>(Ac, M, N, r0, k0, ke, zeros, st, wid, lane);
+    dma_rows<BT, HW>(Bc, M, N, (int64_t)tj * BT, k0, ke, zeros, st + RB, wid, lane);
+    if (W && wid == 0) dma_weights(wb, k0, ke, zeros, st + RB + TB, lane);
   };
-  double acc[2][NJ][4];
+  double acc[2][J][4];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
+    for (int j = 0; j < J; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.0;
   issue(0);
   issue(1);
   for (int t = 0; t < nk; ++t) {
-    if (W && wid == 0) wait_stage<4>(); else wait_stage<3>();
+    if (W && wid == 0) wait_stage<COPIES + 1>(); else wait_stage<COPIES>();
     const unsigned char* st = smem_pipe + (t % NST) * SB;
-    PipeFrag f;
-    f.load(st, st + HB, wr, wc, lane);
-    if (W) f.weight(st + HB + TB, lane);
+    PipeFrag<J> f;
+    f.load(st, st + RB, wr, wc, lane);
+    if (W) f.weight(st + RB + TB, lane);
     compiler_fence();
+    if (!HALF) issue(t + 2);
     if (work) kt_step_pipe<C>(f, 1.0, acc);
-    issue(t + 2);
+    if (HALF) issue(t + 2);
   }
   wait_stage<0>();
   double* out = part + (((int64_t)b * nsplit + sp) * ntiles + tile) * (BT * BT) + half * HR * BT;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
+    for (int j = 0; j < J; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int row = wr * 32 + i * 16 + 4 * (lane >> 4) + v;
-        const int col = wc * 16 * NJ + j * 16 + (lane & 15);
+        const int col = wc * 16 * J + j * 16 + (lane & 15);
         out[row * BT + col] = acc[i][j][v];
       }
 }
 
-template <Core C, bool W>
-__global__ __launch_bounds__(HT, 4) void tn_sym_pipe_kernel(
+template <Core C, bool W, bool HALF>
+__global__ __launch_bounds__(HT, HALF ? 4 : 1) void tn_sym_pipe_kernel(
     const float* __restrict__ A, const float* __restrict__ B, const double* __restrict__ w,
     int64_t w_stride, int N, int64_t M, int nspin, int ntb, int64_t kchunk, int nsplit, int batch,
     const unsigned char* __restrict__ active, const float* __restrict__ zeros,
     double* __restrict__ part) {
-  tn_sym_pipe_body<C, W>(blockIdx.x, A, B, w, w_stride, N, M, nspin, ntb, kchunk, nsplit, batch,
+  tn_sym_pipe_body<C, W, HALF>(blockIdx.x, A, B, w, w_stride, N, M, nspin, ntb, kchunk, nsplit, batch,
                          active, zeros, part);
 }
 
@@ -709,7 +717,7 @@ __device__ inline void backproj_pipe_body(
     for (int t = 0; t < nk; ++t) {
       wait_stage<3>();
       const unsigned char* st = smem_pipe + (t % NST) * SB;
-      PipeFrag f;
+      PipeFrag<NJ> f;
       f.load(st, st + HB, wr, wc, lane);
       compiler_fence();
       int J;
@@ -809,7 +817,7 @@ __global__ __launch_bounds__(HT, 4) void tn_sym_fused_kernel(const FusedProj t,
   const int s = fused_system(t.wg0, t.nsys, blockIdx.x);
   const int lin = blockIdx.x - t.wg0[s];
   if (lin >= t.used[s]) return;
-  tn_sym_pipe_body<Core::F32, true>(lin, t.A[s], t.A[s], t.w[s], t.M[s], t.N[s], t.M[s],
+  tn_sym_pipe_body<Core::F32, true, true>(lin, t.A[s], t.A[s], t.w[s], t.M[s], t.N[s], t.M[s],
                                     t.nspin[s], t.ntb[s], t.kchunk[s], t.nsplit[s], t.batch[s],
                                     t.active[s], zeros, t.part[s]);
 }
@@ -932,7 +940,7 @@ __global__ __launch_bounds__(HT, 4) void adj_psi_pipe_kernel(
     }
     wait_stage<3>();
     const unsigned char* st = smem_pipe + (t % NST) * SB;
-    PipeFrag f;
+    PipeFrag<NJ> f;
     f.load(st, st + HB, wr, wc, lane);
     compiler_fence();
     f4 cc[2][NJ];
@@ -1728,7 +1736,8 @@ int tn_lp_order(int arith, int variant, bool weighted, bool same, bool aligned, 
   if (variant == TN_VAR_STAGED || M % 4 != 0 || !aligned) return TN_STAGED_LP;
   const bool pieces = arith == TN_ARITH_BF16X3 && variant == TN_VAR_DEFAULT && weighted && same &&
                       M % 8 == 0 && nspin <= 2;
-  return pieces ? TN_ARITH_BF16X3 : TN_ARITH_F32;
+  if (pieces) return TN_ARITH_BF16X3;
+  return arith == TN_ARITH_BF16X3 ? TN_SPLIT_LP : TN_ARITH_F32;
 }
 
 template <>
@@ -1783,11 +1792,14 @@ hipError_t launch_tn_sym<float>(lrdm_ctx* ctx, const float* A, const float* B, c
     }
     return launch_tn_reduce(ctx, part, N, BT, ns * parts, batch, H);
   }
-  const int smem = NST * (HB + TB + (w ? 1024 : 0));
+  // workgroups on half tiles: FP32, and BF16X3 while each has a CU of its own (34 x 34 x 33,
+  // 48 states: 1 direction 46 us against 53 on whole tiles, 8 146 against 122)
+  const bool half = order == TN_ARITH_F32 || 2 * grd <= 256;
+  const int smem = NST * ((half ? HB : TB) + TB + (w ? 1024 : 0));
   auto run_pipe = [&](auto kernel) -> hipError_t {
     LRDM_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                  hipFuncAttributeMaxDynamicSharedMemorySize, smem));
-    kernel<<<2 * grd, HT, smem, ctx->stream>>>(A, B, w, w_stride, N, M, nspin, ntb, kchunk, ns,
+    kernel<<<half ? 2 * grd : grd, HT, smem, ctx->stream>>>(A, B, w, w_stride, N, M, nspin, ntb, kchunk, ns,
                                                batch, active, ctx->zeros, part);
     return hipGetLastError();
   };
@@ -1801,12 +1813,15 @@ hipError_t launch_tn_sym<float>(lrdm_ctx* ctx, const float* A, const float* B, c
     const bool bf = (prec == LRDM_BF16X3);
     if (order == TN_STAGED_LP)
       LRDM_HIP(bf ? run_staged(tn_sym_lp_kernel<Core::BF3>) : run_staged(tn_sym_lp_kernel<Core::F32>));
-    else if (w)
-      LRDM_HIP(bf ? run_pipe(tn_sym_pipe_kernel<Core::BF3, true>)
-                  : run_pipe(tn_sym_pipe_kernel<Core::F32, true>));
+    else if (!bf)
+      LRDM_HIP(w ? run_pipe(tn_sym_pipe_kernel<Core::F32, true, true>)
+                 : run_pipe(tn_sym_pipe_kernel<Core::F32, false, true>));
+    else if (half)
+      LRDM_HIP(w ? run_pipe(tn_sym_pipe_kernel<Core::BF3, true, true>)
+                 : run_pipe(tn_sym_pipe_kernel<Core::BF3, false, true>));
     else
-      LRDM_HIP(bf ? run_pipe(tn_sym_pipe_kernel<Core::BF3, false>)
-                  : run_pipe(tn_sym_pipe_kernel<Core::F32, false>));
+      LRDM_HIP(w ? run_pipe(tn_sym_pipe_kernel<Core::BF3, true, false>)
+                 : run_pipe(tn_sym_pipe_kernel<Core::BF3, false, false>));
   }
   return launch_tn_reduce(ctx, part, N, BT, ns, batch, H);
 }

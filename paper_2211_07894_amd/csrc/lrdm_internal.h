@@ -252,9 +252,10 @@ hipError_t noalloc_scratch(int device, void** out);
 
 // Arithmetic of a projection contraction, part of the autotuner's key.
 // Not in a key: TN_ORDERED_F64, FP64 arithmetic on an FP32 block, which keeps one order of
-// its sums; TN_STAGED_LP, either FP32 arithmetic staged through registers.
+// its sums; TN_STAGED_LP, either FP32 arithmetic staged through registers; TN_SPLIT_LP,
+// BF16X3 splitting both operands in the kernel.
 enum { TN_ARITH_F64 = 0, TN_ARITH_F32 = 1, TN_ARITH_BF16X3 = 2, TN_ORDERED_F64 = 3,
-       TN_STAGED_LP = 4 };
+       TN_STAGED_LP = 4, TN_SPLIT_LP = 5 };
 // Kernel variants of the FP32-storage projection (tile and wave layout):
 //  TN_VAR_DEFAULT  operands copied to LDS through a three-stage ring: FP32 8 waves of
 //                  32 x 32 on half a 128 x 128 tile, BF16X3 of 32 x 64 on a whole one
@@ -274,8 +275,8 @@ enum { BP_VAR_NARROW = 0, BP_VAR_WIDE = 1 };
 int tn_variant(const lrdm_ctx* ctx, int N, int64_t M, int batch, int arith, bool weighted);
 // The split count a projection launch uses: the autotuned one for this shape and
 // arithmetic if lrdm_autotune chose one, else the default of `order`: which sums bind the
-// count and its room, and how the workgroups fill the chip (TN_ARITH_F32 and TN_STAGED_LP
-// where FP32 sums end with each K-tile; tn_lp_order says it for the FP32-storage forms).
+// count and its room, and how the workgroups fill the chip (TN_ARITH_F32, TN_STAGED_LP and
+// TN_SPLIT_LP where FP32 sums end with each K-tile; tn_lp_order says it for the FP32-storage forms).
 int tn_lp_order(int arith, int variant, bool weighted, bool same, bool aligned, int64_t M,
                 int nspin);
 int tn_default_splits(int N, int64_t M, int batch, int order, int split_limit);

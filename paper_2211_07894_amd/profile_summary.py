@@ -47,10 +47,10 @@ KERNELS = {
              "backproj": [(r"backproj_f64_kernel", "gemm.hip"),
                           (r"backproj_direct_kernel", "backproj_direct.hip")],
              **FILTER["double"]},
-    "fp32": {"proj": [(r"tn_sym_pipe_kernel<.*true>", "gemm_lp.hip")],
+    "fp32": {"proj": [(r"tn_sym_pipe_kernel<[^,]*, true", "gemm_lp.hip")],
              "backproj": [(r"backproj_pipe_kernel", "gemm_lp.hip")],
              **FILTER["float"]},
-    "bf16x3": {"proj": [(r"tn_sym_p3_kernel|tn_sym_pipe_kernel<.*true>", "gemm_lp.hip")],
+    "bf16x3": {"proj": [(r"tn_sym_p3_kernel|tn_sym_pipe_kernel<[^,]*, true", "gemm_lp.hip")],
                "backproj": [(r"backproj_p3w_kernel|backproj_p3_kernel|backproj_pipe_kernel",
                              "gemm_lp.hip")],
                **FILTER["float"]},
