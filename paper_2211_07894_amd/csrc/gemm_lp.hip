@@ -1202,7 +1202,7 @@ __global__ __launch_bounds__(PT, 1) void adj_psi_p3_kernel(
 
 // Projection, BF16X3, pre-split B: H[b] = (w o A_c) B_c^T with A = B = Psi; A
 // FP32 tiles weighted and split in the kernel, B from the pieces P3
-// [nspin][3][N][M].  Same grid and partial layout as tn_sym_pipe_kernel; M a
+// [nspin][3][N][M].  One workgroup per tile, partial layout of tn_sym_lp_kernel; M a
 // multiple of 8, aligned rows.  PARTS: blockIdx.y names a part of kpart points of the
 // range; the form without keeps its 236 registers and the 1 % that the other 12 cost
 // (64^3, 1024 states, 16 directions: 26.3 ms against 26.6).
