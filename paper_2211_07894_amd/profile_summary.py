@@ -36,7 +36,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 # profiling-scope name -> (kernel-name pattern, source file) for each storage form, with the
 # kernel of the larger sizes first where there are two
 FILTER = {
-    t: {"cheb_step": [(rf"cheb_vec_kernel<{t}|cheb_plane_kernel<{t}, {t}", "stencil.hip")],
+    t: {"cheb_step": [(rf"cheb_(vec|plane)_kernel<{t}, {t}", "stencil.hip")],
         "cheb_sweep": [(rf"cheb_sweep_kernel<{t}", "stencil.hip")],
         "cheb_lds": [(rf"cheb_lds_kernel<{t}", "stencil.hip")]}
     for t in ("double", "float")
